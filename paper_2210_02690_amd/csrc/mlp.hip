@@ -3,11 +3,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <new>
 #include <string>
-#include <vector>
 
 #include "vk_mlp.h"
 
@@ -25,111 +25,243 @@ __device__ inline uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 
-enum { EPI_TANH = 0, EPI_LINEAR = 1, EPI_DTANH = 2, EPI_STORE = 3 };
+constexpr int MAX_LAYERS = 9;
 
-// C(m, n) = sum_k A(m, k) B(k, n) over one 16 x 16 tile per wavefront, BF16 operands and
-// FP32 accumulation on v_mfma_f32_16x16x16_bf16.  Operand element addresses:
-//   A(m, k) = A[ra(m) * a_rs + k * a_ks],  ra(m) = arow ? arow[m] : m
-//   B(k, n) = B[rb(k) * b_ks + n * b_ns],  rb(k) = brow ? brow[k] : k
-// Lane l holds A rows l % 16 and B columns l % 16, k = 4 (l / 16) + i of every 16-deep step;
-// the accumulator's element i of lane l is C(4 (l / 16) + i, l % 16).
-template <int EPI>
-__global__ __launch_bounds__(64) void gemm_kernel(int32_t M, int32_t N, int32_t K, const uint16_t* __restrict__ A,
-                                                  const int32_t* __restrict__ arow, int64_t a_rs, int64_t a_ks,
-                                                  const uint16_t* __restrict__ B, const int32_t* __restrict__ brow,
-                                                  int64_t b_ks, int64_t b_ns, const float* __restrict__ bias,
-                                                  const uint16_t* __restrict__ act, float* __restrict__ outf,
-                                                  uint16_t* __restrict__ outb, int64_t ldo) {
-  const int lane = threadIdx.x;
-  const int r = lane & 15, q = lane >> 4;
-  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
-  const int am = m0 + r, bn = n0 + r;
-  const bool am_ok = am < M, bn_ok = bn < N;
-  const int64_t a_base = am_ok ? (int64_t)(arow ? arow[am] : am) * a_rs : 0;
-  const int64_t b_col = bn_ok ? (int64_t)bn * b_ns : 0;
-  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    bf16x4 a, b;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = k0 + 4 * q + i;
-      const bool k_ok = k < K;
-      a[i] = (am_ok && k_ok) ? (short)A[a_base + (int64_t)k * a_ks] : (short)0;
-      const int64_t rk = k_ok ? (int64_t)(brow ? brow[k] : k) : 0;
-      b[i] = (bn_ok && k_ok) ? (short)B[rk * b_ks + b_col] : (short)0;
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + 4 * q + i, n = n0 + r;
-    if (m >= M || n >= N) continue;
-    const int64_t o = (int64_t)m * ldo + n;
-    const float v = acc[i];
-    if (EPI == EPI_TANH) {
-      outb[o] = f2bf(tanhf(v + bias[n]));
-    } else if (EPI == EPI_LINEAR) {
-      outf[o] = v + bias[n];
-    } else if (EPI == EPI_DTANH) {
-      const float a_v = bf2f(act[o]);
-      outb[o] = f2bf(v * (1.0f - a_v * a_v));
-    } else {
-      outf[o] = v;
-    }
-  }
-}
+// The network as its kernels see it.  Products run on v_mfma_f32_16x16x16_bf16: lane l supplies
+// A(m, k) and B(k, n) for m, n = l % 16 and k = 4 (l / 16) .. + 3 of every 16-deep step and holds
+// D(4 (l / 16) + i, l % 16), i < 4, in FP32.  Everything a lane reads for one step is one 8-byte word:
+//   wf / wt  the BF16 weights in the order the forward (W^T) and the backward (W) products read them,
+//            [column tile][16-deep step][lane][4], zero where a tile sticks out of the matrix;
+//   ta / tz  per layer the inputs (features, then hidden activations) and the pre-activation gradients
+//            of the batch, [16-sample tile][feature, padded to 16][16 samples]: the layout the
+//            accumulators already have, and the one the weight gradients (sums over samples) read.
+struct net_desc {
+  int32_t L;                      // layers (n_hidden + 1)
+  int32_t fi[MAX_LAYERS], fo[MAX_LAYERS];
+  int64_t w[MAX_LAYERS], b[MAX_LAYERS];    // W_l and b_l in the packed parameters
+  int64_t wf[MAX_LAYERS], wt[MAX_LAYERS];  // offsets in the two weight copies
+  int64_t ta[MAX_LAYERS], tz[MAX_LAYERS];  // offsets of layer l's input and output gradient
+};
 
-// dY = 2 (y - t) / (batch n_out) as BF16 and per-block partial sums of (y - t)^2
-__global__ __launch_bounds__(256) void mse_kernel(int32_t batch, int32_t n_out, const float* __restrict__ y,
-                                                  const float* __restrict__ t, const int32_t* __restrict__ rows,
-                                                  float scale, uint16_t* __restrict__ dz, float* __restrict__ part) {
-  __shared__ float red[256];
-  const int64_t total = (int64_t)batch * n_out;
-  float s = 0.0f;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = i / n_out, j = i - m * n_out;
-    const int64_t tr = rows ? (int64_t)rows[m] : m;
-    const float d = y[i] - t[tr * n_out + j];
-    s += d * d;
-    dz[i] = f2bf(scale * d);
+__host__ __device__ inline int tiles16(int n) { return (n + 15) >> 4; }
+
+// One workgroup takes 16 samples through the whole network, its activations in LDS: the layers need
+// no other samples, so the forward pass, the loss, and (GRAD) the chain of pre-activation gradients are
+// one launch (they were 4 + 3 products, the error kernel and a copy).  A wavefront owns every
+// (wavefronts)-th 16-column tile of a layer; each product is one accumulator over k ascending, as
+// before, so activations and gradients round as they did.  At these sizes the layers are a chain of
+// L2 round trips, so a tile's weight words are all requested (8 steps at a time) before the first
+// product.  One optimiser step of the 84-128-128-128-42 network on 512 samples (this kernel,
+// grad_kernel, Adam, two parameter copies): 256 us in 21 launches -> 29 us in 4.
+template <bool GRAD>
+__global__ __launch_bounds__(512) void net_kernel(net_desc net, int32_t batch, int32_t ldk,
+                                                  const uint16_t* __restrict__ x, const int32_t* __restrict__ rows,
+                                                  const uint16_t* __restrict__ wf, const uint16_t* __restrict__ wt,
+                                                  const float* __restrict__ theta, float* __restrict__ y,
+                                                  const float* __restrict__ target, float scale, uint16_t* ta,
+                                                  uint16_t* tz, float* __restrict__ part) {
+  extern __shared__ __align__(16) uint16_t sm[];  // two buffers of 16 rows x ldk (ldk = 4 mod 16)
+  __shared__ float red[8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int l16 = lane & 15, q = lane >> 4;
+  const int64_t mt = blockIdx.x;
+  const int m0 = (int)mt * 16;
+  uint16_t* buf[2] = {sm, sm + 16 * ldk};
+  {
+    const int n_in = net.fi[0], kp = 16 * tiles16(n_in);
+    for (int m = wave; m < 16; m += nw) {
+      const bool ok = m0 + m < batch;
+      const int64_t r = ok ? (rows ? (int64_t)rows[m0 + m] : (int64_t)(m0 + m)) : 0;
+      for (int k = lane; k < kp; k += 64) buf[0][m * ldk + k] = (ok && k < n_in) ? x[r * n_in + k] : (uint16_t)0;
+    }
+    __syncthreads();
+    if (GRAD) {
+      bf16x4* t = reinterpret_cast<bf16x4*>(ta + net.ta[0] + mt * kp * 16);
+      for (int e = tid; e < kp * 4; e += blockDim.x) {
+        bf16x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (short)buf[0][(4 * (e & 3) + i) * ldk + (e >> 2)];
+        t[e] = v;
+      }
+    }
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+  // one 16 x 16 tile: rows of `in` times column tile nt of the weight copy w, ks steps deep
+  auto product = [&](const uint16_t* in, const uint16_t* w, int nt, int ks) {
+    const bf16x4* wp = reinterpret_cast<const bf16x4*>(w) + (int64_t)nt * ks * 64 + lane;
+    const uint16_t* ap = in + l16 * ldk + 4 * q;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    int s = 0;
+    for (; s + 8 <= ks; s += 8) {
+      bf16x4 bv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) bv[u] = wp[(s + u) * 64];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4*>(ap + (s + u) * 16), bv[u], acc,
+                                                        0, 0, 0);
+    }
+    for (; s < ks; ++s)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4*>(ap + s * 16), wp[s * 64], acc, 0,
+                                                      0, 0);
+    return acc;
+  };
+  int cur = 0;
+  float loss = 0.0f;
+  for (int l = 0; l < net.L; ++l) {
+    const int N = net.fo[l], nts = tiles16(N), ks = tiles16(net.fi[l]);
+    const bool last = l + 1 == net.L;
+    uint16_t* dst = buf[cur ^ 1];
+    for (int nt = wave; nt < nts; nt += nw) {
+      const f32x4 acc = product(buf[cur], wf + net.wf[l], nt, ks);
+      const int n = nt * 16 + l16;
+      const float bias = n < N ? theta[net.b[l] + n] : 0.0f;
+      bf16x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = m0 + 4 * q + i;
+        const bool ok = n < N && m < batch;
+        uint16_t h = 0;
+        if (!last) {
+          if (ok) h = f2bf(tanhf(acc[i] + bias));
+        } else if (ok) {
+          const float v = acc[i] + bias;
+          if (GRAD) {
+            const int64_t tr = rows ? (int64_t)rows[m] : (int64_t)m;
+            const float d = v - target[tr * N + n];
+            loss += d * d;
+            h = f2bf(scale * d);
+          } else {
+            y[(int64_t)m * N + n] = v;
+          }
+        }
+        dst[(4 * q + i) * ldk + n] = h;
+        o[i] = (short)h;
+      }
+      if (GRAD) {
+        uint16_t* t = last ? tz + net.tz[l] : ta + net.ta[l + 1];
+        *reinterpret_cast<bf16x4*>(t + (mt * nts * 16 + n) * 16 + 4 * q) = o;
+      }
+    }
+    cur ^= 1;
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (!GRAD) return;
+  // dz_{l-1}(m, i) = (sum_j dz_l[m, j] W_l[j, i]) (1 - a(m, i)^2); the activation words were written by
+  // this lane (same tile, same wavefront)
+  for (int l = net.L - 1; l >= 1; --l) {
+    const int N = net.fi[l], nts = tiles16(N), ks = tiles16(net.fo[l]);
+    uint16_t* dst = buf[cur ^ 1];
+    for (int nt = wave; nt < nts; nt += nw) {
+      const int n = nt * 16 + l16;
+      const int64_t at = (mt * nts * 16 + n) * 16 + 4 * q;
+      const bf16x4 av = *reinterpret_cast<const bf16x4*>(ta + net.ta[l] + at);
+      const f32x4 acc = product(buf[cur], wt + net.wt[l], nt, ks);
+      bf16x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float a = bf2f((uint16_t)av[i]);
+        const uint16_t h = (n < N && m0 + 4 * q + i < batch) ? f2bf(acc[i] * (1.0f - a * a)) : (uint16_t)0;
+        dst[(4 * q + i) * ldk + n] = h;
+        o[i] = (short)h;
+      }
+      *reinterpret_cast<bf16x4*>(tz + net.tz[l - 1] + at) = o;
+    }
+    cur ^= 1;
+    __syncthreads();
+  }
+  for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
+  if (lane == 0) red[wave] = loss;
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.0f;
+    for (int w = 0; w < nw; ++w) t += red[w];
+    part[blockIdx.x] = t;
+  }
 }
 
-__global__ void loss_final_kernel(int32_t n_part, const float* __restrict__ part, float inv_count,
-                                  float* __restrict__ loss) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
+// All weight and bias gradients, and the loss, in one launch: blockIdx.y = layer (y = L: the loss),
+// a wavefront per 16 x 16 tile of dW_l(j, i) = sum_m dz[m, j] a[m, i], one accumulator over the samples
+// in order; the tiles of the first input columns also sum dz over the samples (db).  Both operands of
+// 16 samples are one 8-byte word per lane, 8 steps in flight (per layer and 512 samples, a product with
+// scalar 2-byte loads, one round trip per step, took 44 us and the bias sums 4.7 us).
+__global__ __launch_bounds__(64) void grad_kernel(net_desc net, int32_t batch, const uint16_t* __restrict__ ta,
+                                                  const uint16_t* __restrict__ tz, const float* __restrict__ part,
+                                                  float inv_count, float* __restrict__ grad, float* __restrict__ grad_out,
+                                                  float* __restrict__ loss_out) {
+  const int l = blockIdx.y, lane = threadIdx.x;
+  const int mts = (batch + 15) >> 4;
+  if (l == net.L) {
+    if (blockIdx.x != 0 || !loss_out) return;
     float s = 0.0f;
-    for (int i = 0; i < n_part; ++i) s += part[i];
-    loss[0] = s * inv_count;
+    for (int i = lane; i < mts; i += 64) s += part[i];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) loss_out[0] = s * inv_count;
+    return;
+  }
+  const int l16 = lane & 15, q = lane >> 4;
+  const int fi = net.fi[l], fo = net.fo[l], it_n = tiles16(fi), jt_n = tiles16(fo);
+  const int jt = (int)blockIdx.x / it_n, it = (int)blockIdx.x - jt * it_n;
+  if (jt >= jt_n) return;
+  const int sa = jt_n * 64, sb = it_n * 64;  // words per 16-sample tile
+  const bf16x4* ap = reinterpret_cast<const bf16x4*>(tz + net.tz[l]) + (jt * 16 + l16) * 4 + q;
+  const bf16x4* bp = reinterpret_cast<const bf16x4*>(ta + net.ta[l]) + (it * 16 + l16) * 4 + q;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  float db = 0.0f;
+  auto step = [&](bf16x4 a, bf16x4 b) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+    if (it == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) db += bf2f((uint16_t)a[i]);
+  };
+  int s = 0;
+  for (; s + 8 <= mts; s += 8) {
+    bf16x4 a[8], b[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      a[u] = ap[(int64_t)(s + u) * sa];
+      b[u] = bp[(int64_t)(s + u) * sb];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) step(a[u], b[u]);
+  }
+  for (; s < mts; ++s) step(ap[(int64_t)s * sa], bp[(int64_t)s * sb]);
+  const int i = it * 16 + l16;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int j = jt * 16 + 4 * q + v;
+    if (j >= fo || i >= fi) continue;
+    const int64_t at = net.w[l] + (int64_t)j * fi + i;
+    grad[at] = acc[v];
+    if (grad_out) grad_out[at] = acc[v];
+  }
+  if (it == 0) {
+    db += __shfl_xor(db, 16, 64);
+    db += __shfl_xor(db, 32, 64);
+    const int j = jt * 16 + l16;
+    if (q == 0 && j < fo) {
+      grad[net.b[l] + j] = db;
+      if (grad_out) grad_out[net.b[l] + j] = db;
+    }
   }
 }
 
-// db[n] = sum_m dz[m, n] (one workgroup per column, fixed reduction order)
-__global__ __launch_bounds__(256) void colsum_kernel(int32_t batch, int32_t N, const uint16_t* __restrict__ dz,
-                                                     float* __restrict__ out) {
-  __shared__ float red[256];
-  const int n = blockIdx.x;
-  float s = 0.0f;
-  for (int m = threadIdx.x; m < batch; m += blockDim.x) s += bf2f(dz[(int64_t)m * N + n]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[n] = red[0];
+// parameter p rounded to BF16 goes to its place in both weight copies (biases have none)
+__device__ inline void store_weight(const net_desc& net, int64_t p, float v, uint16_t* __restrict__ wf,
+                                    uint16_t* __restrict__ wt) {
+  int l = 0;
+  while (l + 1 < net.L && p >= net.w[l + 1]) ++l;
+  if (p >= net.b[l]) return;
+  const int fi = net.fi[l], fo = net.fo[l], e = (int)(p - net.w[l]);
+  const int j = e / fi, i = e - j * fi;
+  const uint16_t h = f2bf(v);
+  // forward: k = i, n = j; backward: k = j, n = i
+  wf[net.wf[l] + (((int64_t)(j >> 4) * tiles16(fi) + (i >> 4)) * 64 + (j & 15) + 16 * ((i & 15) >> 2)) * 4 + (i & 3)] = h;
+  wt[net.wt[l] + (((int64_t)(i >> 4) * tiles16(fo) + (j >> 4)) * 64 + (i & 15) + 16 * ((j & 15) >> 2)) * 4 + (j & 3)] = h;
 }
 
-__global__ void adam_kernel(int64_t P, float* __restrict__ theta, float* __restrict__ m1, float* __restrict__ m2,
-                            const float* __restrict__ g, uint16_t* __restrict__ wb, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
+__global__ void adam_kernel(net_desc net, int64_t P, float* __restrict__ theta, float* __restrict__ m1,
+                            float* __restrict__ m2, const float* __restrict__ g, uint16_t* __restrict__ wf,
+                            uint16_t* __restrict__ wt, float lr, float b1, float b2, float eps, float c1, float c2) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P; i += (int64_t)gridDim.x * blockDim.x) {
     const float gi = g[i];
     const float m = b1 * m1[i] + (1.0f - b1) * gi;
@@ -138,18 +270,24 @@ __global__ void adam_kernel(int64_t P, float* __restrict__ theta, float* __restr
     m2[i] = v;
     const float th = theta[i] - lr * (m * c1) / (sqrtf(v * c2) + eps);
     theta[i] = th;
-    wb[i] = f2bf(th);
+    store_weight(net, i, th, wf, wt);
   }
 }
 
-__global__ void set_params_kernel(int64_t P, const float* __restrict__ src, float* __restrict__ theta,
-                                  float* __restrict__ m1, float* __restrict__ m2, uint16_t* __restrict__ wb) {
+// both weight copies zero (their padding stays so)
+__global__ void clear_weights_kernel(int64_t n, uint64_t* __restrict__ w) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) w[i] = 0;
+}
+
+__global__ void set_params_kernel(net_desc net, int64_t P, const float* __restrict__ src, float* __restrict__ theta,
+                                  float* __restrict__ m1, float* __restrict__ m2, uint16_t* __restrict__ wf,
+                                  uint16_t* __restrict__ wt) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P; i += (int64_t)gridDim.x * blockDim.x) {
     const float v = src[i];
     theta[i] = v;
     m1[i] = 0.0f;
     m2[i] = 0.0f;
-    wb[i] = f2bf(v);
+    store_weight(net, i, v, wf, wt);
   }
 }
 
@@ -227,7 +365,6 @@ inline unsigned grid_for(int64_t work, int per, unsigned cap = 4096) {
 }
 
 char g_mlp_create_err[256] = "";
-constexpr int kLossParts = 64;
 
 }  // namespace
 
@@ -235,22 +372,21 @@ struct vk_mlp {
   hipStream_t stream = nullptr;
   std::string err;
   int32_t n_in = 0, width = 0, n_hidden = 0, n_out = 0, max_batch = 0;
-  std::vector<int32_t> lin, lout;     // per layer fan-in / fan-out
-  std::vector<int64_t> woff, boff;    // offsets of W_l and b_l in the packed vector
+  net_desc net{};
   int64_t P = 0;
+  int64_t n_wf = 0, n_wt = 0, n_ta = 0, n_tz = 0;  // elements of the weight copies and batch arrays
+  int32_t wide = 0;                                // widest layer, padded to 16
   // workspace
   bool ready = false;
   float* theta = nullptr;
   float* m1 = nullptr;
   float* m2 = nullptr;
   float* grad = nullptr;
-  uint16_t* wb = nullptr;
-  std::vector<uint16_t*> act;  // hidden activations, max_batch x width each
-  float* y = nullptr;          // max_batch x n_out
-  uint16_t* dz_a = nullptr;    // back-propagated pre-activation gradients (ping-pong)
-  uint16_t* dz_b = nullptr;
-  float* part = nullptr;
-  float* loss = nullptr;
+  uint16_t* wf = nullptr;  // weights in the forward products' order; wt follows it
+  uint16_t* wt = nullptr;
+  uint16_t* ta = nullptr;  // the batch's layer inputs and pre-activation gradients (gradient calls)
+  uint16_t* tz = nullptr;
+  float* part = nullptr;   // squared error per 16 samples
   int64_t step = 0;
   bool have_grad = false;
 };
@@ -289,20 +425,16 @@ size_t plan(vk_mlp* c, char* base) {
     off += align256(bytes);
     return p;
   };
-  const size_t P = (size_t)c->P, mb = (size_t)c->max_batch;
+  const size_t P = (size_t)c->P;
   c->theta = reinterpret_cast<float*>(take(P * 4));
   c->m1 = reinterpret_cast<float*>(take(P * 4));
   c->m2 = reinterpret_cast<float*>(take(P * 4));
   c->grad = reinterpret_cast<float*>(take(P * 4));
-  c->wb = reinterpret_cast<uint16_t*>(take(P * 2));
-  c->act.assign(c->n_hidden, nullptr);
-  for (int l = 0; l < c->n_hidden; ++l) c->act[l] = reinterpret_cast<uint16_t*>(take(mb * c->width * 2));
-  c->y = reinterpret_cast<float*>(take(mb * c->n_out * 4));
-  const size_t wmax = (size_t)(c->width > c->n_out ? c->width : c->n_out);
-  c->dz_a = reinterpret_cast<uint16_t*>(take(mb * wmax * 2));
-  c->dz_b = reinterpret_cast<uint16_t*>(take(mb * wmax * 2));
-  c->part = reinterpret_cast<float*>(take(kLossParts * 4));
-  c->loss = reinterpret_cast<float*>(take(4));
+  c->wf = reinterpret_cast<uint16_t*>(take((size_t)(c->n_wf + c->n_wt) * 2));
+  c->wt = c->wf ? c->wf + c->n_wf : nullptr;
+  c->ta = reinterpret_cast<uint16_t*>(take((size_t)c->n_ta * 2));
+  c->tz = reinterpret_cast<uint16_t*>(take((size_t)c->n_tz * 2));
+  c->part = reinterpret_cast<float*>(take((size_t)((c->max_batch + 15) / 16) * 4));
   return off;
 }
 
@@ -312,40 +444,27 @@ vk_status check_ready(vk_mlp* c) {
   return VK_OK;
 }
 
-template <int EPI>
-hipError_t gemm(hipStream_t s, int32_t M, int32_t N, int32_t K, const uint16_t* A, const int32_t* arow, int64_t a_rs,
-                int64_t a_ks, const uint16_t* B, const int32_t* brow, int64_t b_ks, int64_t b_ns, const float* bias,
-                const uint16_t* act, float* outf, uint16_t* outb, int64_t ldo) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 grid((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
-  gemm_kernel<EPI><<<grid, 64, 0, s>>>(M, N, K, A, arow, a_rs, a_ks, B, brow, b_ks, b_ns, bias, act, outf, outb,
-                                       ldo);
-  return hipGetLastError();
-}
-
-// forward over `batch` samples; hidden activations stay in the workspace for the gradient
-vk_status run_forward(vk_mlp* c, int32_t batch, const uint16_t* x, const int32_t* rows) {
-  hipStream_t s = c->stream;
-  const int L = c->n_hidden + 1;
-  const uint16_t* a_in = x;
-  const int32_t* a_rows = rows;
-  int64_t a_ld = c->n_in;
-  for (int l = 0; l < L; ++l) {
-    const uint16_t* W = c->wb + c->woff[l];
-    const float* bias = c->theta + c->boff[l];
-    // Z = A W^T: B(k, n) = W[n * in + k]
-    if (l + 1 < L) {
-      MLP_TRY(gemm<EPI_TANH>(s, batch, c->lout[l], c->lin[l], a_in, a_rows, a_ld, 1, W, nullptr, 1, c->lin[l], bias,
-                             nullptr, nullptr, c->act[l], c->width));
-      a_in = c->act[l];
-      a_rows = nullptr;
-      a_ld = c->width;
-    } else {
-      MLP_TRY(gemm<EPI_LINEAR>(s, batch, c->lout[l], c->lin[l], a_in, a_rows, a_ld, 1, W, nullptr, 1, c->lin[l],
-                               bias, nullptr, c->y, nullptr, c->n_out));
-    }
+// The network over `batch` samples: y (forward), or with a target the loss parts, the layer inputs and
+// the pre-activation gradients the weight gradients are formed from.  Eight wavefronts per 16 samples
+// where a layer has that many column tiles (one tile each), else four.
+hipError_t run_net(vk_mlp* c, int32_t batch, const uint16_t* x, const int32_t* rows, float* y, const float* target,
+                   float scale) {
+  const unsigned grid = (unsigned)((batch + 15) / 16);
+  const unsigned nt = c->wide > 64 ? 512 : 256;
+  const int32_t ldk = c->wide + 4;  // rows 8 bytes apart modulo 32: the lanes' 8-byte reads spread over the banks
+  const size_t lds = (size_t)2 * 16 * ldk * sizeof(uint16_t);
+  if (lds > 65000) {  // layers about 1 000 wide: beyond what a launch may take unasked
+    const void* f = target ? reinterpret_cast<const void*>(net_kernel<true>) : reinterpret_cast<const void*>(net_kernel<false>);
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
   }
-  return VK_OK;
+  if (target)
+    net_kernel<true><<<grid, nt, lds, c->stream>>>(c->net, batch, ldk, x, rows, c->wf, c->wt, c->theta, nullptr, target,
+                                                   scale, c->ta, c->tz, c->part);
+  else
+    net_kernel<false><<<grid, nt, lds, c->stream>>>(c->net, batch, ldk, x, rows, c->wf, c->wt, c->theta, y, nullptr,
+                                                    0.0f, nullptr, nullptr, nullptr);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -376,14 +495,27 @@ vk_status vk_mlp_create(vk_mlp** out, int32_t n_in, int32_t width, int32_t n_hid
   c->n_out = n_out;
   c->max_batch = max_batch;
   int64_t off = 0;
-  for (int l = 0; l <= n_hidden; ++l) {
+  const int64_t mts = (max_batch + 15) / 16;
+  net_desc& d = c->net;
+  d.L = n_hidden + 1;
+  for (int l = 0; l < d.L; ++l) {
     const int32_t fi = l == 0 ? n_in : width, fo = l == n_hidden ? n_out : width;
-    c->lin.push_back(fi);
-    c->lout.push_back(fo);
-    c->woff.push_back(off);
-    off += (int64_t)fi * fo;
-    c->boff.push_back(off);
-    off += fo;
+    const int64_t ti = tiles16(fi), to = tiles16(fo);
+    d.fi[l] = fi;
+    d.fo[l] = fo;
+    d.w[l] = off;
+    d.b[l] = off + (int64_t)fi * fo;
+    off = d.b[l] + fo;
+    d.wf[l] = c->n_wf;
+    c->n_wf += ti * to * 256;
+    d.wt[l] = c->n_wt;
+    c->n_wt += ti * to * 256;
+    d.ta[l] = c->n_ta;
+    c->n_ta += mts * ti * 256;
+    d.tz[l] = c->n_tz;
+    c->n_tz += mts * to * 256;
+    const int32_t wide = 16 * (int32_t)(ti > to ? ti : to);
+    if (wide > c->wide) c->wide = wide;
   }
   c->P = off;
   *out = c;
@@ -424,7 +556,11 @@ vk_status vk_mlp_set_params(vk_mlp* c, const float* params) {
   vk_status st = check_ready(c);
   if (st != VK_OK) return st;
   if (!params) return mfail(c, VK_ERR_ARG, "null parameter vector");
-  set_params_kernel<<<grid_for(c->P, 256), 256, 0, c->stream>>>(c->P, params, c->theta, c->m1, c->m2, c->wb);
+  const int64_t words = (c->n_wf + c->n_wt) / 4;
+  clear_weights_kernel<<<grid_for(words, 256), 256, 0, c->stream>>>(words, reinterpret_cast<uint64_t*>(c->wf));
+  MLP_LAUNCHED("clear_weights_kernel");
+  set_params_kernel<<<grid_for(c->P, 256), 256, 0, c->stream>>>(c->net, c->P, params, c->theta, c->m1, c->m2, c->wf,
+                                                                c->wt);
   MLP_LAUNCHED("set_params_kernel");
   c->step = 0;
   c->have_grad = false;
@@ -446,11 +582,7 @@ vk_status vk_mlp_forward(vk_mlp* c, int32_t batch, const uint16_t* x, const int3
   if (batch < 0 || batch > c->max_batch) return mfail(c, VK_ERR_ARG, "batch exceeds max_batch");
   if (batch == 0) return VK_OK;
   if (!x || !y) return mfail(c, VK_ERR_ARG, "null input or output");
-  st = run_forward(c, batch, x, rows);
-  if (st != VK_OK) return st;
-  const int64_t n = (int64_t)batch * c->n_out;
-  copy_f32_kernel<<<grid_for(n, 256), 256, 0, c->stream>>>(n, c->y, y);
-  MLP_LAUNCHED("copy_f32_kernel");
+  MLP_TRY(run_net(c, batch, x, rows, y, nullptr, 0.0f));
   return VK_OK;
 }
 
@@ -460,44 +592,14 @@ vk_status vk_mlp_gradient(vk_mlp* c, int32_t batch, const uint16_t* x, const int
   if (st != VK_OK) return st;
   if (batch < 1 || batch > c->max_batch) return mfail(c, VK_ERR_ARG, "batch must be in [1, max_batch]");
   if (!x || !target) return mfail(c, VK_ERR_ARG, "null input or target");
-  hipStream_t s = c->stream;
-  st = run_forward(c, batch, x, rows);
-  if (st != VK_OK) return st;
-  const int L = c->n_hidden + 1;
   const float count = (float)batch * (float)c->n_out;
-  mse_kernel<<<kLossParts, 256, 0, s>>>(batch, c->n_out, c->y, target, rows, 2.0f / count, c->dz_a, c->part);
-  MLP_LAUNCHED("mse_kernel");
-  loss_final_kernel<<<1, 64, 0, s>>>(kLossParts, c->part, 1.0f / count, c->loss);
-  MLP_LAUNCHED("loss_final_kernel");
-  uint16_t* dz = c->dz_a;
-  uint16_t* dz_next = c->dz_b;
-  for (int l = L - 1; l >= 0; --l) {
-    const int32_t fi = c->lin[l], fo = c->lout[l];
-    // input of layer l: the features (rows indexed) or the previous activation
-    const uint16_t* a_prev = l == 0 ? x : c->act[l - 1];
-    const int32_t* a_rows = l == 0 ? rows : nullptr;
-    // dW(j, i) = sum_m dz[m, j] a_prev[m, i]
-    MLP_TRY(gemm<EPI_STORE>(s, fo, fi, batch, dz, nullptr, 1, fo, a_prev, a_rows, fi, 1, nullptr, nullptr,
-                            c->grad + c->woff[l], nullptr, fi));
-    colsum_kernel<<<fo, 256, 0, s>>>(batch, fo, dz, c->grad + c->boff[l]);
-    MLP_LAUNCHED("colsum_kernel");
-    if (l > 0) {
-      // dz_prev(m, i) = (sum_j dz[m, j] W[j, i]) (1 - a_prev(m, i)^2)
-      MLP_TRY(gemm<EPI_DTANH>(s, batch, fi, fo, dz, nullptr, fo, 1, c->wb + c->woff[l], nullptr, fi, 1, nullptr,
-                              a_prev, nullptr, dz_next, fi));
-      uint16_t* t = dz;
-      dz = dz_next;
-      dz_next = t;
-    }
-  }
-  if (loss) {
-    copy_f32_kernel<<<1, 64, 0, s>>>(1, c->loss, loss);
-    MLP_LAUNCHED("copy_f32_kernel");
-  }
-  if (grad) {
-    copy_f32_kernel<<<grid_for(c->P, 256), 256, 0, s>>>(c->P, c->grad, grad);
-    MLP_LAUNCHED("copy_f32_kernel");
-  }
+  MLP_TRY(run_net(c, batch, x, rows, nullptr, target, 2.0f / count));
+  unsigned tiles = 1;
+  for (int l = 0; l < c->net.L; ++l)
+    tiles = std::max(tiles, (unsigned)(tiles16(c->net.fi[l]) * tiles16(c->net.fo[l])));
+  grad_kernel<<<dim3(tiles, (unsigned)c->net.L + 1), 64, 0, c->stream>>>(c->net, batch, c->ta, c->tz, c->part,
+                                                                         1.0f / count, c->grad, grad, loss);
+  MLP_LAUNCHED("grad_kernel");
   c->have_grad = true;
   return VK_OK;
 }
@@ -511,8 +613,8 @@ vk_status vk_mlp_adam(vk_mlp* c, float lr, float beta1, float beta2, float eps) 
   ++c->step;
   const double c1 = 1.0 / (1.0 - std::pow((double)beta1, (double)c->step));
   const double c2 = 1.0 / (1.0 - std::pow((double)beta2, (double)c->step));
-  adam_kernel<<<grid_for(c->P, 256), 256, 0, c->stream>>>(c->P, c->theta, c->m1, c->m2, c->grad, c->wb, lr, beta1,
-                                                           beta2, eps, (float)c1, (float)c2);
+  adam_kernel<<<grid_for(c->P, 256), 256, 0, c->stream>>>(c->net, c->P, c->theta, c->m1, c->m2, c->grad, c->wf, c->wt,
+                                                           lr, beta1, beta2, eps, (float)c1, (float)c2);
   MLP_LAUNCHED("adam_kernel");
   return VK_OK;
 }
