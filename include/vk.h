@@ -160,7 +160,7 @@ vk_status vk_set_workspace(vk_ctx* ctx, void* dev, size_t bytes, vk_prec prec, i
  * level l >= 1 gather J_K = J_l restricted to dof(K, .) x dof(K, .), entries
  * not stored in J_l being zero, invert it in FP64 by Gauss-Jordan elimination
  * with partial pivoting (first row of maximal |pivot|, the LU pivot sequence;
- * the matrix-core kernel of the 170-wide patches counts candidates within a
+ * the matrix-core kernels count candidates within a
  * relative 2^-13 of the largest as tied) and store A_K in `prec`; compute 1/p_mu, p_mu = number of cells containing
  * DoF mu (Eq. 3.5b); and form the FP64 inverse of J_0 for the coarsest-level
  * direct solve (blocked Gauss-Jordan with partial pivoting: the largest |pivot|
@@ -277,19 +277,22 @@ vk_status vk_set_sweep_variant(vk_ctx* ctx, int32_t variant);
 
 /* Patch inversion kernel used by vanka_setup: 0 (default) keeps the patch
  * matrix in registers where a kernel for the patch width is compiled: blocked
- * Gauss-Jordan on the FP64 matrix cores for n_K = 170 (16 x 16 tiles over a
- * 704-thread workgroup, rank-4 panel updates), its patches gathered through a
- * patch entry map (per cell and patch entry the entry's offset in its CSR row,
- * 2 bytes each, kept in the workspace and built at the first vanka_setup after
- * vk_set_level or vk_set_workspace); one row per lane for n_K = 42, 63, spread
- * over a 512-thread workgroup with vector FP64 for n_K = 84, 85, 105, 120,
- * 180; inverts other patches wider than 88 (up to 512) with the blocked
- * kernels of the directly solved blocks, one block per cell, and the rest in
- * LDS; 1 always uses the LDS / global-memory kernel; 2 is 0 without the
- * matrix-core kernel (n_K = 170 on the vector unit); 3 is 0 with the n_K = 170
- * patches gathered by a search of their CSR rows instead of the map.  All
- * compute the Gauss-Jordan inverse with the same partial pivoting; setup must
- * run again after a change. */
+ * Gauss-Jordan on the FP64 matrix cores (16 x 16 tiles, rank-4 panel updates),
+ * one wavefront per patch for n_K <= 64, a workgroup for n_K = 84, 85, 105, 120
+ * and 170, the patches gathered through a patch entry map (per cell and patch
+ * entry the entry's offset in its CSR row, 2 bytes each, kept in the workspace
+ * and built at the first vanka_setup after vk_set_level or vk_set_workspace; a
+ * level with a patch row of more than 65535 entries has none and takes the
+ * kernels of variant 3); spread over a 512-thread workgroup with vector FP64
+ * for n_K = 180; inverts other patches wider than 88 (up to 512) with the
+ * blocked kernels of the directly solved blocks, one block per cell, and the
+ * rest in LDS; 1 always uses the LDS / global-memory kernel; 2 is 0 without the
+ * matrix-core kernels (one row per lane for n_K = 42, 63, the workgroup kernel
+ * with vector FP64 for n_K = 84, 85, 105, 120, 170, 180); 3 is 2 but for
+ * n_K = 170, which takes the matrix-core kernel with its patches gathered by a
+ * search of their CSR rows instead of the map.  All compute the Gauss-Jordan
+ * inverse with partial pivoting (the matrix-core kernels compare pivots up to a
+ * relative 2^-13, see vanka_setup); setup must run again after a change. */
 vk_status vk_set_setup_variant(vk_ctx* ctx, int32_t variant);
 
 /* Pivot choice of the directly solved blocks' Gauss-Jordan inversion (the

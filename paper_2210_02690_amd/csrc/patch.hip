@@ -747,7 +747,8 @@ __global__ __launch_bounds__(64 * RowCfg<N>::W) void patch_setup_rows_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Wide patches (compiled for n_K = 84, 85, 105, 120, 170, 180: 2D Q2/P1disc
+// Wide patches on the vector unit (setup variant 2, and n_K = 180; compiled for
+// n_K = 84, 85, 105, 120, 170, 180: 2D Q2/P1disc
 // dG(3), dG(4), the 3D Q2/P1disc dG(0), dG(1) patches and (Q4)^2/P3disc dG(1),
 // dG(2)): beyond 64 rows one row per lane takes several wavefronts per cell that
 // each hold whole rows, so the FP64 matrix is instead spread over a 512-thread
@@ -1024,7 +1025,7 @@ __device__ inline double recip_f64(double a) {
 }
 
 // ---------------------------------------------------------------------------
-// Wide patches on the FP64 matrix cores (compiled for n_K = 170, the 3D Q2/P1disc dG(1) patch):
+// Wide patches on the FP64 matrix cores (compiled for n_K = 84, 85, 105, 120 and 170):
 // blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
 // registers as T x T tiles of 16 x 16: tile-row wavefront w (of T) holds tile row w, and one more
 // wavefront, which holds no tiles, eliminates the panels.  Columns are eliminated in panels of
@@ -1075,31 +1076,34 @@ __device__ __forceinline__ int patch_map_pos(int i, int j, int T) {
   return (((i >> 4) * T + (j >> 4)) * 64 + n + 16 * (m & 3)) * 4 + (m >> 2);
 }
 
-template <int N>
+// LDS: the map, then row starts (padded to 8 bytes), lengths
+inline size_t patch_map_lds(int n, int T) { return (size_t)T * T * 512 + (size_t)n * 8 + (size_t)n * 4; }
+
 __global__ __launch_bounds__(512) void patch_map_kernel(const int64_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ col,
-                                                        const int32_t* __restrict__ cell_dofs, uint64_t* pmap,
+                                                        const int32_t* __restrict__ cell_dofs, int32_t n, uint64_t* pmap,
                                                         int32_t* too_long) {
-  constexpr int T = MfCfg<N>::T, NT = 512, ME = T * T * 256;
-  __shared__ uint16_t sm[ME];
+  extern __shared__ __align__(16) char smem[];
+  const int T = (n + 15) >> 4, ME = T * T * 256, NT = blockDim.x;
+  uint16_t* sm = reinterpret_cast<uint16_t*>(smem);
+  int64_t* rbeg = reinterpret_cast<int64_t*>(smem + (size_t)ME * 2);
+  int* rlen = reinterpret_cast<int*>(rbeg + n);
   __shared__ int2 htab[PatchHash::SLOTS];
-  __shared__ int64_t rbeg[N];
-  __shared__ int rlen[N];
   const int K = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int h = tid; h < PatchHash::SLOTS; h += NT) htab[h] = make_int2(-1, 0);
   for (int e = tid; e < ME / 2; e += NT) reinterpret_cast<uint32_t*>(sm)[e] = 0xFFFFFFFFu;
   __syncthreads();
-  if (tid < N) {
-    const int dof = cell_dofs[(int64_t)K * N + tid];
+  for (int r = tid; r < n; r += NT) {
+    const int dof = cell_dofs[(int64_t)K * n + r];
     const int64_t b0 = row_ptr[dof];
     const int64_t len = row_ptr[dof + 1] - b0;
-    rbeg[tid] = b0;
-    rlen[tid] = (int)(len < 65535 ? len : 65535);
+    rbeg[r] = b0;
+    rlen[r] = (int)(len < 65535 ? len : 65535);
     if (len > 65535) atomicOr(too_long, 1);
-    PatchHash::insert(htab, dof, tid);
+    PatchHash::insert(htab, dof, r);
   }
   __syncthreads();
-  for (int i = wv; i < N; i += NT / 64) {
+  for (int i = wv; i < n; i += NT / 64) {
     const int len = rlen[i];
     const int32_t* cr = col + rbeg[i];
     for (int e0 = 0; e0 < len; e0 += 256) {
@@ -1146,9 +1150,9 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
   __shared__ double pan[2][NP * PLD];     // eliminated panel columns M (double-buffered)
   __shared__ double pc[2][NP * PLD];      // the next panel's columns before its last update
   __shared__ double bs[2][NB * NP];       // old pivot rows (double-buffered)
-  __shared__ int2 htab[PatchHash::SLOTS]; // DoF -> local index
-  __shared__ int64_t rbeg[N];             // first CSR entry of each patch row
-  __shared__ int rlen[NP];                // CSR entries per patch row (0 beyond N)
+  __shared__ int2 htab[MAP ? 1 : PatchHash::SLOTS];  // DoF -> local index
+  __shared__ int64_t rbeg[MAP ? 1 : N];              // first CSR entry of each patch row
+  __shared__ int rlen[NP];                           // CSR entries per patch row (0 beyond N)
   __shared__ int pre[17];
   __shared__ int bad_s;
   const int K = blockIdx.x;
@@ -1490,10 +1494,253 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
   if (tid == 0 && bad_s) atomicMin(status, K);
 }
 
+// ---------------------------------------------------------------------------
+// Patches of at most 64 rows on the FP64 matrix cores, one wavefront per patch.  The patch, padded to
+// NP = 16 T, lives in the wavefront's registers as T x T accumulator tiles (the layout of the kernel
+// above; T = 4 takes 128 registers, so two patches share a SIMD), and no step needs a barrier.  Columns
+// are eliminated in panels of four, the first four columns left in tile column 0:
+//   1. the panel's columns go through LDS to one row per lane;
+//   2. four elimination steps in registers: the same 32-bit pivot keys, the pivot row read out with
+//      readlane, the refined reciprocal; M and the pivot rows q_t result;
+//   3. the pivot rows' old values go to LDS as B (identity in the panel's own columns) and are cleared,
+//      as are the panel's columns; W' = W + M B on every tile then also writes M into those columns.
+// After four panels the tile columns rotate by one, so the code has one copy of the panel.
+// What bounds it: the steps (a chain of about 50 instructions each) and the matrix cores share a SIMD
+// with one other patch.  A row per lane with the pivot row broadcast through LDS reads 8 n bytes per
+// lane and step, four times what a CU's LDS returns in the time of the FMAs: that kernel (variant 2)
+// takes 719 us for the 5 632 patches 63 wide of the 176 x 32 channel and 145 us for 1 408 patches 42
+// wide, this one 194 and 36 us (88 patches: 179 -> 42 and 111 -> 23 us).
+// ---------------------------------------------------------------------------
+template <int P, int T>
+__global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
+    const int64_t* __restrict__ row_ptr, const double* __restrict__ val, const int32_t* __restrict__ cell_dofs,
+    const uint64_t* __restrict__ pmap, int32_t n, void* inv_out, int32_t ld, int64_t cell_stride, int32_t* status) {
+  using S = typename PT<P>::S;
+  constexpr int NP = 16 * T, NB = 4, VW = PT<P>::VW, SLD = NP + VW;
+  constexpr int STAGE = 16 * SLD * (int)sizeof(S), WORK = (NP * NB + NB * NP) * 8;
+  __shared__ __align__(16) char smem[STAGE > WORK ? STAGE : WORK];
+  __shared__ int qs[64], kinv[64];
+  double* pan = reinterpret_cast<double*>(smem);  // the panel's columns, then M: row r at NB r
+  double* bs = pan + NP * NB;                     // B: row t at NP t
+  int64_t* rb_s = reinterpret_cast<int64_t*>(smem);
+  const int K = blockIdx.x;
+  const int lane = threadIdx.x, l16 = lane & 15, l4 = lane >> 4;
+  // LDS operations of one wavefront complete in order; the compiler must keep that order
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  f64x4_t acc[T][T];
+  {
+    // gather through the patch entry map
+    const uint64_t* mp = pmap + (int64_t)K * T * T * 64 + lane;
+    uint64_t mw[T][T];
+#pragma unroll
+    for (int I = 0; I < T; ++I)
+#pragma unroll
+      for (int J = 0; J < T; ++J) mw[I][J] = mp[(I * T + J) * 64];
+    rb_s[lane] = lane < n ? row_ptr[cell_dofs[(int64_t)K * n + (lane < n ? lane : 0)]] : 0;
+    fence();
+#pragma unroll
+    for (int I = 0; I < T; ++I) {
+      int64_t rb[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) rb[v] = rb_s[16 * I + 4 * v + l4];
+#pragma unroll
+      for (int J = 0; J < T; ++J)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const uint32_t o = (uint32_t)(mw[I][J] >> (16 * v)) & 0xFFFFu;
+          acc[I][J][v] = 0.0;
+          if (o != 0xFFFFu) acc[I][J][v] = val[rb[v] + o];
+        }
+    }
+    fence();
+  }
+  uint32_t um = lane < n ? 0xFFFFFFFFu : 0u;  // all ones while the lane's row may still become a pivot
+  const uint32_t rid = 255u - (uint32_t)lane;
+  int my_q = lane, my_k = lane;  // pivot row of column `lane`, column of pivot row `lane`
+  bool singular = false;
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += NB) {
+    const int h0 = k0 & 15;
+    const bool in_pan = l16 >= h0 && l16 < h0 + NB;
+    if (in_pan) {
+#pragma unroll
+      for (int I = 0; I < T; ++I)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pan[(16 * I + 4 * v + l4) * NB + (l16 - h0)] = acc[I][0][v];
+    }
+    // the panel's own columns restart from zero: M B with B = identity there leaves M
+#pragma unroll
+    for (int I = 0; I < T; ++I)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[I][0][v] = in_pan ? 0.0 : acc[I][0][v];
+    fence();
+    double pr[NB];
+    {
+      const int r = lane < NP ? lane : 0;
+#pragma unroll
+      for (int c = 0; c < NB; ++c) pr[c] = pan[r * NB + c];
+    }
+    int q[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const int k = k0 + t;
+      const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, pr[t]) >> 32);
+      const uint32_t mk = wave_max_u32((((hi & 0x7FFFFF80u) << 1) | rid) & um);
+      const int p = 255 - (int)(mk & 0xFFu);
+      // uniform: a padding column, no nonzero candidate, or a non-finite largest one
+      const bool skip = k >= n || (mk >> 8) == 0 || (mk >> 21) == 0x7FFu;
+      singular = singular || (skip && k < n);
+      const int pl = p & 63;
+      double prow[NB];
+#pragma unroll
+      for (int c = 0; c < NB; ++c) prow[c] = readlane_f64(pr[c], pl);
+      const double inv = skip ? 0.0 : recip_f64(prow[t]);
+#pragma unroll
+      for (int c = 0; c < NB; ++c) prow[c] = (c == t) ? inv : prow[c] * inv;
+      const bool isp = !skip && lane == pl;
+      const double f = pr[t];
+#pragma unroll
+      for (int cc = 0; cc < NB; ++cc) {
+        const int c = (t + 1 + cc) % NB;
+        const double u = (c == t) ? -f * inv : fma(-f, prow[c], pr[c]);
+        pr[c] = isp ? prow[c] : u;
+      }
+      um = isp ? 0u : um;
+      my_k = isp ? k : my_k;
+      my_q = (!skip && lane == k) ? pl : my_q;
+      q[t] = skip ? -1 : pl;
+    }
+    if (lane < NP) {
+#pragma unroll
+      for (int c = 0; c < NB; ++c) pan[lane * NB + c] = pr[c];
+    }
+    // rows of B without a pivot are zero
+    if ((q[0] | q[1] | q[2] | q[3]) < 0) {  // uniform
+      for (int e = lane; e < NB * NP; e += 64) bs[e] = 0.0;
+      fence();
+    }
+    // the pivot rows' old values to B; the rows are cleared.  Bit 4 I + v of `own`: some pivot row lies
+    // among the rows 16 I + 4 v .. + 3
+    uint32_t own = 0;
+#pragma unroll
+    for (int t = 0; t < NB; ++t) own |= q[t] >= 0 ? 1u << (q[t] >> 2) : 0u;
+#pragma unroll
+    for (int I = 0; I < T; ++I)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (own & (1u << (4 * I + v))) {  // uniform
+          const int row = 16 * I + 4 * v + l4;
+          const int t = row == q[0] ? 0 : row == q[1] ? 1 : row == q[2] ? 2 : row == q[3] ? 3 : -1;
+          if (t >= 0) {
+#pragma unroll
+            for (int J = 0; J < T; ++J)
+              bs[t * NP + 16 * J + l16] = J == 0 && in_pan ? (l16 - h0 == t ? 1.0 : 0.0) : acc[I][J][v];
+          }
+          const double kv = t >= 0 ? 0.0 : 1.0;
+#pragma unroll
+          for (int J = 0; J < T; ++J) acc[I][J][v] *= kv;
+        }
+      }
+    fence();
+    double a[T], b[T];
+#pragma unroll
+    for (int I = 0; I < T; ++I) a[I] = pan[(16 * I + l16) * NB + l4];
+#pragma unroll
+    for (int J = 0; J < T; ++J) b[J] = bs[l4 * NP + 16 * J + l16];
+    fence();
+#pragma unroll
+    for (int J = 0; J < T; ++J)
+#pragma unroll
+      for (int I = 0; I < T; ++I) acc[I][J] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[I], b[J], acc[I][J], 0, 0, 0);
+    if (h0 + NB == 16) {  // uniform
+#pragma unroll
+      for (int I = 0; I < T; ++I) {
+        const f64x4_t first = acc[I][0];
+#pragma unroll
+        for (int J = 0; J + 1 < T; ++J) acc[I][J] = acc[I][J + 1];
+        acc[I][T - 1] = first;
+      }
+    }
+  }
+  const int turns = (n + 3) >> 4;  // rotations done: after every panel that ends a tile column
+  if (singular && lane == 0) atomicMin(status, K);
+  qs[lane] = my_q;
+  kinv[lane] = my_k;
+  fence();
+  int dr[T][4];
+#pragma unroll
+  for (int I = 0; I < T; ++I)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dr[I][v] = kinv[16 * I + 4 * v + l4];
+  // J_K^{-1}[kinv[i]][q_j] = W[i][j], 16 columns at a time through LDS, then whole 16-byte pieces
+  S* out = reinterpret_cast<S*>(inv_out) + (int64_t)K * cell_stride;
+  S* stage = reinterpret_cast<S*>(smem);
+  const int nv = ld / VW;
+#pragma unroll
+  for (int J = 0; J < T; ++J) {
+    const int c0 = 16 * ((J + turns) % T);  // the columns in tile column J
+    fence();
+#pragma unroll
+    for (int I = 0; I < T; ++I)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) stage[l16 * SLD + dr[I][v]] = store_cvt<P>(acc[I][J][v]);
+    fence();
+    for (int e = lane; e < 16 * nv; e += 64) {
+      const int jj = e / nv, r = (e - jj * nv) * VW;
+      if (c0 + jj < n)
+        *reinterpret_cast<uint4*>(out + (int64_t)qs[c0 + jj] * ld + r) =
+            *reinterpret_cast<const uint4*>(stage + jj * SLD + r);
+    }
+  }
+}
+
+// Tiles per dimension of the matrix-core kernels for patches n wide, 0 where none is compiled: any width
+// up to 64 on one wavefront (T = 4 is the widest whose tiles leave room for a second patch per SIMD),
+// the widths of the repository's 3D, dG(3), dG(4) and Q4 patches up to 176 on a workgroup (12 tile rows
+// and their panels do not fit a workgroup's registers).  Against the vector kernels: 28 288 patches 84
+// wide 8.8 -> 3.9 ms, 1 408 patches 120 wide (FP64 storage) 956 -> 589 us.
+inline int mfma_tiles(int n) {
+  return n <= 64 || n == 84 || n == 85 || n == 105 || n == 120 || n == 170 ? (n + 15) / 16 : 0;
+}
+
 template <int P>
 hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t* status, bool* handled,
                       bool mfma, bool map) {
   *handled = true;
+  const bool mapped = mfma && map && L.pmap && L.pmap_ok;
+  const uint64_t* pm = reinterpret_cast<const uint64_t*>(L.pmap);
+#define VK_WAVE_CASE(TT)                                                                                   \
+  patch_setup_wave_kernel<P, TT><<<L.n_cells, 64, 0, s>>>(J.row_ptr, J.val, L.cell_dofs, pm, L.n_K, L.inv, \
+                                                          L.ld, L.cell_stride, status)
+#define VK_MFMA_CASE(NN)                                                                     \
+  case NN:                                                                                   \
+    patch_setup_mfma_kernel<P, NN, true><<<L.n_cells, MfCfg<NN>::NT, 0, s>>>(                \
+        J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.inv, L.ld, L.cell_stride, status);       \
+    return hipGetLastError();
+  if (mapped) {
+    if (L.n_K <= 64) {
+      switch ((L.n_K + 15) / 16) {
+        case 1: VK_WAVE_CASE(1); break;
+        case 2: VK_WAVE_CASE(2); break;
+        case 3: VK_WAVE_CASE(3); break;
+        default: VK_WAVE_CASE(4); break;
+      }
+      return hipGetLastError();
+    }
+    switch (L.n_K) {
+      VK_MFMA_CASE(84)
+      VK_MFMA_CASE(85)
+      VK_MFMA_CASE(105)
+      VK_MFMA_CASE(120)
+      VK_MFMA_CASE(170)
+      default: break;
+    }
+  }
+#undef VK_WAVE_CASE
+#undef VK_MFMA_CASE
   switch (L.n_K) {
 #define VK_ROWS_CASE(NN)                                                                                \
   case NN:                                                                                              \
@@ -1508,24 +1755,19 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
     patch_setup_wide_kernel<P, NN><<<L.n_cells, 64 * WideCfg<NN>::NW, 0, s>>>(                          \
         J.row_ptr, J.col, J.val, L.cell_dofs, L.inv, L.ld, L.cell_stride, status);                     \
     return hipGetLastError();
-    VK_WIDE_CASE(84)   // measured faster than a row per lane on two wavefronts (batch setup 29.8 -> 27.7 ms)
+    VK_WIDE_CASE(84)
     VK_WIDE_CASE(85)
     VK_WIDE_CASE(105)
     VK_WIDE_CASE(120)
     VK_WIDE_CASE(180)
 #undef VK_WIDE_CASE
     case 170:
-      if (mfma && map && L.pmap && L.pmap_ok) {
-        patch_setup_mfma_kernel<P, 170, true><<<L.n_cells, MfCfg<170>::NT, 0, s>>>(
-            J.row_ptr, J.col, J.val, L.cell_dofs, reinterpret_cast<const uint64_t*>(L.pmap), L.inv, L.ld,
-            L.cell_stride, status);
-      } else if (mfma) {
+      if (mfma)
         patch_setup_mfma_kernel<P, 170, false><<<L.n_cells, MfCfg<170>::NT, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.inv, L.ld, L.cell_stride, status);
-      } else {
+      else
         patch_setup_wide_kernel<P, 170><<<L.n_cells, 64 * WideCfg<170>::NW, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, L.inv, L.ld, L.cell_stride, status);
-      }
       return hipGetLastError();
     default:
       *handled = false;
@@ -1760,12 +2002,18 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
 
 }  // namespace
 
-int64_t vk_patch_map_elems(int32_t n_K) { return n_K == 170 ? (int64_t)MfCfg<170>::T * MfCfg<170>::T * 256 : 0; }
+int64_t vk_patch_map_elems(int32_t n_K) { return (int64_t)mfma_tiles(n_K) * mfma_tiles(n_K) * 256; }
 
 hipError_t launch_patch_map(hipStream_t s, const vk_csr& J, const vk_group& G, int32_t* too_long) {
-  if (!G.pmap || G.n_cells == 0 || vk_patch_map_elems(G.n_K) == 0) return hipSuccess;
-  patch_map_kernel<170><<<G.n_cells, 512, 0, s>>>(J.row_ptr, J.col, G.cell_dofs,
-                                                   reinterpret_cast<uint64_t*>(G.pmap), too_long);
+  if (!G.pmap || G.n_cells == 0 || mfma_tiles(G.n_K) == 0) return hipSuccess;
+  const size_t lds = patch_map_lds(G.n_K, mfma_tiles(G.n_K));
+  if (lds > 57000) {  // with the hash table beyond 64 KB, which a launch may not take unasked
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(patch_map_kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  patch_map_kernel<<<G.n_cells, G.n_K <= 64 ? 256 : 512, lds, s>>>(J.row_ptr, J.col, G.cell_dofs, G.n_K,
+                                                                  reinterpret_cast<uint64_t*>(G.pmap), too_long);
   return hipGetLastError();
 }
 
