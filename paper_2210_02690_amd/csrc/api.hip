@@ -1461,6 +1461,14 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     return ms;
   };
   const int lprs[7] = {1, 2, 4, 8, 16, 32, 64};
+  // GEMV tiles: cells per 256-thread workgroup, or one cell on 512 or 1 024 threads where the cells are
+  // few (beyond the default rule's line they only lose)
+  constexpr int kTiles = 6, kCycled = 4;  // the first kCycled are timed again inside V-cycles
+  const int tiles[kTiles] = {1, 2, 4, 8, -512, -1024};
+  auto tile_ok = [&](const vk_group& G, int t) {
+    if (t < 0) return (int64_t)G.n_cells * -t <= (1 << 20) && -t >= G.ld / vk_prec_vw(ctx->prec);
+    return VK_NT / t >= G.ld / vk_prec_vw(ctx->prec);
+  };
   for (int l = 0; l < ctx->n_levels; ++l) {
     vk_level& L = ctx->lv[l];
     VK_TRY(launch_fill(s, L.J.n_rows, 1.0, L.b));
@@ -1497,8 +1505,8 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     for (vk_group& G : L.groups) {
       int best = 0;
       float tb = 1e30f;
-      for (int cpb : {1, 2, 4, 8}) {
-        if (VK_NT / cpb < G.ld / vk_prec_vw(ctx->prec)) continue;
+      for (int cpb : tiles) {
+        if (!tile_ok(G, cpb)) continue;
         const float t = time_ms([&] { return launch_patch_gemv(s, G, ctx->prec, L.b, ctx->Y, cpb); });
         if (t < tb) { tb = t; best = cpb; }
       }
@@ -1511,7 +1519,8 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
   // data through the caches as the solve does: back-to-back launches of one tile reread inverses
   // the last-level cache still holds (176x32 dG(2): 4 and 8 cells per workgroup time alike back
   // to back, 16.8 and 18.5 us inside the solve).  Levels with one cell group; the candidates
-  // alternate over three rounds of `reps` V-cycles, every GEMV launch timed by its own events.
+  // alternate over three rounds of `reps` V-cycles, every GEMV launch timed by its own events.  A level
+  // whose pick is one cell on 512 or 1 024 threads keeps it (few cells: nothing streams there).
   const int Lf = ctx->n_levels - 1;
   bool single = false;
   for (int l = 1; l <= Lf; ++l) single = single || ctx->lv[l].groups.size() == 1;
@@ -1519,25 +1528,24 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     const bool t_on = ctx->timing;
     const int32_t t_level = ctx->timing_level, t_every = ctx->timing_every;
     const uint32_t t_kinds = ctx->timing_kinds;
-    const int cands[4] = {1, 2, 4, 8};
     int32_t first[32] = {0};
-    bool valid[32][4] = {};
-    double tot[32][4] = {};
-    int64_t cnt[32][4] = {};
+    bool valid[32][kCycled] = {};
+    double tot[32][kCycled] = {};
+    int64_t cnt[32][kCycled] = {};
     for (int l = 1; l <= Lf; ++l)
       if (ctx->lv[l].groups.size() == 1) {
         const vk_group& G = ctx->lv[l].groups[0];
         first[l] = G.cpb_tuned;
-        for (int c = 0; c < 4; ++c) valid[l][c] = VK_NT / cands[c] >= G.ld / vk_prec_vw(ctx->prec);
+        for (int c = 0; c < kCycled; ++c) valid[l][c] = G.cpb_tuned > 0 && tile_ok(G, tiles[c]);
       }
     vk_level& F = ctx->lv[Lf];
     VK_TRY(launch_fill(s, F.J.n_rows, 1.0, F.b));
     vk_status st = ctx->coarse_pending ? coarse_wait(ctx, true) : VK_OK;
     for (int round = 0; round < 3 && st == VK_OK; ++round)
-      for (int c = 0; c < 4 && st == VK_OK; ++c) {
+      for (int c = 0; c < kCycled && st == VK_OK; ++c) {
         for (int l = 1; l <= Lf; ++l)
           if (ctx->lv[l].groups.size() == 1)
-            ctx->lv[l].groups[0].cpb_tuned = valid[l][c] ? cands[c] : first[l];
+            ctx->lv[l].groups[0].cpb_tuned = valid[l][c] ? tiles[c] : first[l];
         if ((st = vk_timing_kinds(ctx, 1u << VK_KERNEL_PATCH_GEMV, 1)) != VK_OK) break;
         if ((st = vk_timing_enable(ctx, 1, -1)) != VK_OK) break;
         for (int r = 0; r < reps && st == VK_OK; ++r) st = vcycle_level(ctx, Lf, F.b, F.d, 2, 2);
@@ -1553,10 +1561,10 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     for (int l = 1; l <= Lf; ++l) {
       if (ctx->lv[l].groups.size() != 1) continue;
       int best = -1;
-      for (int c = 0; c < 4; ++c)
+      for (int c = 0; c < kCycled; ++c)
         if (valid[l][c] && cnt[l][c] > 0 && (best < 0 || tot[l][c] / cnt[l][c] < tot[l][best] / cnt[l][best]))
           best = c;
-      ctx->lv[l].groups[0].cpb_tuned = (st == VK_OK && best >= 0) ? cands[best] : first[l];
+      ctx->lv[l].groups[0].cpb_tuned = (st == VK_OK && best >= 0) ? tiles[best] : first[l];
     }
     ctx->timing = t_on;
     ctx->timing_level = t_level;

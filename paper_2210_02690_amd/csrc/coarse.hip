@@ -783,6 +783,9 @@ hipError_t launch_block_invert(hipStream_t s, const vk_level& L, int32_t* status
   // outer blocks of 128 columns halve the passes of the rank-NBO updates over the blocks (HBM
   // traffic) at twice the inner updates' width: worth it for one or a few blocks, whose updates
   // are few workgroups wide; many blocks per level keep 64
+  // (512 threads x 3 rows keep the 16-column panels up to 1 536 rows: one block of 1 184 rows 3.58 -> 2.66
+  // ms, of 1 500 rows 4.78 -> 3.57 ms, twenty of 1 500 rows 10.9 -> 8.9 ms against 8-column panels; with 4
+  // or 5 rows a thread the wide panels no longer pay: 2 060 rows 7.15 -> 7.44 ms)
   const int64_t m = L.cb_max;
   const bool wide = nbk <= 8;
   if (m > min_tourney) {
@@ -793,6 +796,8 @@ hipError_t launch_block_invert(hipStream_t s, const vk_level& L, int32_t* status
   }
   if (m <= 1024)
     e = wide ? run_blocked<512, 2, 16, 128>(s, L, status, -1, la) : run_blocked<512, 2, 16, 64>(s, L, status, -1, la);
+  else if (m <= 1536)
+    e = wide ? run_blocked<512, 3, 16, 128>(s, L, status, -1, la) : run_blocked<512, 3, 16, 64>(s, L, status, -1, la);
   else if (m <= 2048)
     e = wide ? run_blocked<256, 8, 8, 128>(s, L, status, -1, la) : run_blocked<256, 8, 8, 64>(s, L, status, -1, la);
   else if (m <= 4096)
@@ -811,6 +816,7 @@ hipError_t launch_block_invert_dense_any(hipStream_t s, const vk_level& L, int32
   if (e != hipSuccess) return e;
   const int64_t m = L.cb_max;
   if (m <= 1024) return run_blocked<512, 2, 16, 128>(s, L, status);
+  if (m <= 1536) return run_blocked<512, 3, 16, 128>(s, L, status);
   if (m <= 2048) return run_blocked<256, 8, 8, 128>(s, L, status);
   if (m <= 4096) return run_blocked<512, 8, 8, 128>(s, L, status);
   if (m <= 8192) return run_blocked<1024, 8, 4, 128>(s, L, status);

@@ -528,6 +528,22 @@ int vk_default_cpb(int32_t n_K, int32_t ld, vk_prec prec) {
   return best;
 }
 
+// Tile of the patch GEMV: vk_default_cpb's where the cells alone fill the chip (it streams from there);
+// otherwise, where the launch is one cell's chain of round trips, one cell per workgroup on as many
+// threads (a power of two up to 1 024, returned negative) as leave each thread the eight columns it
+// requests up front.  The line is 2^20 threads, 4 096 per CU: 22 cells 120 wide (FP64) took 20 us with
+// 30 columns a thread, 384 cells 255 wide (FP32) 44 us with 255; with this tile 5.7 and 23 us (88 cells 42
+// wide, FP64: 6.4 -> 4.4 us).  1 408 cells 120 wide and 3 072 cells 85 wide stay with the others (29 us,
+// 5.6 TB/s; 38 us on 1 024 threads each).
+int vk_gemv_tile(int32_t n_cells, int32_t n_K, int32_t ld, vk_prec prec) {
+  const int cpb = vk_default_cpb(n_K, ld, prec);
+  const int64_t want = (int64_t)(ld / vk_prec_vw(prec)) * ((n_K + 7) / 8);
+  int nt = 64;
+  while (nt < want && nt < 1024) nt *= 2;
+  if (cpb <= 0 || nt <= VK_NT / cpb || (int64_t)n_cells * nt > (1 << 20)) return cpb;
+  return -nt;
+}
+
 hipError_t launch_count_add(hipStream_t s, int32_t n_cells, int32_t n_K, const int32_t* cell_dofs, int32_t* count) {
   const int64_t total = (int64_t)n_cells * n_K;
   if (total == 0) return hipSuccess;
@@ -1792,8 +1808,10 @@ __device__ inline uint4 ld_stream(const void* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p)));
 }
 
-template <int P>
-__global__ __launch_bounds__(VK_NT) void patch_gemv_kernel(const void* __restrict__ inv_, int32_t ld,
+// One workgroup takes cpb cells; a thread owns one 16-byte vector of a column and every G-th column of
+// its cell.  NT: threads per workgroup (512 and 1 024 for one cell each).
+template <int P, int NT>
+__global__ __launch_bounds__(NT) void patch_gemv_kernel(const void* __restrict__ inv_, int32_t ld,
                                                            int64_t cell_stride, int32_t n_K, int32_t n_cells,
                                                            const int32_t* __restrict__ cell_dofs,
                                                            const double* __restrict__ r,
@@ -1804,7 +1822,7 @@ __global__ __launch_bounds__(VK_NT) void patch_gemv_kernel(const void* __restric
   extern __shared__ __align__(16) char smem[];
   A* srk = reinterpret_cast<A*>(smem);
   A* part = srk + cpb * n_K;
-  const int tpc = VK_NT / cpb;
+  const int tpc = NT / cpb;
   const int slot = threadIdx.x / tpc, t = threadIdx.x - slot * tpc;
   const int64_t K = (int64_t)xcd_block(blockIdx.x, gridDim.x) * cpb + slot;
   const bool valid = K < n_cells;
@@ -1987,16 +2005,24 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
                      hipEvent_t ev1) {
   using A = typename PT<P>::A;
   constexpr int VW = PT<P>::VW;
+  const unsigned nt = cpb < 0 ? (unsigned)-cpb : VK_NT;  // one cell on -cpb threads, or cpb cells on VK_NT
+  if (cpb < 0) cpb = 1;
   const unsigned grid = (unsigned)((L.n_cells + cpb - 1) / cpb);
-  const size_t lds = (size_t)cpb * L.n_K * sizeof(A) + (size_t)VK_NT * VW * sizeof(A);
+  const size_t lds = (size_t)cpb * L.n_K * sizeof(A) + (size_t)nt * VW * sizeof(A);
   A* y = reinterpret_cast<A*>(Y) + L.y_off;
-  if (ev0 || ev1)  // the kernel's own start and end times go to the events (no extra packets)
-    hipExtLaunchKernelGGL(patch_gemv_kernel<P>, dim3(grid), dim3(VK_NT), (uint32_t)lds, s, ev0, ev1, 0u,
-                          (const void*)L.inv, (int32_t)L.ld, (int64_t)L.cell_stride, (int32_t)L.n_K,
-                          (int32_t)L.n_cells, (const int32_t*)L.cell_dofs, r, y, (int32_t)cpb);
-  else
-    patch_gemv_kernel<P><<<grid, VK_NT, lds, s>>>(L.inv, L.ld, L.cell_stride, L.n_K, L.n_cells, L.cell_dofs, r, y,
-                                                  cpb);
+  auto launch = [&](auto kernel) {
+    if (ev0 || ev1)  // the kernel's own start and end times go to the events (no extra packets)
+      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(nt), (uint32_t)lds, s, ev0, ev1, 0u, (const void*)L.inv,
+                            (int32_t)L.ld, (int64_t)L.cell_stride, (int32_t)L.n_K, (int32_t)L.n_cells,
+                            (const int32_t*)L.cell_dofs, r, y, (int32_t)cpb);
+    else
+      kernel<<<grid, nt, lds, s>>>(L.inv, L.ld, L.cell_stride, L.n_K, L.n_cells, L.cell_dofs, r, y, cpb);
+  };
+  if (nt == VK_NT) launch(patch_gemv_kernel<P, VK_NT>);
+  else if (nt == 512) launch(patch_gemv_kernel<P, 512>);
+  else if (nt == 1024) launch(patch_gemv_kernel<P, 1024>);
+  else if (nt == 128) launch(patch_gemv_kernel<P, 128>);
+  else launch(patch_gemv_kernel<P, 64>);
   return hipGetLastError();
 }
 
@@ -2063,8 +2089,8 @@ hipError_t launch_dof_map(hipStream_t s, const vk_level& L, int32_t* count) {
 hipError_t launch_patch_gemv(hipStream_t s, const vk_group& G, vk_prec prec, const double* r, void* Y, int cpb,
                              hipEvent_t ev0, hipEvent_t ev1) {
   if (G.n_cells == 0) return hipSuccess;
-  if (cpb <= 0)
-    cpb = G.cpb_override > 0 ? G.cpb_override : (G.cpb_tuned > 0 ? G.cpb_tuned : vk_default_cpb(G.n_K, G.ld, prec));
+  if (cpb == 0)
+    cpb = G.cpb_override > 0 ? G.cpb_override : (G.cpb_tuned != 0 ? G.cpb_tuned : vk_gemv_tile(G.n_cells, G.n_K, G.ld, prec));
   switch (prec) {
     case VK_F64: return gemv_prec<VK_F64>(s, G, cpb, r, Y, ev0, ev1);
     case VK_F32: return gemv_prec<VK_F32>(s, G, cpb, r, Y, ev0, ev1);

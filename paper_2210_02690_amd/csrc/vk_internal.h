@@ -97,7 +97,7 @@ struct vk_group {
   int32_t n_colours = 0;
   int32_t max_colour_cells = 0;
   int32_t cpb_override = 0;
-  int32_t cpb_tuned = 0;      // picked by vk_autotune for the patch GEMV
+  int32_t cpb_tuned = 0;      // picked by vk_autotune for the patch GEMV (0: none; as vk_gemv_tile)
   // carved from the workspace
   void* inv = nullptr;        // stored patch inverses
   int32_t ld = 0;             // leading dimension (rows, padded)
@@ -368,12 +368,15 @@ hipError_t launch_patch_residual(hipStream_t s, const vk_csr& J, int lpr, const 
                                  const double* b, const double* d, double* rK);
 hipError_t launch_patch_export(hipStream_t s, const vk_group& G, vk_prec prec, int32_t cell0, int32_t n, double* out);
 // ev0 / ev1 (may be null): events that take the kernel's start and end times
+// cpb: as vk_gemv_tile (0: the group's override, tuned or default tile)
 hipError_t launch_patch_gemv(hipStream_t s, const vk_group& G, vk_prec prec, const double* r, void* Y, int cpb = 0,
                              hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // d += omega / p * (sum of the cell products); overwrite: d = that term
 hipError_t launch_dof_gather(hipStream_t s, const vk_level& L, vk_prec prec, const void* Y, double omega, double* d,
                              bool overwrite = false, bool fixed_width = true);
 int vk_default_cpb(int32_t n_K, int32_t ld, vk_prec prec);
+// tile of the patch GEMV for n_cells cells: cells per workgroup, or minus the threads given to one cell
+int vk_gemv_tile(int32_t n_cells, int32_t n_K, int32_t ld, vk_prec prec);
 int vk_prec_vw(vk_prec prec);
 int vk_prec_bytes(vk_prec prec);
 // directly solved blocks (the coarsest level, and in batches every system's coarsest level)
