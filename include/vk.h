@@ -163,7 +163,8 @@ vk_status vk_set_workspace(vk_ctx* ctx, void* dev, size_t bytes, vk_prec prec, i
  * the matrix-core kernels count candidates within a
  * relative 2^-13 of the largest as tied) and store A_K in `prec`; compute 1/p_mu, p_mu = number of cells containing
  * DoF mu (Eq. 3.5b); and form the FP64 inverse of J_0 for the coarsest-level
- * direct solve (blocked Gauss-Jordan with partial pivoting: the largest |pivot|
+ * direct solve (vk_set_coarse_solver; blocked Gauss-Jordan with partial pivoting:
+ * the largest |pivot|
  * up to a relative 2^-38, the lowest row among those).  omega is the
  * under-relaxation of Eq. 3.4 (the paper uses 0.7).
  * The patch inversions run on an internal stream restricted to 7/8 of the
@@ -336,8 +337,14 @@ double vk_spmv_bytes(vk_ctx* ctx, int32_t level);
  * Schur-complement block inverted densely by Gauss-Jordan with partial
  * pivoting inside the block); the solve runs forward and back over the blocks.
  * The plan is made on the host at the first vanka_setup after vk_set_level or
- * vk_set_workspace (the pattern is copied to the host once).  Blocks without
- * such a structure, and every block under mode 1, get the dense inverse.  Both
+ * vk_set_workspace (the pattern is copied to the host once).  Directly solved
+ * blocks of 384 to 4096 unknowns (any number a level, vk_set_coarse_pivoting 0)
+ * get their dense inverse through the same structure with blocks of at least 64
+ * unknowns, where that is estimated to be faster; such inverses are checked on
+ * a fixed vector before their first use, which waits on the host for them, and
+ * a level that fails the check is inverted by Gauss-Jordan, then and at later
+ * setups.  Blocks without such a structure, and every block under mode 1, get
+ * the dense inverse by Gauss-Jordan with partial pivoting.  All
  * compute J_0^{-1} b up to rounding; a singular block is reported by the first
  * solve either way.  vk_get_coarse_inverse needs the dense inverse.  Setup must
  * run again after a change. */
@@ -347,7 +354,8 @@ vk_status vk_set_coarse_solver(vk_ctx* ctx, int32_t mode);
  * factorisation (0 when its directly solved blocks are inverted densely, -1 for
  * an invalid call), and in *setup_flops (if not null) the algorithmic flop
  * count of one factorisation or inversion (2 sum s_i^3 + 4 sum s_i^2 s_(i+1),
- * or 2 sum m_b^3 for dense inverses of blocks of m_b rows). */
+ * or 2 sum m_b^3 for dense inverses of blocks of m_b rows; inverses through
+ * a chain of blocks count their block products instead). */
 int32_t vk_coarse_plan(vk_ctx* ctx, int32_t level, double* setup_flops);
 
 /* Autotuner: after vanka_setup, times each level's SpMV kernels (J, P, R)

@@ -157,7 +157,16 @@ size_t plan_workspace(vk_ctx* ctx, vk_prec prec, int32_t restart, char* base) {
     if (nbk > 0) {
       L.cb_a = cv.take<double>(L.cb_sq);
       L.bt = vk_bt();  // a block-tridiagonal plan lives in cb_a: made again for the new buffer
-      L.cb_gi = cv.take<double>((int64_t)nbk * VK_GJ_NBI_MAX * VK_GJ_NBO);
+      // a chain plan lives in its own buffers
+      L.chain = vk_chain();
+      L.chain.cap = vk_chain_buffer(L);
+      L.chain.table_cap = vk_chain_table_bytes(L);
+      if (L.chain.cap > 0) {
+        L.chain.buf = cv.take<double>(L.chain.cap);
+        L.chain.table = cv.take<char>(L.chain.table_cap);
+      }
+      // (a chain's elimination step inverts up to two blocks of each block at once)
+      L.cb_gi = cv.take<double>((int64_t)nbk * (L.chain.cap > 0 ? 2 : 1) * VK_GJ_NBI_MAX * VK_GJ_NBO);
       L.cb_go = cv.take<double>((int64_t)VK_GJ_NBO * (L.cb_rows[nbk] - L.cb_rows[0]));
       L.d_cb_rows = cv.take<int64_t>(nbk + 1);
       L.d_cb_woff = cv.take<int64_t>(nbk);
@@ -527,11 +536,37 @@ vk_status replay(vk_ctx* ctx, size_t slot, const int64_t (&key)[6], F&& enqueue)
   return VK_OK;
 }
 
-// Make the context stream wait for the block inversions of the last setup (no host wait).
+// Levels whose chained inverses failed their check are inverted densely, once and for all, before
+// anything uses them (a host wait for the block inversions, on levels with chains only).
+vk_status chain_settle(vk_ctx* ctx) {
+  bool any = false;
+  for (const vk_level& L : ctx->lv) any = any || L.chain.active;
+  if (!any) return VK_OK;
+  for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->side, ctx->xjoin[i], 0));
+  int32_t bad[64];
+  const hipStream_t user = ctx->stream;
+  ctx->stream = ctx->side;
+  const vk_status rc = to_host(ctx, bad, ctx->status + 900, sizeof(bad));
+  ctx->stream = user;
+  VK_CHECK(rc);
+  for (int l = 0; l < ctx->n_levels; ++l) {
+    vk_level& L = ctx->lv[l];
+    if (!L.chain.active || bad[l] == 0) continue;
+    L.chain.active = false;
+    ++ctx->gen;
+    VK_TRY(launch_block_invert(ctx->side, L, ctx->status, &L.cb_W, &ctx->la, ctx->coarse_min_tourney));
+    VK_TRY(hipEventRecord(ctx->join_ev, ctx->side));
+  }
+  return VK_OK;
+}
+
+// Make the context stream wait for the block inversions of the last setup (no host wait but
+// chain_settle's).
 // With check_now the stream is synchronised and their status words are checked at once.
 vk_status coarse_check(vk_ctx* ctx);
 vk_status coarse_wait(vk_ctx* ctx, bool check_now) {
   if (ctx->coarse_pending) {
+    VK_CHECK(chain_settle(ctx));
     VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->join_ev, 0));
     for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->xjoin[i], 0));
     ctx->coarse_pending = false;
@@ -1031,6 +1066,18 @@ vk_status vanka_setup(vk_ctx* ctx, double omega, vk_mode mode, int32_t* bad_leve
       }
       if (L.bt.active || was) ++ctx->gen;
     }
+    if (!L.chain.planned) {
+      const bool was = L.chain.active;
+      L.chain.active = false;
+      L.chain.planned = true;
+      if (ctx->coarse_solver == 0 && ctx->coarse_min_tourney == VK_TOURNEY_MIN_N && !L.bt.active && L.chain.buf) {
+        VK_TRY(hipStreamSynchronize(s));  // the last solve may still read the old plan's tables
+        VK_TRY(hipStreamSynchronize(ctx->side));
+        for (hipStream_t x : ctx->xside) VK_TRY(hipStreamSynchronize(x));
+        (void)vk_chain_plan(L);
+      }
+      if (L.chain.active || was) ++ctx->gen;
+    }
   }
   std::stable_sort(blevels.begin(), blevels.end(),
                    [&](int a, int b) { return ctx->lv[a].cb_max > ctx->lv[b].cb_max; });
@@ -1059,6 +1106,10 @@ vk_status vanka_setup(vk_ctx* ctx, double omega, vk_mode mode, int32_t* bad_leve
       Timed t(ctx, VK_KERNEL_BLOCK_INVERT, blevels[k], st);
       // the level with the largest blocks (the longest chain) gets the look-ahead stream
       if (L.bt.active) VK_TRY(launch_bt_factor(st, L, ctx->status));
+      else if (L.chain.active) {
+        L.cb_W = L.cb_a;
+        VK_TRY(launch_chain_invert(st, L, ctx->status, ctx->status + 964, ctx->status + 900 + blevels[k]));
+      }
       else VK_TRY(launch_block_invert(st, L, ctx->status, &L.cb_W, k == 0 ? &ctx->la : nullptr, ctx->coarse_min_tourney));
     }
     if (k > 0) {
@@ -1639,7 +1690,7 @@ vk_status vk_set_coarse_solver(vk_ctx* ctx, int32_t mode) {
   if (mode != 0 && mode != 1) return fail(ctx, VK_ERR_ARG, "unknown coarse solver");
   if (mode != ctx->coarse_solver) {
     if (ctx->side) (void)hipStreamSynchronize(ctx->side);
-    for (vk_level& L : ctx->lv) L.bt.planned = false;
+    for (vk_level& L : ctx->lv) L.bt.planned = L.chain.planned = false;
   }
   ctx->coarse_solver = mode;
   ctx->setup_done = false;
@@ -1652,6 +1703,10 @@ int32_t vk_coarse_plan(vk_ctx* ctx, int32_t level, double* setup_flops) {
   if (L.bt.active) {
     if (setup_flops) *setup_flops = L.bt.flops;
     return L.bt.nb;
+  }
+  if (L.chain.active) {
+    if (setup_flops) *setup_flops = L.chain.flops;
+    return 0;
   }
   if (setup_flops) {
     double f = 0.0;
@@ -1667,6 +1722,7 @@ int32_t vk_coarse_plan(vk_ctx* ctx, int32_t level, double* setup_flops) {
 vk_status vk_set_coarse_pivoting(vk_ctx* ctx, int32_t mode) {
   if (!ctx) return VK_ERR_ARG;
   if (mode < 0 || mode > 2) return fail(ctx, VK_ERR_ARG, "unknown coarse pivoting mode");
+  for (vk_level& L : ctx->lv) L.chain.planned = false;
   ctx->coarse_min_tourney = mode == 0 ? VK_TOURNEY_MIN_N : (mode == 1 ? INT64_MAX : 0);
   ctx->setup_done = false;
   return VK_OK;

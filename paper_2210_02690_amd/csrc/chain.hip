@@ -1,0 +1,681 @@
+// Dense inverses of directly solved blocks through their block-tridiagonal structure (Sec. 3: a direct
+// solver for J_0 d_0 = b_0 on T_0; the paper names no method).
+//
+// The dense Gauss-Jordan inversion of a block of n unknowns is a chain of n column steps with a pivot
+// search over all rows (about 2 us a step: 1.8 ms for the 888 unknowns of the 176 x 32 channel, 7.1 ms
+// for 2 060).  Breadth-first level sets of the block's pattern from two ends of the mesh make it block
+// tridiagonal (the order of coarse_bt.hip), and the two chains of small blocks are eliminated towards a
+// middle block side by side, for every block of the level at once:
+//   left,  i < c:  X_i = S_i^{-1} U_i,  S_{i+1} = D_{i+1} - L_{i+1} X_i,   S_0 = D_0,
+//   right, i > c:  Y_i = T_i^{-1} L_i,  T_{i-1} = D_{i-1} - U_{i-1} Y_i,   T_{nb-1} = D_{nb-1},
+//   middle:        S_c = D_c - L_c X_{c-1} - U_c Y_{c+1},
+// the S_i, T_i inverted by the register-resident matrix-core kernel (up to VK_ITEM_MAX rows) or the blocked
+// Gauss-Jordan kernels.  Then the whole inverse G grows outwards from G_cc = S_c^{-1}; with M the
+// blocks already there, i the next block on the left and j on the right,
+//   G_iM = -X_i G_{i+1,M},  G_Mi = -G_{M,i+1} Z_i,  G_jM = -Y_j G_{j-1,M},  G_Mj = -G_{M,j-1} W_j,
+//   G_ii = S_i^{-1} - X_i G_{i+1,i},  G_jj = T_j^{-1} - Y_j G_{j-1,j},  G_ij = -X_i G_{i+1,j},
+//   G_ji = -Y_j G_{j-1,i},   Z_i = L_{i+1} S_i^{-1},  W_j = U_{j-1} T_j^{-1},
+// two launches of matrix-core products a step.  The solve stays one product with the dense inverse.
+// Measured, dense -> chain: 592 unknowns (88 x 16, k = 1) 1.14 -> 0.37 ms, 888 (176 x 32, k = 2) 1.79 -> 0.77 ms,
+// 2 060 (88 x 16, Q4) 7.15 -> 2.65 ms, the blocks of 64 systems 17 -> 11.6 ms.  What bounds it now is
+// the chain of pivot steps inside the S_i (0.5 us each up to 176 rows, 1.7 us in the blocked kernels).
+//
+// Pivots are sought inside a chain block only, so a regular matrix can meet a singular or badly
+// conditioned chain block.  Each inverse is therefore checked (max |v - J G v| for a fixed v); a
+// level that fails is inverted densely before the solve goes on, and stays dense.
+#include <algorithm>
+#include <climits>
+#include <vector>
+
+#include "vk_internal.h"
+
+namespace {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// One wavefront per row: a chained row's entries go to D (column-major), U or L (row-major) of its chain
+// block, a row of a dense block to the block (column-major).  cb: the row's chain block, or -1 - b
+// for dense block b; ri: the row's index in it.
+__global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_t n_rows, const int64_t* __restrict__ row_ptr,
+                                                           const int32_t* __restrict__ col,
+                                                           const double* __restrict__ val,
+                                                           const int32_t* __restrict__ cb, const int32_t* __restrict__ ri,
+                                                           const vk_chain_block* __restrict__ blk,
+                                                           const vk_chain_dense* __restrict__ dense, int32_t* status) {
+  const int64_t r = first + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (r >= n_rows) return;
+  const int b = cb[r], i = ri[r];
+  const int64_t e1 = row_ptr[r + 1];
+  if (b < 0) {
+    const vk_chain_dense q = dense[-1 - b];
+    for (int64_t e = row_ptr[r] + lane; e < e1; e += 64) {
+      const int64_t c = (int64_t)col[e] - q.r0;
+      if (c < 0 || c >= q.n) atomicOr(&status[1], 1);
+      else q.w[c * q.n + i] = val[e];
+    }
+    return;
+  }
+  const vk_chain_block q = blk[b];
+  for (int64_t e = row_ptr[r] + lane; e < e1; e += 64) {
+    const int64_t c = col[e];
+    if (c < q.r0 || c >= q.r1) {
+      atomicOr(&status[1], 1);
+      continue;
+    }
+    const int bc = cb[c], j = ri[c];
+    if (bc == b) q.D[(int64_t)j * q.s + i] = val[e];
+    else if (bc == b + 1) q.U[(int64_t)i * q.s_next + j] = val[e];
+    else if (bc == b - 1) q.L[(int64_t)i * q.s_prev + j] = val[e];
+    else atomicOr(&status[1], 2);  // the plan makes this impossible
+  }
+}
+
+// C = base + alpha A B per item (blockIdx.y; x: its tile), A, B row-major, C and base row- or column-major (base null:
+// zero; k = 0 copies).  32 x 32 tiles, a 16 x 16 tile per wavefront on the FP64 matrix cores, 32-step
+// chunks through LDS with the next chunk's loads in flight: the matrices are 50 to 500 wide, so the
+// tiles are small enough to give a launch tens of workgroups.
+__global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __restrict__ items) {
+  const vk_gemm_item p = items[blockIdx.y];
+  constexpr int KC = 32, LA = KC + 2, LB = 32 + 1;
+  __shared__ double As[32 * LA];
+  __shared__ double Bs[KC * LB];
+  const int tn = (p.n + 31) / 32, m0 = (int)blockIdx.x / tn * 32, n0 = (int)blockIdx.x % tn * 32;
+  if (m0 >= p.m) return;  // uniform: the grid covers the largest item
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+  double av[4], bv[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = tid + 256 * q, r = e >> 5, c = e & 31;
+      const bool oka = m0 + r < p.m && k0 + c < p.k, okb = k0 + r < p.k && n0 + c < p.n;
+      const double a = p.A[oka ? (int64_t)(m0 + r) * p.lda + k0 + c : 0];
+      const double b = p.B[okb ? (int64_t)(k0 + r) * p.ldb + n0 + c : 0];
+      av[q] = oka ? a : 0.0;
+      bv[q] = okb ? b : 0.0;
+    }
+  };
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  if (p.k > 0) load(0);
+  for (int k0 = 0; k0 < p.k; k0 += KC) {
+    if (k0 > 0) __syncthreads();  // the previous chunk has been read
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = tid + 256 * q;
+      As[(e >> 5) * LA + (e & 31)] = av[q];
+      Bs[(e >> 5) * LB + (e & 31)] = bv[q];
+    }
+    __syncthreads();
+    if (k0 + KC < p.k) load(k0 + KC);
+#pragma unroll
+    for (int s4 = 0; s4 < KC / 4; ++s4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(As[(wm + l16) * LA + 4 * s4 + l4], Bs[(4 * s4 + l4) * LB + wn + l16], acc,
+                                                 0, 0, 0);
+  }
+  const int c = n0 + wn + l16;
+  if (c >= p.n) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int r = m0 + wm + 4 * v + l4;
+    if (r >= p.m) continue;
+    const int64_t at = p.col_major ? (int64_t)c * p.ldc + r : (int64_t)r * p.ldc + c;
+    const double base = p.base ? p.base[p.col_major ? (int64_t)c * p.ldbase + r : (int64_t)r * p.ldbase + c] : 0.0;
+    p.C[at] = base + p.alpha * acc[v];
+  }
+}
+
+// eliminated blocks (row-major W, pivot rows q) in natural order: out[k][q_j] = W[q_k][j]
+__global__ __launch_bounds__(256) void chain_export_kernel(const vk_chain_export* __restrict__ items) {
+  const vk_chain_export p = items[blockIdx.y];
+  const int64_t total = (int64_t)p.n * p.n;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+    const int k = (int)(e / p.n), j = (int)(e - (int64_t)k * p.n);
+    p.out[(int64_t)k * p.n + p.q[j]] = p.w[(int64_t)p.q[k] * p.n + j];
+  }
+}
+
+// the row and column maps of a densely inverted block's rows are its pivot rows
+__global__ void chain_dense_maps_kernel(const vk_chain_dense* __restrict__ real, const int64_t* __restrict__ rows,
+                                        const int32_t* __restrict__ q, int32_t* rmap, int32_t* cmap) {
+  const vk_chain_dense d = real[blockIdx.y];
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < d.n) rmap[d.r0 + i] = cmap[d.r0 + i] = q[rows[blockIdx.y] + i];
+}
+
+__device__ inline double probe_value(int64_t i) { return 1.0 + 0.125 * (double)(i % 13) - 0.0625 * (double)(i % 7); }
+
+__global__ void chain_probe_kernel(int64_t n, double* v) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    v[i] = probe_value(i);
+}
+
+// flags the level when some chained row's |v - J G v| is not small (entries of v are 0.6 to 2.5; a good
+// inverse leaves 1e-15 times the condition number)
+__global__ void chain_check_kernel(int64_t first, int64_t n, const int32_t* __restrict__ cb, const double* __restrict__ jz,
+                                   int32_t* flag) {
+  for (int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    if (cb[i] >= 0 && !(fabs(jz[i] - probe_value(i)) <= 1e-8)) atomicOr(flag, 1);
+}
+
+// breadth-first levels from `start`; the number reached, and the lowest vertex of the last level
+int64_t bfs(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, int32_t start,
+            std::vector<int32_t>& level, int32_t* last) {
+  level.assign(n, -1);
+  std::vector<int32_t> frontier{start}, next;
+  level[start] = 0;
+  int64_t seen = 1;
+  for (int l = 1; !frontier.empty(); ++l) {
+    next.clear();
+    for (int32_t v : frontier)
+      for (int64_t e = ap[v]; e < ap[v + 1]; ++e)
+        if (level[aj[e]] < 0) {
+          level[aj[e]] = l;
+          next.push_back(aj[e]);
+        }
+    if (next.empty()) *last = *std::min_element(frontier.begin(), frontier.end());
+    seen += (int64_t)next.size();
+    frontier.swap(next);
+  }
+  return seen;
+}
+
+// The chain order of one block from its symmetric adjacency: chain block of every vertex (numbered along
+// the chain) and the middle block c; false if the block has no such structure.  The construction and
+// its reasons are those of vk_bt_plan in coarse_bt.hip, with smaller blocks.
+bool chain_order(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, std::vector<int32_t>& blk,
+                 std::vector<int64_t>& size, int* c) {
+  std::vector<int32_t> d1, d2;
+  int32_t s1 = 0, s2 = 0, tmp = 0;
+  if (bfs(n, ap, aj, 0, d1, &s1) != n || bfs(n, ap, aj, s1, d1, &s2) != n || bfs(n, ap, aj, s2, d2, &tmp) != n)
+    return false;
+  const int dist = d1[s2];
+  int h1 = dist / 2, h2 = dist - h1;
+  if (h1 < 1 || h2 < 1) return false;
+  // the middle block takes level sets of both sides until it has the size of the others
+  std::vector<int64_t> lcnt, rcnt;
+  int64_t nmid = 0;
+  for (;;) {
+    lcnt.assign(h1, 0);
+    rcnt.assign(h2, 0);
+    nmid = 0;
+    for (int64_t v = 0; v < n; ++v) {
+      if (d1[v] < h1) ++lcnt[d1[v]];
+      else if (d2[v] < h2) ++rcnt[d2[v]];
+      else ++nmid;
+    }
+    if (nmid >= VK_CHAIN_MIN_BLOCK || h1 + h2 <= 2) break;
+    if (h2 >= h1) --h2;
+    else --h1;
+  }
+  if (nmid == 0) return false;
+  auto group = [](const std::vector<int64_t>& cnt, std::vector<int32_t>& lb, std::vector<int64_t>& bs) {
+    lb.assign(cnt.size(), 0);
+    for (size_t l = 0; l < cnt.size(); ++l) {
+      if (bs.empty() || bs.back() >= VK_CHAIN_MIN_BLOCK) bs.push_back(0);
+      lb[l] = (int32_t)bs.size() - 1;
+      bs.back() += cnt[l];
+    }
+    if (bs.size() > 1 && bs.back() < VK_CHAIN_MIN_BLOCK) {
+      const int64_t tail = bs.back();
+      bs.pop_back();
+      bs.back() += tail;
+      for (int32_t& b : lb) b = std::min(b, (int32_t)bs.size() - 1);
+    }
+  };
+  std::vector<int32_t> lb, rb;
+  std::vector<int64_t> ls, rs;
+  group(lcnt, lb, ls);
+  group(rcnt, rb, rs);
+  const int nl = (int)ls.size(), nb = nl + 1 + (int)rs.size();
+  size.assign(nb, 0);
+  for (int i = 0; i < nl; ++i) size[i] = ls[i];
+  size[nl] = nmid;
+  for (size_t i = 0; i < rs.size(); ++i) size[nb - 1 - i] = rs[i];
+  blk.resize(n);
+  for (int64_t v = 0; v < n; ++v)
+    blk[v] = d1[v] < h1 ? lb[d1[v]] : (d2[v] < h2 ? nb - 1 - rb[d2[v]] : nl);
+  *c = nl;
+  return true;
+}
+
+// A block is chained where the estimated time of its chain is below 0.8 of the dense inversion's: the
+// estimate (us) for one s-row matrix, the register-resident kernel (80 rows 45 us, 160 rows 123 us) or 16-column
+// panels with their updates (20 + 6 us and the outer updates: 888 rows 1.8 ms); 35 us a step for the
+// products and the launches.
+double invert_us(double s) { return s <= VK_ITEM_MAX ? 20.0 + 0.55 * s : 30.0 * std::ceil(s / 16.0) + 40.0; }
+
+// doubles reserved for a block: a chain of blocks of s rows takes about 6 s n
+int64_t reserve(int64_t n) { return n < VK_CHAIN_MIN_N ? 0 : (n <= 1024 ? 2 : 1) * n * n; }
+
+int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
+
+}  // namespace
+
+int64_t vk_chain_buffer(const vk_level& L) {
+  if (L.cb_rows.size() < 2 || L.cb_max < VK_CHAIN_MIN_N || L.cb_max > VK_TOURNEY_MIN_N) return 0;
+  int64_t need = 3 * up32(L.J.n_rows) + 32;
+  for (size_t b = 0; b + 1 < L.cb_rows.size(); ++b) need += reserve(L.cb_rows[b + 1] - L.cb_rows[b]);
+  return need;
+}
+
+size_t vk_chain_table_bytes(const vk_level& L) {
+  if (vk_chain_buffer(L) == 0) return 0;
+  return (size_t)L.cb_rows.back() * 24 + (L.cb_rows.size() - 1) * (size_t)(160 * 1024) + 65536;
+}
+
+bool vk_chain_plan(vk_level& L) {
+  vk_chain& T = L.chain;
+  double* const buf = T.buf;
+  char* const table = T.table;
+  const int64_t cap = T.cap;
+  const size_t table_cap = T.table_cap;
+  T = vk_chain();
+  T.buf = buf;
+  T.cap = cap;
+  T.table = table;
+  T.table_cap = table_cap;
+  T.planned = true;
+  if (!buf || L.cb_rows.size() < 2) return false;
+  const int nblk = (int)L.cb_rows.size() - 1;
+  const int64_t rows = L.cb_rows.back();
+  std::vector<int64_t> rp(rows + 1);
+  if (hipMemcpy(rp.data(), L.J.row_ptr, sizeof(int64_t) * (rows + 1), hipMemcpyDeviceToHost) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  std::vector<int32_t> cj(rp[rows]);
+  if (rp[rows] > 0 && hipMemcpy(cj.data(), L.J.col, sizeof(int32_t) * rp[rows], hipMemcpyDeviceToHost) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  T.first = L.cb_rows[0];
+  std::vector<int32_t> cb(rows, -1), ri(rows), rmap(rows), cmap(rows);
+  std::vector<vk_chain_block> blocks;
+  std::vector<vk_chain_dense>& dense = T.dense;
+  struct step_lists {
+    std::vector<vk_dense_item> small;
+    std::vector<int> gj;  // chain blocks
+    std::vector<vk_gemm_item> cp, u1, u2;
+  };
+  std::vector<step_lists> steps;
+  std::vector<vk_gemm_item> zw;
+  std::vector<std::vector<vk_gemm_item>> ga, gb;
+  std::vector<double*> dinv;
+  int64_t used = 0;
+  auto take = [&](int64_t n) {
+    double* p = buf + used;
+    used += up32(n);
+    return p;
+  };
+  auto item = [](int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
+                 const double* base, int64_t ldbase, double* C, int64_t ldc, bool cm) {
+    vk_gemm_item g{};
+    g.m = (int32_t)m;
+    g.n = (int32_t)n;
+    g.k = (int32_t)k;
+    g.alpha = alpha;
+    g.A = A;
+    g.lda = (int32_t)lda;
+    g.B = B;
+    g.ldb = (int32_t)ldb;
+    g.base = base;
+    g.ldbase = (int32_t)ldbase;
+    g.C = C;
+    g.ldc = (int32_t)ldc;
+    g.col_major = cm;
+    return g;
+  };
+  struct block_plan {
+    bool ok = false;
+    int c = 0;
+    std::vector<int32_t> blk;
+    std::vector<int64_t> size;
+  };
+  std::vector<block_plan> plans(nblk);
+  // which blocks have a chain that is worth it, and the zero-filled part of the buffer (D, U, L of all)
+  int64_t w0 = 0;
+  std::vector<int64_t> woff(nblk);
+  for (int b = 0; b < nblk; ++b) {
+    const int64_t r0 = L.cb_rows[b], n = L.cb_rows[b + 1] - r0;
+    woff[b] = w0;
+    w0 += n * n;
+    if (n < VK_CHAIN_MIN_N) continue;
+    std::vector<int64_t> ap(n + 1, 0);
+    bool inside = true;
+    for (int64_t r = 0; r < n && inside; ++r)
+      for (int64_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
+        const int64_t c = (int64_t)cj[e] - r0;
+        if (c < 0 || c >= n) {
+          inside = false;  // a coupling outside the block: the dense path reports it
+          break;
+        }
+        if (c != r) {
+          ++ap[r + 1];
+          ++ap[c + 1];
+        }
+      }
+    if (!inside) continue;
+    for (int64_t r = 0; r < n; ++r) ap[r + 1] += ap[r];
+    std::vector<int32_t> aj(ap[n]);
+    std::vector<int64_t> at(ap.begin(), ap.end() - 1);
+    for (int64_t r = 0; r < n; ++r)
+      for (int64_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
+        const int64_t c = (int64_t)cj[e] - r0;
+        if (c != r) {
+          aj[at[r]++] = (int32_t)c;
+          aj[at[c]++] = (int32_t)r;
+        }
+      }
+    block_plan& p = plans[b];
+    if (!chain_order(n, ap, aj, p.blk, p.size, &p.c)) continue;
+    const int nb = (int)p.size.size();
+    if (*std::max_element(p.size.begin(), p.size.end()) > 1024 || *std::min_element(p.size.begin(), p.size.end()) < 16)
+      continue;
+    double us = invert_us((double)p.size[p.c]) + 60.0;
+    for (int k = 0; k < std::max(p.c, nb - 1 - p.c); ++k) {
+      const double a = k < p.c ? invert_us((double)p.size[k]) : 0.0, z = nb - 1 - k > p.c ? invert_us((double)p.size[nb - 1 - k]) : 0.0;
+      us += std::max(a, z) + 35.0;
+    }
+    int64_t need = 0;
+    for (int i = 0; i < nb; ++i) {
+      need += 2 * up32(p.size[i] * p.size[i]);
+      if (i + 1 < nb) need += 4 * up32(p.size[i] * p.size[i + 1]);
+    }
+    if (us > 0.8 * invert_us((double)n) || need > reserve(n)) continue;
+    p.ok = true;
+  }
+  int64_t n_chained = 0;
+  for (int b = 0; b < nblk; ++b) n_chained += plans[b].ok;
+  if (n_chained == 0) return false;
+  std::vector<int> first(nblk, 0);
+  for (int b = 0; b < nblk; ++b) {
+    const int64_t r0 = L.cb_rows[b], n = L.cb_rows[b + 1] - r0;
+    if (!plans[b].ok) {
+      for (int64_t r = 0; r < n; ++r) {
+        cb[r0 + r] = -1 - (int32_t)dense.size();
+        ri[r0 + r] = (int32_t)r;
+      }
+      dense.push_back(vk_chain_dense{L.cb_a + woff[b], r0, n});
+      T.flops += 2.0 * (double)n * n * n;
+      continue;
+    }
+    const block_plan& p = plans[b];
+    const int nb = (int)p.size.size(), f = (int)blocks.size();
+    first[b] = f;
+    std::vector<int64_t> off(nb + 1, 0);
+    for (int i = 0; i < nb; ++i) off[i + 1] = off[i] + p.size[i];
+    std::vector<int64_t> pos(off.begin(), off.end() - 1);
+    for (int64_t v = 0; v < n; ++v) {
+      const int i = p.blk[v];
+      const int64_t q = pos[i]++;
+      cb[r0 + v] = f + i;
+      ri[r0 + v] = (int32_t)(q - off[i]);
+      rmap[r0 + v] = (int32_t)q;
+      cmap[r0 + q] = (int32_t)v;
+    }
+    for (int i = 0; i < nb; ++i) {
+      vk_chain_block q{};
+      q.r0 = r0;
+      q.r1 = r0 + n;
+      q.s = (int32_t)p.size[i];
+      q.s_prev = i > 0 ? (int32_t)p.size[i - 1] : 0;
+      q.s_next = i + 1 < nb ? (int32_t)p.size[i + 1] : 0;
+      q.D = take(p.size[i] * p.size[i]);
+      q.U = i + 1 < nb ? take(p.size[i] * p.size[i + 1]) : nullptr;
+      q.L = i > 0 ? take(p.size[i] * p.size[i - 1]) : nullptr;
+      blocks.push_back(q);
+    }
+  }
+  T.n_zero = used;
+  for (int b = 0; b < nblk; ++b) {
+    if (!plans[b].ok) continue;
+    const block_plan& p = plans[b];
+    const int64_t n = L.cb_rows[b + 1] - L.cb_rows[b];
+    const int nb = (int)p.size.size(), f = first[b], c = p.c;
+    auto sz = [&](int i) { return p.size[i]; };
+    std::vector<int64_t> off(nb + 1, 0);
+    for (int i = 0; i < nb; ++i) off[i + 1] = off[i] + p.size[i];
+    std::vector<double*> inv(nb), X(nb, nullptr), Z(nb, nullptr);
+    for (int i = 0; i < nb; ++i) {
+      inv[i] = take(sz(i) * sz(i));
+      const int j = i < c ? i + 1 : (i > c ? i - 1 : -1);  // the next block inwards
+      if (j >= 0) {
+        X[i] = take(sz(i) * sz(j));  // X_i or Y_i
+        Z[i] = take(sz(j) * sz(i));  // Z_i or W_i
+      }
+      dinv.push_back(inv[i]);
+    }
+    const int ns = std::max(c, nb - 1 - c) + 1;
+    if ((int)steps.size() < ns) steps.resize(ns);
+    if ((int)ga.size() < ns - 1) {
+      ga.resize(ns - 1);
+      gb.resize(ns - 1);
+    }
+    auto invert = [&](step_lists& S, int i) {
+      const double s = (double)sz(i);
+      T.flops += 2.0 * s * s * s;
+      if (sz(i) <= VK_ITEM_MAX) S.small.push_back(vk_dense_item{blocks[f + i].D, inv[i], (int32_t)sz(i)});
+      else S.gj.push_back(f + i);
+    };
+    for (int k = 0; k < ns; ++k) {
+      step_lists& S = steps[k];
+      if (k == ns - 1) {
+        invert(S, c);
+        continue;
+      }
+      bool first_update = true;
+      for (int side = 0; side < 2; ++side) {
+        const int i = side == 0 ? k : nb - 1 - k;
+        if (side == 0 ? i >= c : i <= c) continue;
+        const int j = side == 0 ? i + 1 : i - 1;
+        invert(S, i);
+        const double* out = side == 0 ? blocks[f + i].U : blocks[f + i].L;  // i -> j
+        const double* back = side == 0 ? blocks[f + j].L : blocks[f + j].U;  // j -> i
+        S.cp.push_back(item(sz(i), sz(j), sz(i), 1.0, inv[i], sz(i), out, sz(j), nullptr, 0, X[i], sz(j), false));
+        const vk_gemm_item u = item(sz(j), sz(j), sz(i), -1.0, back, sz(i), X[i], sz(j), blocks[f + j].D, sz(j),
+                                    blocks[f + j].D, sz(j), true);
+        // both chains can reach the middle block in one step: its updates run one after the other
+        if (j == c && !first_update) S.u2.push_back(u);
+        else S.u1.push_back(u);
+        if (j == c) first_update = false;
+        T.flops += 2.0 * sz(i) * sz(i) * sz(j) + 2.0 * sz(j) * sz(j) * sz(i);
+        zw.push_back(item(sz(j), sz(i), sz(i), 1.0, back, sz(i), inv[i], sz(i), nullptr, 0, Z[i], sz(i), false));
+      }
+    }
+    // the whole inverse, outwards from the middle
+    double* G = L.cb_a + woff[b];
+    auto g = [&](int64_t r, int64_t q) { return G + r * n + q; };
+    zw.push_back(item(sz(c), sz(c), 0, 0.0, inv[c], sz(c), inv[c], sz(c), inv[c], sz(c), g(off[c], off[c]), n, false));
+    for (int t = 1; t < ns; ++t) {
+      const int i = c - t, j = c + t;
+      const int64_t a0 = off[std::max(i + 1, 0)], a1 = off[std::min(j, nb)], M = a1 - a0;
+      std::vector<vk_gemm_item>&A = ga[t - 1], &B = gb[t - 1];
+      if (i >= 0) {
+        A.push_back(item(sz(i), M, sz(i + 1), -1.0, X[i], sz(i + 1), g(off[i + 1], a0), n, nullptr, 0, g(off[i], a0), n, false));
+        A.push_back(item(M, sz(i), sz(i + 1), -1.0, g(a0, off[i + 1]), n, Z[i], sz(i), nullptr, 0, g(a0, off[i]), n, false));
+        B.push_back(item(sz(i), sz(i), sz(i + 1), -1.0, X[i], sz(i + 1), g(off[i + 1], off[i]), n, inv[i], sz(i),
+                         g(off[i], off[i]), n, false));
+        T.flops += 4.0 * sz(i) * sz(i + 1) * M;
+      }
+      if (j < nb) {
+        A.push_back(item(sz(j), M, sz(j - 1), -1.0, X[j], sz(j - 1), g(off[j - 1], a0), n, nullptr, 0, g(off[j], a0), n, false));
+        A.push_back(item(M, sz(j), sz(j - 1), -1.0, g(a0, off[j - 1]), n, Z[j], sz(j), nullptr, 0, g(a0, off[j]), n, false));
+        B.push_back(item(sz(j), sz(j), sz(j - 1), -1.0, X[j], sz(j - 1), g(off[j - 1], off[j]), n, inv[j], sz(j),
+                         g(off[j], off[j]), n, false));
+        T.flops += 4.0 * sz(j) * sz(j - 1) * M;
+      }
+      if (i >= 0 && j < nb) {
+        B.push_back(item(sz(i), sz(j), sz(i + 1), -1.0, X[i], sz(i + 1), g(off[i + 1], off[j]), n, nullptr, 0,
+                         g(off[i], off[j]), n, false));
+        B.push_back(item(sz(j), sz(i), sz(j - 1), -1.0, X[j], sz(j - 1), g(off[j - 1], off[i]), n, nullptr, 0,
+                         g(off[j], off[i]), n, false));
+      }
+    }
+  }
+  T.v = take(L.J.n_rows);
+  T.z = take(L.J.n_rows);
+  T.jz = take(L.J.n_rows);
+  if (used > cap) return false;
+  // upload the tables
+  size_t tused = 0;
+  bool ok = true;
+  auto put = [&](const void* src, size_t bytes) -> char* {
+    tused = (tused + 63) / 64 * 64;
+    char* dst = table + tused;
+    if (!ok || tused + bytes > table_cap) {
+      ok = false;
+      return nullptr;
+    }
+    if (bytes > 0 && hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess) {
+      (void)hipGetLastError();
+      ok = false;
+    }
+    tused += bytes;
+    return dst;
+  };
+  auto put_gemm = [&](const std::vector<vk_gemm_item>& v) {
+    vk_gemm_list l;
+    l.count = (int)v.size();
+    for (const vk_gemm_item& g : v) l.tiles = std::max<int64_t>(l.tiles, (int64_t)((g.m + 31) / 32) * ((g.n + 31) / 32));
+    l.items = reinterpret_cast<vk_gemm_item*>(put(v.data(), v.size() * sizeof(vk_gemm_item)));
+    return l;
+  };
+  T.cb = reinterpret_cast<int32_t*>(put(cb.data(), rows * 4));
+  T.ri = reinterpret_cast<int32_t*>(put(ri.data(), rows * 4));
+  T.rmap = reinterpret_cast<int32_t*>(put(rmap.data(), rows * 4));
+  T.cmap = reinterpret_cast<int32_t*>(put(cmap.data(), rows * 4));
+  T.blocks = reinterpret_cast<vk_chain_block*>(put(blocks.data(), blocks.size() * sizeof(vk_chain_block)));
+  T.d_dense = reinterpret_cast<vk_chain_dense*>(put(dense.data(), dense.size() * sizeof(vk_chain_dense)));
+  T.rows = rows;
+  for (step_lists& S : steps) {
+    vk_chain_step st;
+    // the widest first: the launch's workgroups of the longest chains start first
+    std::stable_sort(S.small.begin(), S.small.end(), [](const vk_dense_item& a, const vk_dense_item& b) { return a.n > b.n; });
+    st.n_small = (int)S.small.size();
+    st.small_max = st.n_small ? S.small[0].n : 0;
+    st.small = reinterpret_cast<vk_dense_item*>(put(S.small.data(), S.small.size() * sizeof(vk_dense_item)));
+    if (!S.gj.empty()) {
+      std::vector<int64_t> gr{0}, gw;
+      std::vector<vk_chain_export> ex;
+      for (int i : S.gj) {
+        const int64_t s = blocks[i].s;
+        gw.push_back(blocks[i].D - buf);
+        ex.push_back(vk_chain_export{blocks[i].D, L.cb_q + gr.back(), dinv[i], (int32_t)s});
+        gr.push_back(gr.back() + s);
+        st.gj_max = std::max(st.gj_max, s);
+      }
+      st.gj_rows = gr;
+      st.d_gj_rows = reinterpret_cast<int64_t*>(put(gr.data(), gr.size() * 8));
+      st.d_gj_woff = reinterpret_cast<int64_t*>(put(gw.data(), gw.size() * 8));
+      st.gj_export = reinterpret_cast<vk_chain_export*>(put(ex.data(), ex.size() * sizeof(vk_chain_export)));
+    }
+    st.cp = put_gemm(S.cp);
+    st.u1 = put_gemm(S.u1);
+    st.u2 = put_gemm(S.u2);
+    T.steps.push_back(st);
+  }
+  T.zw = put_gemm(zw);
+  for (size_t t = 0; t < ga.size(); ++t) {
+    T.ga.push_back(put_gemm(ga[t]));
+    T.gb.push_back(put_gemm(gb[t]));
+  }
+  // dense blocks in classes of the panel kernels' widths (a class runs at its widest block's speed)
+  const int64_t cls[4] = {512, 1024, 1536, VK_TOURNEY_MIN_N};
+  for (int k = 0; k < 4; ++k) {
+    vk_chain_rest R;
+    std::vector<vk_chain_dense> real;
+    std::vector<int64_t> gr{0}, gw;
+    for (const vk_chain_dense& q : dense) {
+      if (q.n > cls[k] || (k > 0 && q.n <= cls[k - 1])) continue;
+      real.push_back(q);
+      gw.push_back(q.w - L.cb_a);
+      gr.push_back(gr.back() + q.n);
+    }
+    if (real.empty()) continue;
+    R.rows = gr;
+    R.d_rows = reinterpret_cast<int64_t*>(put(gr.data(), gr.size() * 8));
+    R.d_woff = reinterpret_cast<int64_t*>(put(gw.data(), gw.size() * 8));
+    R.d_real = reinterpret_cast<vk_chain_dense*>(put(real.data(), real.size() * sizeof(vk_chain_dense)));
+    T.rest.push_back(R);
+  }
+  if (!ok) return false;
+  T.active = true;
+  return true;
+}
+
+static hipError_t gemm_list(hipStream_t s, const vk_gemm_list& l) {
+  if (l.count == 0) return hipSuccess;
+  chain_gemm_kernel<<<dim3((unsigned)l.tiles, (unsigned)l.count), 256, 0, s>>>(l.items);
+  return hipGetLastError();
+}
+
+hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status, int32_t* scratch, int32_t* flag) {
+  const vk_chain& T = L.chain;
+  hipError_t e;
+  auto virtual_level = [&](double* base, const std::vector<int64_t>& rows, int64_t* d_rows, int64_t* d_woff) {
+    vk_level V;
+    V.cb_rows = rows;
+    for (size_t b = 0; b + 1 < rows.size(); ++b) V.cb_max = std::max(V.cb_max, rows[b + 1] - rows[b]);
+    V.d_cb_rows = d_rows;
+    V.d_cb_woff = d_woff;
+    V.cb_a = V.cb_W = base;
+    V.cb_q = L.cb_q;
+    V.cb_used = L.cb_used;
+    V.cb_gi = L.cb_gi;
+    V.cb_go = L.cb_go;
+    return V;
+  };
+  if ((e = launch_fill(s, T.n_zero, 0.0, T.buf)) != hipSuccess) return e;
+  for (size_t i = 0; i < T.dense.size();) {  // runs of adjacent dense blocks
+    size_t j = i;
+    int64_t len = 0;
+    for (; j < T.dense.size() && T.dense[j].w == T.dense[i].w + len; ++j) len += T.dense[j].n * T.dense[j].n;
+    if ((e = launch_fill(s, len, 0.0, T.dense[i].w)) != hipSuccess) return e;
+    i = j;
+  }
+  if ((e = launch_fill_i32(s, 1, INT_MAX, scratch)) != hipSuccess) return e;
+  chain_gather_kernel<<<(unsigned)((T.rows - T.first + 3) / 4), 256, 0, s>>>(T.first, T.rows, L.J.row_ptr, L.J.col, L.J.val, T.cb, T.ri,
+                                                                   T.blocks, T.d_dense, status);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  for (const vk_chain_step& S : T.steps) {
+    // a chain block without a pivot only marks `scratch`: the check decides
+    if ((e = launch_invert_items(s, S.n_small, S.small_max, S.small, scratch)) != hipSuccess) return e;
+    if (S.gj_rows.size() > 1) {
+      const vk_level V = virtual_level(T.buf, S.gj_rows, S.d_gj_rows, S.d_gj_woff);
+      if ((e = launch_block_invert_dense_any(s, V, scratch)) != hipSuccess) return e;
+      chain_export_kernel<<<dim3((unsigned)std::min<int64_t>((S.gj_max * S.gj_max + 255) / 256, 1024),
+                                 (unsigned)(S.gj_rows.size() - 1)),
+                            256, 0, s>>>(S.gj_export);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if ((e = gemm_list(s, S.cp)) != hipSuccess) return e;
+    if ((e = gemm_list(s, S.u1)) != hipSuccess) return e;
+    if ((e = gemm_list(s, S.u2)) != hipSuccess) return e;
+  }
+  if ((e = gemm_list(s, T.zw)) != hipSuccess) return e;
+  for (size_t t = 0; t < T.ga.size(); ++t) {
+    if ((e = gemm_list(s, T.ga[t])) != hipSuccess) return e;
+    if ((e = gemm_list(s, T.gb[t])) != hipSuccess) return e;
+  }
+  for (const vk_chain_rest& R : T.rest) {
+    const vk_level V = virtual_level(L.cb_a, R.rows, R.d_rows, R.d_woff);
+    if ((e = launch_block_invert_dense_any(s, V, status)) != hipSuccess) return e;
+    chain_dense_maps_kernel<<<dim3((unsigned)((V.cb_max + 255) / 256), (unsigned)(R.rows.size() - 1)), 256, 0, s>>>(
+        R.d_real, R.d_rows, L.cb_q, T.rmap, T.cmap);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  // the check: v - J (G v) on the chained rows
+  const int64_t nr = T.rows - T.first;
+  const unsigned g = (unsigned)std::min<int64_t>((nr + 255) / 256, 1024);
+  chain_probe_kernel<<<g, 256, 0, s>>>(T.rows, T.v);
+  if ((e = launch_fill_i32(s, 1, 0, flag)) != hipSuccess) return e;
+  if ((e = launch_block_apply(s, L, T.v, T.z)) != hipSuccess) return e;
+  vk_csr A = L.J;
+  A.n_rows = nr;
+  A.row_ptr += T.first;
+  if ((e = launch_spmv(s, A, L.lpr_J, 1.0, T.z, 0.0, nullptr, T.jz + T.first)) != hipSuccess) return e;
+  chain_check_kernel<<<g, 256, 0, s>>>(T.first, T.rows, T.cb, T.jz, flag);
+  return hipGetLastError();
+}

@@ -659,7 +659,8 @@ __global__ __launch_bounds__(256) void block_transpose_kernel(const int64_t* __r
 __global__ __launch_bounds__(256) void block_apply_kernel(int n_blocks, const int64_t* __restrict__ rows,
                                                           const int64_t* __restrict__ woff,
                                                           const double* __restrict__ W_,
-                                                          const int32_t* __restrict__ q_all,
+                                                          const int32_t* __restrict__ rmap,
+                                                          const int32_t* __restrict__ cmap,
                                                           const double* __restrict__ x, double* __restrict__ y) {
   const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
@@ -667,8 +668,8 @@ __global__ __launch_bounds__(256) void block_apply_kernel(int n_blocks, const in
   const int64_t r = rows[0] + t;
   const int b = block_of(rows, n_blocks, r);
   const int64_t r0 = rows[b], n = rows[b + 1] - r0, k = r - r0;
-  const int32_t* q = q_all + r0;
-  const double* w = W_ + woff[b] + (int64_t)q[k] * n;
+  const int32_t* q = cmap + r0;
+  const double* w = W_ + woff[b] + (int64_t)rmap[r] * n;
   // four independent (q, x[q], w) load chains in flight per lane
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   int64_t j = lane;
@@ -687,12 +688,12 @@ __global__ __launch_bounds__(256) void block_apply_kernel(int n_blocks, const in
 }
 
 // out[k][q_j] = W_b[q_k][j]: block b's inverse in natural order
-__global__ void block_export_kernel(int64_t n, const double* __restrict__ W, const int32_t* __restrict__ q,
-                                    double* out) {
+__global__ void block_export_kernel(int64_t n, const double* __restrict__ W, const int32_t* __restrict__ rmap,
+                                    const int32_t* __restrict__ cmap, double* out) {
   const int64_t total = n * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t k = e / n, j = e - k * n;
-    out[k * n + q[j]] = W[(int64_t)q[k] * n + j];
+    out[k * n + cmap[j]] = W[(int64_t)rmap[k] * n + j];
   }
 }
 
@@ -762,6 +763,31 @@ hipError_t run_blocked(hipStream_t s, const vk_level& L, int32_t* status, int32_
   return hipGetLastError();
 }
 
+// column-by-column pivoting, by the widest block
+hipError_t run_columns(hipStream_t s, const vk_level& L, int32_t* status, const vk_lookahead* la = nullptr) {
+  // panel rows per thread R, panel width NB: R * NB <= 64 doubles in registers (<= 36 at
+  // 1024 threads, whose waves may hold 128 registers each)
+  // outer blocks of 128 columns halve the passes of the rank-NBO updates over the blocks (HBM
+  // traffic) at twice the inner updates' width: worth it for one or a few blocks, whose updates
+  // are few workgroups wide; many blocks per level keep 64
+  // (512 threads x 3 rows keep the 16-column panels up to 1 536 rows: one block of 1 184 rows 3.58 -> 2.66
+  // ms, of 1 500 rows 4.78 -> 3.57 ms, twenty of 1 500 rows 10.9 -> 8.9 ms against 8-column panels; with 4
+  // or 5 rows a thread the wide panels no longer pay: 2 060 rows 7.15 -> 7.44 ms)
+  const int64_t m = L.cb_max;
+  const bool wide = (int)L.cb_rows.size() - 1 <= 8;
+  if (m <= 1024)
+    return wide ? run_blocked<512, 2, 16, 128>(s, L, status, -1, la) : run_blocked<512, 2, 16, 64>(s, L, status, -1, la);
+  if (m <= 1536)
+    return wide ? run_blocked<512, 3, 16, 128>(s, L, status, -1, la) : run_blocked<512, 3, 16, 64>(s, L, status, -1, la);
+  if (m <= 2048)
+    return wide ? run_blocked<256, 8, 8, 128>(s, L, status, -1, la) : run_blocked<256, 8, 8, 64>(s, L, status, -1, la);
+  if (m <= 4096)
+    return wide ? run_blocked<512, 8, 8, 128>(s, L, status, -1, la) : run_blocked<512, 8, 8, 64>(s, L, status, -1, la);
+  if (m <= 8192)
+    return wide ? run_blocked<1024, 8, 4, 128>(s, L, status, -1, la) : run_blocked<1024, 8, 4, 64>(s, L, status, -1, la);
+  return wide ? run_blocked<1024, 9, 4, 128>(s, L, status, -1, la) : run_blocked<1024, 9, 4, 64>(s, L, status, -1, la);
+}
+
 }  // namespace
 
 int64_t vk_coarse_max_n() { return 9216; }
@@ -778,35 +804,14 @@ hipError_t launch_block_invert(hipStream_t s, const vk_level& L, int32_t* status
       nbk, L.d_cb_rows, L.d_cb_woff, L.J.row_ptr, L.J.col, L.J.val, L.cb_a, status);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_fill_i32(s, L.J.n_rows, 0, L.cb_used)) != hipSuccess) return e;
-  // panel rows per thread R, panel width NB: R * NB <= 64 doubles in registers (<= 36 at
-  // 1024 threads, whose waves may hold 128 registers each)
-  // outer blocks of 128 columns halve the passes of the rank-NBO updates over the blocks (HBM
-  // traffic) at twice the inner updates' width: worth it for one or a few blocks, whose updates
-  // are few workgroups wide; many blocks per level keep 64
-  // (512 threads x 3 rows keep the 16-column panels up to 1 536 rows: one block of 1 184 rows 3.58 -> 2.66
-  // ms, of 1 500 rows 4.78 -> 3.57 ms, twenty of 1 500 rows 10.9 -> 8.9 ms against 8-column panels; with 4
-  // or 5 rows a thread the wide panels no longer pay: 2 060 rows 7.15 -> 7.44 ms)
-  const int64_t m = L.cb_max;
-  const bool wide = nbk <= 8;
-  if (m > min_tourney) {
+  if (L.cb_max > min_tourney) {
+    const int64_t m = L.cb_max;
     // proposals: TP per TL rows, at most one per thread of the final round
     if ((m + TL - 1) / TL * TP > 64 * TRW || L.cb_cand_stride < (m + TL - 1) / TL * TP) return hipErrorInvalidValue;
-    return wide ? run_blocked<256, 1, TP, VK_TOURNEY_NBO, true>(s, L, status, -1, la)
-                : run_blocked<256, 1, TP, 64, true>(s, L, status, -1, la);
+    return nbk <= 8 ? run_blocked<256, 1, TP, VK_TOURNEY_NBO, true>(s, L, status, -1, la)
+                    : run_blocked<256, 1, TP, 64, true>(s, L, status, -1, la);
   }
-  if (m <= 1024)
-    e = wide ? run_blocked<512, 2, 16, 128>(s, L, status, -1, la) : run_blocked<512, 2, 16, 64>(s, L, status, -1, la);
-  else if (m <= 1536)
-    e = wide ? run_blocked<512, 3, 16, 128>(s, L, status, -1, la) : run_blocked<512, 3, 16, 64>(s, L, status, -1, la);
-  else if (m <= 2048)
-    e = wide ? run_blocked<256, 8, 8, 128>(s, L, status, -1, la) : run_blocked<256, 8, 8, 64>(s, L, status, -1, la);
-  else if (m <= 4096)
-    e = wide ? run_blocked<512, 8, 8, 128>(s, L, status, -1, la) : run_blocked<512, 8, 8, 64>(s, L, status, -1, la);
-  else if (m <= 8192)
-    e = wide ? run_blocked<1024, 8, 4, 128>(s, L, status, -1, la) : run_blocked<1024, 8, 4, 64>(s, L, status, -1, la);
-  else
-    e = wide ? run_blocked<1024, 9, 4, 128>(s, L, status, -1, la) : run_blocked<1024, 9, 4, 64>(s, L, status, -1, la);
-  return e;
+  return run_columns(s, L, status, la);
 }
 
 hipError_t launch_block_invert_dense_any(hipStream_t s, const vk_level& L, int32_t* status) {
@@ -814,13 +819,7 @@ hipError_t launch_block_invert_dense_any(hipStream_t s, const vk_level& L, int32
   if (nbk <= 0) return hipSuccess;
   const hipError_t e = launch_fill_i32(s, L.cb_rows[nbk] - L.cb_rows[0], 0, L.cb_used);
   if (e != hipSuccess) return e;
-  const int64_t m = L.cb_max;
-  if (m <= 1024) return run_blocked<512, 2, 16, 128>(s, L, status);
-  if (m <= 1536) return run_blocked<512, 3, 16, 128>(s, L, status);
-  if (m <= 2048) return run_blocked<256, 8, 8, 128>(s, L, status);
-  if (m <= 4096) return run_blocked<512, 8, 8, 128>(s, L, status);
-  if (m <= 8192) return run_blocked<1024, 8, 4, 128>(s, L, status);
-  return run_blocked<1024, 9, 4, 128>(s, L, status);
+  return run_columns(s, L, status);
 }
 
 hipError_t launch_blocks_invert_dense(hipStream_t s, const vk_level& L, int32_t* status, int32_t bad_base) {
@@ -839,7 +838,8 @@ hipError_t launch_block_apply(hipStream_t s, const vk_level& L, const double* x,
   if (nbk <= 0) return hipSuccess;
   const int64_t rows_total = L.cb_rows[nbk] - L.cb_rows[0];
   block_apply_kernel<<<(unsigned)((rows_total * 64 + 255) / 256), 256, 0, s>>>(nbk, L.d_cb_rows, L.d_cb_woff,
-                                                                              L.cb_W, L.cb_q, x, y);
+                                                                              L.cb_W, L.chain.active ? L.chain.rmap : L.cb_q,
+                                                                              L.chain.active ? L.chain.cmap : L.cb_q, x, y);
   return hipGetLastError();
 }
 
@@ -853,6 +853,8 @@ hipError_t launch_block_export(hipStream_t s, const vk_level& L, int32_t block, 
   int64_t g = (n * n + 255) / 256;
   if (g > 8192) g = 8192;
   if (g < 1) g = 1;
-  block_export_kernel<<<(unsigned)g, 256, 0, s>>>(n, L.cb_W + woff, L.cb_q + L.cb_rows[block], out);
+  const int64_t r0 = L.cb_rows[block];
+  block_export_kernel<<<(unsigned)g, 256, 0, s>>>(n, L.cb_W + woff, (L.chain.active ? L.chain.rmap : L.cb_q) + r0,
+                                                  (L.chain.active ? L.chain.cmap : L.cb_q) + r0, out);
   return hipGetLastError();
 }

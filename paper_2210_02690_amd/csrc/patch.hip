@@ -1069,15 +1069,16 @@ __device__ inline double recip_f64(double a) {
 // (the register arrays are never indexed at run time) and the branches depend on wave-uniform
 // values only.
 // ---------------------------------------------------------------------------
-template <int N> struct MfCfg {
-  static constexpr int NP = (N + 15) / 16 * 16;  // padded width
-  static constexpr int T = NP / 16;              // tiles per dimension = wavefronts
+template <int T> struct MfCfg {
+  static constexpr int NP = 16 * T;              // padded width
   static constexpr int NT = 64 * (T + 1);       // T tile-row wavefronts and the panel wavefront
   static constexpr int NB = 4;                   // panel width (one MFMA depth)
   static constexpr int R = (NP + 63) / 64;       // panel rows per lane
   static constexpr int PW = T;                   // the wavefront that eliminates the panels
   static constexpr int PLD = NB + 1;             // LDS row length of a panel (doubles)
 };
+// where the matrices come from: a search of the CSR rows, the patch entry map, or dense matrices
+enum { SRC_SEARCH = 0, SRC_MAP = 1, SRC_DENSE = 2 };
 
 // The patch entry map of the matrix-core kernel, planned once per pattern: for every cell and every
 // accumulator element of its T x T tiles (the layout above: tile (I, J), lane l, element v hold
@@ -1152,13 +1153,14 @@ __global__ __launch_bounds__(512) void patch_map_kernel(const int64_t* __restric
   for (int e = tid; e < ME / 4; e += NT) out[e] = reinterpret_cast<const uint64_t*>(sm)[e];
 }
 
-template <int P, int N, bool MAP>
-__global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
+template <int P, int T, int SRC>
+__global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
-    const int32_t* __restrict__ cell_dofs, const uint64_t* __restrict__ pmap, void* inv_out, int32_t ld,
-    int64_t cell_stride, int32_t* status) {
-  using C = MfCfg<N>;
-  constexpr int NP = C::NP, T = C::T, NT = C::NT, NB = C::NB, R = C::R, PW = C::PW, PLD = C::PLD;
+    const int32_t* __restrict__ cell_dofs, const uint64_t* __restrict__ pmap, int32_t n_K, void* inv_out, int32_t ld_,
+    int64_t cell_stride, const vk_dense_item* __restrict__ items, int32_t* status) {
+  using C = MfCfg<T>;
+  constexpr bool MAP = SRC != SRC_SEARCH;  // no hash table
+  constexpr int NP = C::NP, NT = C::NT, NB = C::NB, R = C::R, PW = C::PW, PLD = C::PLD;
   static_assert(R <= 4 && NP <= 256, "patch width");
   __shared__ int qs[NP], kinv[NP];
   __shared__ __align__(16) int pq[2][NB];  // the panel's pivot rows (-1: none), double-buffered
@@ -1167,11 +1169,14 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
   __shared__ double pc[2][NP * PLD];      // the next panel's columns before its last update
   __shared__ double bs[2][NB * NP];       // old pivot rows (double-buffered)
   __shared__ int2 htab[MAP ? 1 : PatchHash::SLOTS];  // DoF -> local index
-  __shared__ int64_t rbeg[MAP ? 1 : N];              // first CSR entry of each patch row
+  __shared__ int64_t rbeg[MAP ? 1 : NP];             // first CSR entry of each patch row
   __shared__ int rlen[NP];                           // CSR entries per patch row (0 beyond N)
   __shared__ int pre[17];
   __shared__ int bad_s;
   const int K = blockIdx.x;
+  const int N = SRC == SRC_DENSE ? items[K].n : (SRC == SRC_SEARCH ? 170 : n_K);  // the width (a search: 170 only)
+  const int ld = SRC == SRC_DENSE ? N : ld_;
+  if (N <= 0) return;                                     // uniform
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // this wavefront's tile row
   const int l16 = lane & 15, l4 = lane >> 4;
@@ -1187,7 +1192,22 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
   f64x4_t acc[T];
 #pragma unroll
   for (int J = 0; J < T; ++J) acc[J] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-  if constexpr (MAP) {
+  if constexpr (SRC == SRC_DENSE) {
+    // the stored matrix read by rows (a column-major matrix transposed: so is its inverse)
+    if (w < T) {
+      const double* A = items[K].a;
+#pragma unroll
+      for (int J = 0; J < T; ++J)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = 16 * w + 4 * v + l4, j = 16 * J + l16;
+          const bool ok = i < N && j < N;
+          const double x = A[ok ? (int64_t)i * N + j : 0];
+          acc[J][v] = ok ? x : 0.0;
+        }
+    }
+    __syncthreads();
+  } else if constexpr (MAP) {
     // ---- gather through the patch entry map: every load of the tile row issued at once ----
     if (w < T) {  // the tile-row wavefronts
       int64_t rb[4];  // first CSR entry of this lane's rows 16 w + 4 v + l / 16
@@ -1247,9 +1267,9 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
   //      wavefronts finish panel j's update.  The two kinds of wavefront run separate loops with
   //      the same sequence of barriers (the panel wavefront holds no tiles, so none of its
   //      registers go to them) ----
-  constexpr int NPAN = (N + NB - 1) / NB;
+  const int NPAN = (N + NB - 1) / NB;
   using S = typename PT<P>::S;
-  S* out = reinterpret_cast<S*>(inv_out) + (int64_t)K * cell_stride;
+  S* out = SRC == SRC_DENSE ? reinterpret_cast<S*>(items[K].out) : reinterpret_cast<S*>(inv_out) + (int64_t)K * cell_stride;
   // output: J_K^{-1}[kinv[i]][q_j] = W[i][j], one 16-column block at a time through LDS; every
   // thread copies its share of block J from stage to the output columns
   constexpr int OW = (16 * NP + NT - 1) / NT;  // output elements per thread and block
@@ -1272,7 +1292,7 @@ __global__ __launch_bounds__(MfCfg<N>::NT) void patch_setup_mfma_kernel(
       if (cq[o] >= 0) out[(int64_t)cq[o] * ld + r] = store_cvt<P>(xv[o]);
     }
   };
-  static_assert(NPAN >= 2 && 2 * NB <= 16, "two panels in the first tile column");
+  static_assert(2 * NB <= 16, "two panels in the first tile column");
   // panels 0 and 1: their columns to LDS
   if (w < T) {
     if (l16 < 2 * NB) {
@@ -1733,8 +1753,8 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
                                                           L.ld, L.cell_stride, status)
 #define VK_MFMA_CASE(NN)                                                                     \
   case NN:                                                                                   \
-    patch_setup_mfma_kernel<P, NN, true><<<L.n_cells, MfCfg<NN>::NT, 0, s>>>(                \
-        J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.inv, L.ld, L.cell_stride, status);       \
+    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP><<<L.n_cells, MfCfg<(NN + 15) / 16>::NT, 0, s>>>( \
+        J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);   \
     return hipGetLastError();
   if (mapped) {
     if (L.n_K <= 64) {
@@ -1747,7 +1767,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
       return hipGetLastError();
     }
     switch (L.n_K) {
-      VK_MFMA_CASE(84)
+      case 84:
       VK_MFMA_CASE(85)
       VK_MFMA_CASE(105)
       VK_MFMA_CASE(120)
@@ -1779,8 +1799,8 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #undef VK_WIDE_CASE
     case 170:
       if (mfma)
-        patch_setup_mfma_kernel<P, 170, false><<<L.n_cells, MfCfg<170>::NT, 0, s>>>(
-            J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.inv, L.ld, L.cell_stride, status);
+        patch_setup_mfma_kernel<P, 11, SRC_SEARCH><<<L.n_cells, MfCfg<11>::NT, 0, s>>>(
+            J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);
       else
         patch_setup_wide_kernel<P, 170><<<L.n_cells, 64 * WideCfg<170>::NW, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, L.inv, L.ld, L.cell_stride, status);
@@ -2027,6 +2047,31 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
 }
 
 }  // namespace
+
+template <int T>
+static hipError_t invert_items(hipStream_t s, int n_items, const vk_dense_item* items, int32_t* status) {
+  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE><<<(unsigned)n_items, MfCfg<T>::NT, 0, s>>>(
+      nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, 0, items, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_invert_items(hipStream_t s, int n_items, int n_max, const vk_dense_item* items, int32_t* status) {
+  if (n_items <= 0) return hipSuccess;
+  switch ((n_max + 15) / 16) {
+    case 1:
+    case 2: return invert_items<2>(s, n_items, items, status);
+    case 3: return invert_items<3>(s, n_items, items, status);
+    case 4: return invert_items<4>(s, n_items, items, status);
+    case 5: return invert_items<5>(s, n_items, items, status);
+    case 6: return invert_items<6>(s, n_items, items, status);
+    case 7: return invert_items<7>(s, n_items, items, status);
+    case 8: return invert_items<8>(s, n_items, items, status);
+    case 9: return invert_items<9>(s, n_items, items, status);
+    case 10: return invert_items<10>(s, n_items, items, status);
+    case 11: return invert_items<11>(s, n_items, items, status);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 int64_t vk_patch_map_elems(int32_t n_K) { return (int64_t)mfma_tiles(n_K) * mfma_tiles(n_K) * 256; }
 

@@ -163,6 +163,80 @@ struct vk_bt {
   int64_t *d_prows = nullptr, *d_pwoff = nullptr;
 };
 
+// A dense FP64 matrix to be inverted by the register-resident matrix-core kernel (n <= VK_ITEM_MAX): a is
+// column-major, out receives the inverse row-major; n <= 0: nothing.
+#define VK_ITEM_MAX 176
+struct vk_dense_item {
+  const double* a;
+  double* out;
+  int32_t n;
+};
+
+// Dense inverses of directly solved blocks through a chain of small blocks (chain.hip): the plan is
+// made on the host once per pattern and workspace; buffers and tables lie in reserved workspace.
+#define VK_CHAIN_MIN_N 384     // narrower blocks are inverted densely
+#define VK_CHAIN_MIN_BLOCK 64  // consecutive level sets are grouped into chain blocks of at least this size
+struct vk_chain_block {  // D column-major s x s, U row-major s x s_next, L row-major s x s_prev
+  double *D, *U, *L;
+  int64_t r0, r1;  // rows of the directly solved block it belongs to
+  int32_t s, s_prev, s_next;
+};
+struct vk_chain_dense {  // a densely inverted block of a level with chains
+  double* w;
+  int64_t r0, n;
+};
+struct vk_gemm_item {  // C = base + alpha A B
+  const double *A, *B, *base;
+  double* C;
+  double alpha;
+  int32_t m, n, k, lda, ldb, ldbase, ldc, col_major;
+};
+struct vk_gemm_list {
+  vk_gemm_item* items = nullptr;  // device
+  int count = 0;
+  int64_t tiles = 0;  // 32 x 32 tiles of the largest item
+};
+struct vk_chain_export {
+  const double* w;
+  const int32_t* q;
+  double* out;
+  int32_t n;
+};
+struct vk_chain_step {
+  int n_small = 0, small_max = 0;
+  vk_dense_item* small = nullptr;   // device
+  std::vector<int64_t> gj_rows;     // blocks wider than VK_ITEM_MAX: row offsets
+  int64_t gj_max = 0;
+  int64_t *d_gj_rows = nullptr, *d_gj_woff = nullptr;
+  vk_chain_export* gj_export = nullptr;  // device
+  vk_gemm_list cp, u1, u2;
+};
+struct vk_chain_rest {  // densely inverted blocks of one width class
+  std::vector<int64_t> rows;
+  int64_t *d_rows = nullptr, *d_woff = nullptr;
+  vk_chain_dense* d_real = nullptr;
+};
+struct vk_chain {
+  bool planned = false, active = false;
+  double* buf = nullptr;  // reserved space: cap doubles, table_cap bytes
+  int64_t cap = 0;
+  char* table = nullptr;
+  size_t table_cap = 0;
+  int64_t first = 0, rows = 0;  // the blocks' rows [first, rows)
+  int64_t n_zero = 0;           // leading doubles of buf cleared before the gather
+  double flops = 0.0;
+  int32_t *cb = nullptr, *ri = nullptr;      // per row: chain block (-1 - b: dense block b), index in it
+  int32_t *rmap = nullptr, *cmap = nullptr;  // row k of the inverse is row rmap[k] of cb_a, its column j belongs to cmap[j]
+  vk_chain_block* blocks = nullptr;
+  vk_chain_dense* d_dense = nullptr;
+  std::vector<vk_chain_dense> dense;
+  std::vector<vk_chain_step> steps;
+  vk_gemm_list zw;
+  std::vector<vk_gemm_list> ga, gb;
+  std::vector<vk_chain_rest> rest;
+  double *v = nullptr, *z = nullptr, *jz = nullptr;
+};
+
 struct vk_level {
   bool set = false;
   vk_csr J{}, P{}, R{};
@@ -202,6 +276,7 @@ struct vk_level {
   double* cb_prs = nullptr;
   int32_t* cb_pq = nullptr;
   vk_bt bt;
+  vk_chain chain;
 };
 
 // A second stream for the look-ahead of the blocked inversion: after each outer block of columns
@@ -358,6 +433,9 @@ int64_t vk_patch_map_elems(int32_t n_K);
 hipError_t launch_patch_map(hipStream_t s, const vk_csr& J, const vk_group& G, int32_t* too_long);
 hipError_t launch_patch_setup_fast(hipStream_t s, const vk_csr& J, const vk_group& G, vk_prec prec, int32_t* status,
                                    bool* handled, bool mfma = true, bool map = false);
+// inverses of n_items dense matrices of at most n_max <= VK_ITEM_MAX rows (items: device); a matrix with
+// no nonzero pivot sets status[0] to min(item)
+hipError_t launch_invert_items(hipStream_t s, int n_items, int n_max, const vk_dense_item* items, int32_t* status);
 // Patches of more than VK_LDS_SETUP_MAX_NK (at most 512) rows through the blocked Gauss-Jordan
 // kernels of the directly solved blocks, in chunks of the workspace's blocked-setup buffers.
 hipError_t launch_patch_setup_blocked(hipStream_t s, const vk_csr& J, const vk_group& G, vk_prec prec,
@@ -397,6 +475,13 @@ hipError_t launch_block_invert_dense_any(hipStream_t s, const vk_level& L, int32
 bool vk_bt_plan(vk_level& L);
 hipError_t launch_bt_factor(hipStream_t s, const vk_level& L, int32_t* status);
 hipError_t launch_bt_solve(hipStream_t s, const vk_level& L, const double* b, double* x);
+// chain.hip: reserved workspace (doubles; bytes of tables), plan (host, once per pattern and
+// workspace; false: every block stays with the dense inversion) and the inversion.  *flag becomes
+// nonzero if a chained block's inverse fails its check; scratch takes chain blocks' pivot failures.
+int64_t vk_chain_buffer(const vk_level& L);
+size_t vk_chain_table_bytes(const vk_level& L);
+bool vk_chain_plan(vk_level& L);
+hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status, int32_t* scratch, int32_t* flag);
 hipError_t launch_block_export(hipStream_t s, const vk_level& L, int32_t block, double* out);
 // Krylov
 hipError_t launch_dot(hipStream_t s, int64_t n, const double* x, const double* y, double* partial,
