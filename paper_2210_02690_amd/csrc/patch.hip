@@ -1041,8 +1041,8 @@ __device__ inline double recip_f64(double a) {
 }
 
 // ---------------------------------------------------------------------------
-// Wide patches on the FP64 matrix cores (compiled for n_K = 84, 85, 105, 120 and 170):
-// blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
+// Wide patches (n_K = 84, 85, 105, 120 and 170) and the small blocks of a chain inverse on the FP64 matrix
+// cores: blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
 // registers as T x T tiles of 16 x 16: tile-row wavefront w (of T) holds tile row w, and one more
 // wavefront, which holds no tiles, eliminates the panels.  Columns are eliminated in panels of
 // NB = 4; with panel j factored (its eliminated columns M and pivot rows q_t in LDS):
@@ -1058,6 +1058,12 @@ __device__ inline double recip_f64(double a) {
 // W'[i][c] = W[i][c] - W[i][k] W[p][c] / W[p][k], W'[p][c] = W[p][c] / W[p][k]).  After all steps
 // J_K^{-1}[k][q_j] = W[q_k][j], written out through LDS one 16-column block at a time so the
 // stores of a column are contiguous.
+// What bounds it: the chain of pivot steps in the panel wavefront, 600 (two rows a lane) to 750 cycles
+// (three) a step, and at 170 rows, nearly as long, the tile wavefronts' 121 matrix products a panel.
+// FP64 matrix products hold up the FP64 instructions of other wavefronts on their SIMD, so the panel
+// wavefront has one to itself; the tile wavefronts find their pivot rows in a per-row table.
+// Measured (per matrix of 512): 170 rows 0.60 -> 0.50 us, 128 rows 0.36 -> 0.27 us, 80 rows 0.12 ->
+// 0.10 us; a single one of 170 rows 143 -> 116 us.
 // Pivot choice: the largest |a| among the rows not yet pivotal, compared on a 32-bit key (|a|'s
 // exponent and 13 leading mantissa bits, then 255 - row), so one integer wavefront maximum gives
 // the row as well: candidates within a relative 2^-13 count as ties and the lowest row wins (the
@@ -1069,13 +1075,16 @@ __device__ inline double recip_f64(double a) {
 // (the register arrays are never indexed at run time) and the branches depend on wave-uniform
 // values only.
 // ---------------------------------------------------------------------------
-template <int T> struct MfCfg {
+template <int T, bool SEP> struct MfCfg {
   static constexpr int NP = 16 * T;              // padded width
-  static constexpr int NT = 64 * (T + 1);       // T tile-row wavefronts and the panel wavefront
+  // wavefronts go to the SIMDs in turn: with SEP the panel wavefront is the fourth and every fourth one
+  // after it holds nothing, so no tile row shares its SIMD (the search, whose 168 registers a lane leave
+  // room for three wavefronts a SIMD, keeps T + 1)
+  static constexpr int NT = 64 * (SEP ? (T + 2) / 3 * 4 : T + 1);
   static constexpr int NB = 4;                   // panel width (one MFMA depth)
   static constexpr int R = (NP + 63) / 64;       // panel rows per lane
   static constexpr int PW = T;                   // the wavefront that eliminates the panels
-  static constexpr int PLD = NB + 1;             // LDS row length of a panel (doubles)
+  static constexpr int PLD = NB + 2;             // LDS row length of a panel: 16-byte rows without bank conflicts
 };
 // where the matrices come from: a search of the CSR rows, the patch entry map, or dense matrices
 enum { SRC_SEARCH = 0, SRC_MAP = 1, SRC_DENSE = 2 };
@@ -1154,19 +1163,20 @@ __global__ __launch_bounds__(512) void patch_map_kernel(const int64_t* __restric
 }
 
 template <int P, int T, int SRC>
-__global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
+__global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_setup_mfma_kernel(
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
     const int32_t* __restrict__ cell_dofs, const uint64_t* __restrict__ pmap, int32_t n_K, void* inv_out, int32_t ld_,
     int64_t cell_stride, const vk_dense_item* __restrict__ items, int32_t* status) {
-  using C = MfCfg<T>;
+  using C = MfCfg<T, (SRC != SRC_SEARCH)>;
   constexpr bool MAP = SRC != SRC_SEARCH;  // no hash table
   constexpr int NP = C::NP, NT = C::NT, NB = C::NB, R = C::R, PW = C::PW, PLD = C::PLD;
   static_assert(R <= 4 && NP <= 256, "patch width");
   __shared__ int qs[NP], kinv[NP];
-  __shared__ __align__(16) int pq[2][NB];  // the panel's pivot rows (-1: none), double-buffered
+  // the panel's step that chose row 16 w + 4 v + l at 16 w + 4 l + v (-1: none), double-buffered
+  __shared__ __align__(16) int rowt[2][NP];
   __shared__ double stage[16 * NP];       // gather rows / output columns
-  __shared__ double pan[2][NP * PLD];     // eliminated panel columns M (double-buffered)
-  __shared__ double pc[2][NP * PLD];      // the next panel's columns before its last update
+  __shared__ __align__(16) double pan[2][NP * PLD];  // eliminated panel columns M (double-buffered)
+  __shared__ __align__(16) double pc[2][NP * PLD];   // the next panel's columns before its last update
   __shared__ double bs[2][NB * NP];       // old pivot rows (double-buffered)
   __shared__ int2 htab[MAP ? 1 : PatchHash::SLOTS];  // DoF -> local index
   __shared__ int64_t rbeg[MAP ? 1 : NP];             // first CSR entry of each patch row
@@ -1178,7 +1188,13 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
   const int ld = SRC == SRC_DENSE ? N : ld_;
   if (N <= 0) return;                                     // uniform
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // this wavefront's tile row
+  // this wavefront's tile row; PW: the panel wavefront, above: none
+  int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (SRC != SRC_SEARCH) {
+    const int hw = w;
+    w = (hw & 3) == 3 ? (hw == 3 ? PW : PW + 1) : (hw >> 2) * 3 + (hw & 3);
+    w = (hw & 3) != 3 && w >= T ? PW + 1 : w;
+  }
   const int l16 = lane & 15, l4 = lane >> 4;
   if (!MAP)
     for (int h = tid; h < PatchHash::SLOTS; h += NT) htab[h] = make_int2(-1, 0);
@@ -1186,6 +1202,7 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
     qs[i] = i < N ? i : 0;  // overwritten by every pivot; keeps the output in range otherwise
     kinv[i] = -1;
     rlen[i] = 0;
+    rowt[0][i] = rowt[1][i] = -1;
   }
   for (int e = tid; e < 2 * NB * NP; e += NT) (&bs[0][0])[e] = 0.0;
   if (tid == 0) bad_s = 0;
@@ -1312,6 +1329,7 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
       rid[r] = (uint32_t)(255 - 64 * r - lane);
     }
     bool singular = false;
+    int old1 = -1, old2 = -1;  // lane t: the places in rowt of the last two panels' step t
     double pr[R][NB];  // the current panel's columns, the lane's rows r * 64 + lane
     bool zr[R];        // the lane's rows that became pivots in the current panel
     int pv[NB];        // the current panel's pivot rows (-1: none); uniform
@@ -1378,14 +1396,16 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
 #pragma unroll
         for (int c = 0; c < NB; ++c)
           if (r * 64 + lane < NP) pn[(r * 64 + lane) * PLD + c] = pr[r][c];
-      if (lane == 0) {
-        *reinterpret_cast<int4*>(pq[jj & 1]) = make_int4(pv[0], pv[1], pv[2], pv[3]);
-#pragma unroll
-        for (int t = 0; t < NB; ++t)
-          if (pv[t] >= 0) {
-            qs[k0 + t] = pv[t];
-            kinv[pv[t]] = k0 + t;
-          }
+      // lane t records step t's pivot row
+      const int pl4 = lane == 0 ? pv[0] : lane == 1 ? pv[1] : lane == 2 ? pv[2] : pv[3];
+      int* rt = rowt[jj & 1];
+      if (lane < NB && old2 >= 0) rt[old2] = -1;  // of panel jj - 2
+      old2 = old1;
+      old1 = pl4 >= 0 ? (pl4 & ~15) + 4 * (pl4 & 3) + ((pl4 >> 2) & 3) : -1;
+      if (lane < NB && pl4 >= 0) {
+        rt[old1] = lane;
+        qs[k0 + lane] = pl4;
+        kinv[pl4] = k0 + lane;
       }
     };
     // panel jj's columns from LDS buffer b (rows beyond NP read as zero)
@@ -1395,6 +1415,7 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
 #pragma unroll
         for (int c = 0; c < NB; ++c) x[r][c] = (r * 64 + lane < NP) ? b[(r * 64 + lane) * PLD + c] : 0.0;
     };
+    __builtin_amdgcn_s_setprio(3);  // the chain of pivot steps is what the tile wavefronts wait for
     load_cols(pc[0], pr);
     factor(0);
     for (int j = 0; j < NPAN; ++j) {
@@ -1410,7 +1431,10 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
 #pragma unroll
         for (int t = 0; t < NB; ++t)
 #pragma unroll
-          for (int c = 0; c < NB; ++c) bv[t][c] = pv[t] >= 0 ? b[pv[t] * PLD + c] : 0.0;
+          for (int c = 0; c < NB; ++c) {
+            const double y = b[(pv[t] >= 0 ? pv[t] : 0) * PLD + c];  // loaded in any case: no branch
+            bv[t][c] = pv[t] >= 0 ? y : 0.0;
+          }
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -1436,6 +1460,19 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
       __syncthreads();  // block J's columns in stage
       copy_block(J);
     }
+  } else if (w > PW) {
+    // ---- no tiles: the barriers and the output only ----
+    for (int j = 0; j < NPAN; ++j) {
+      __syncthreads();
+      __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int J = 0; J < T; ++J) {
+      __syncthreads();
+      __syncthreads();
+      copy_block(J);
+    }
   } else {
     // ---- the tile-row wavefronts ----
     for (int j = 0; j < NPAN; ++j) {
@@ -1445,23 +1482,14 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
       const int J2 = nxt2 ? NB * (j + 2) / 16 : -1, h2 = NB * (j + 2) % 16;
       double* pn = pan[j & 1];
       double* bb = bs[j & 1];
-      const int* pqj = pq[j & 1];
-      // the owners of the panel's pivot rows copy their old values to LDS and clear the rows (rows
-      // of steps without a pivot stay zero in B).  Each lane finds, for each of its four rows,
+      // The owners of the panel's pivot rows copy their old values to LDS and clear the rows (rows
+      // of steps without a pivot stay zero in B).  Each lane reads, for each of its four rows,
       // the step whose pivot it is (if any), so the accumulator element is fixed at compile time
       // and only the LDS row depends on the lane.
       {
-        const int4 q4 = *reinterpret_cast<const int4*>(pqj);
-        const int q0 = __builtin_amdgcn_readfirstlane(q4.x), q1 = __builtin_amdgcn_readfirstlane(q4.y);
-        const int q2 = __builtin_amdgcn_readfirstlane(q4.z), q3 = __builtin_amdgcn_readfirstlane(q4.w);
-        // uniform: does this wavefront hold a pivot row of the panel (-1 >> 4 is -1, never w)
-        if ((q0 >> 4) == w || (q1 >> 4) == w || (q2 >> 4) == w || (q3 >> 4) == w) {
-          int tv[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int row = 16 * w + 4 * v + l4;
-            tv[v] = row == q0 ? 0 : row == q1 ? 1 : row == q2 ? 2 : row == q3 ? 3 : -1;
-          }
+        const int4 t4 = *reinterpret_cast<const int4*>(&rowt[j & 1][16 * w + 4 * l4]);
+        const int tv[4] = {t4.x, t4.y, t4.z, t4.w};
+        if (__builtin_amdgcn_readfirstlane((int)(__ballot(max(max(tv[0], tv[1]), max(tv[2], tv[3])) >= 0) != 0))) {  // uniform
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             if (tv[v] >= 0) {
@@ -1505,7 +1533,7 @@ __global__ __launch_bounds__(MfCfg<T>::NT) void patch_setup_mfma_kernel(
         }
         // the next panel's buffer of old pivot rows, cleared while nobody reads it
         double* bo = bs[(j + 1) & 1];
-        for (int e = tid; e < NB * NP; e += 64 * T) bo[e] = 0.0;
+        for (int e = 64 * w + lane; e < NB * NP; e += 64 * T) bo[e] = 0.0;
       }
     }
     __syncthreads();  // the panel wavefront's singular flag
@@ -1753,7 +1781,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
                                                           L.ld, L.cell_stride, status)
 #define VK_MFMA_CASE(NN)                                                                     \
   case NN:                                                                                   \
-    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP><<<L.n_cells, MfCfg<(NN + 15) / 16>::NT, 0, s>>>( \
+    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP><<<L.n_cells, MfCfg<(NN + 15) / 16, true>::NT, 0, s>>>( \
         J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);   \
     return hipGetLastError();
   if (mapped) {
@@ -1799,7 +1827,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #undef VK_WIDE_CASE
     case 170:
       if (mfma)
-        patch_setup_mfma_kernel<P, 11, SRC_SEARCH><<<L.n_cells, MfCfg<11>::NT, 0, s>>>(
+        patch_setup_mfma_kernel<P, 11, SRC_SEARCH><<<L.n_cells, MfCfg<11, false>::NT, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);
       else
         patch_setup_wide_kernel<P, 170><<<L.n_cells, 64 * WideCfg<170>::NW, 0, s>>>(
@@ -2050,7 +2078,7 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
 
 template <int T>
 static hipError_t invert_items(hipStream_t s, int n_items, const vk_dense_item* items, int32_t* status) {
-  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE><<<(unsigned)n_items, MfCfg<T>::NT, 0, s>>>(
+  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE><<<(unsigned)n_items, MfCfg<T, true>::NT, 0, s>>>(
       nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, 0, items, status);
   return hipGetLastError();
 }
