@@ -9,8 +9,8 @@
 //   left,  i < c:  X_i = S_i^{-1} U_i,  S_{i+1} = D_{i+1} - L_{i+1} X_i,   S_0 = D_0,
 //   right, i > c:  Y_i = T_i^{-1} L_i,  T_{i-1} = D_{i-1} - U_{i-1} Y_i,   T_{nb-1} = D_{nb-1},
 //   middle:        S_c = D_c - L_c X_{c-1} - U_c Y_{c+1},
-// the S_i, T_i inverted by the register-resident matrix-core kernel (up to VK_ITEM_MAX rows) or the blocked
-// Gauss-Jordan kernels.  Then the whole inverse G grows outwards from G_cc = S_c^{-1}; with M the
+// the S_i, T_i inverted by the register-resident matrix-core kernel, those wider than VK_ITEM_MAX rows piece by
+// piece (block Gauss-Jordan).  Then the whole inverse G grows outwards from G_cc = S_c^{-1}; with M the
 // blocks already there, i the next block on the left and j on the right,
 //   G_iM = -X_i G_{i+1,M},  G_Mi = -G_{M,i+1} Z_i,  G_jM = -Y_j G_{j-1,M},  G_Mj = -G_{M,j-1} W_j,
 //   G_ii = S_i^{-1} - X_i G_{i+1,i},  G_jj = T_j^{-1} - Y_j G_{j-1,j},  G_ij = -X_i G_{i+1,j},
@@ -33,8 +33,7 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront per row: a chained row's entries go to D (column-major), U or L (row-major) of its chain
-// block, a row of a dense block to the block (column-major).  cb: the row's chain block, or -1 - b
+// One wavefront per row: a chained row's entries go to D, U or L of its chain block, a row of a dense block to the block (column-major).  cb: the row's chain block, or -1 - b
 // for dense block b; ri: the row's index in it.
 __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_t n_rows, const int64_t* __restrict__ row_ptr,
                                                            const int32_t* __restrict__ col,
@@ -64,15 +63,15 @@ __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_
       continue;
     }
     const int bc = cb[c], j = ri[c];
-    if (bc == b) q.D[(int64_t)j * q.s + i] = val[e];
+    if (bc == b) q.D[q.d_cm ? (int64_t)j * q.s + i : (int64_t)i * q.s + j] = val[e];
     else if (bc == b + 1) q.U[(int64_t)i * q.s_next + j] = val[e];
     else if (bc == b - 1) q.L[(int64_t)i * q.s_prev + j] = val[e];
     else atomicOr(&status[1], 2);  // the plan makes this impossible
   }
 }
 
-// C = base + alpha A B per item (blockIdx.y; x: its tile), A, B row-major, C and base row- or column-major (base null:
-// zero; k = 0 copies).  32 x 32 tiles, a 16 x 16 tile per wavefront on the FP64 matrix cores, 32-step
+// C = beta base + alpha A B per item (blockIdx.y; x: its tile), each row- or column-major (base null: zero, k = 0
+// copies; base may be C).  32 x 32 tiles, a 16 x 16 tile per wavefront on the FP64 matrix cores, 32-step
 // chunks through LDS with the next chunk's loads in flight: the matrices are 50 to 500 wide, so the
 // tiles are small enough to give a launch tens of workgroups.
 __global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __restrict__ items) {
@@ -89,10 +88,12 @@ __global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __r
   auto load = [&](int k0) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q, r = e >> 5, c = e & 31;
-      const bool oka = m0 + r < p.m && k0 + c < p.k, okb = k0 + r < p.k && n0 + c < p.n;
-      const double a = p.A[oka ? (int64_t)(m0 + r) * p.lda + k0 + c : 0];
-      const double b = p.B[okb ? (int64_t)(k0 + r) * p.ldb + n0 + c : 0];
+      // the fast index along the storage
+      const int e = tid + 256 * q, s = e >> 5, f = e & 31;
+      const int ra = p.a_cm ? f : s, ca = p.a_cm ? s : f, rb = p.b_cm ? f : s, cb = p.b_cm ? s : f;
+      const bool oka = m0 + ra < p.m && k0 + ca < p.k, okb = k0 + rb < p.k && n0 + cb < p.n;
+      const double a = p.A[oka ? (p.a_cm ? (int64_t)(k0 + ca) * p.lda + m0 + ra : (int64_t)(m0 + ra) * p.lda + k0 + ca) : 0];
+      const double b = p.B[okb ? (p.b_cm ? (int64_t)(n0 + cb) * p.ldb + k0 + rb : (int64_t)(k0 + rb) * p.ldb + n0 + cb) : 0];
       av[q] = oka ? a : 0.0;
       bv[q] = okb ? b : 0.0;
     }
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __r
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int e = tid + 256 * q;
-      As[(e >> 5) * LA + (e & 31)] = av[q];
-      Bs[(e >> 5) * LB + (e & 31)] = bv[q];
+      As[(p.a_cm ? e & 31 : e >> 5) * LA + (p.a_cm ? e >> 5 : e & 31)] = av[q];
+      Bs[(p.b_cm ? e & 31 : e >> 5) * LB + (p.b_cm ? e >> 5 : e & 31)] = bv[q];
     }
     __syncthreads();
     if (k0 + KC < p.k) load(k0 + KC);
@@ -120,19 +121,9 @@ __global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __r
   for (int v = 0; v < 4; ++v) {
     const int r = m0 + wm + 4 * v + l4;
     if (r >= p.m) continue;
-    const int64_t at = p.col_major ? (int64_t)c * p.ldc + r : (int64_t)r * p.ldc + c;
-    const double base = p.base ? p.base[p.col_major ? (int64_t)c * p.ldbase + r : (int64_t)r * p.ldbase + c] : 0.0;
-    p.C[at] = base + p.alpha * acc[v];
-  }
-}
-
-// eliminated blocks (row-major W, pivot rows q) in natural order: out[k][q_j] = W[q_k][j]
-__global__ __launch_bounds__(256) void chain_export_kernel(const vk_chain_export* __restrict__ items) {
-  const vk_chain_export p = items[blockIdx.y];
-  const int64_t total = (int64_t)p.n * p.n;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(e / p.n), j = (int)(e - (int64_t)k * p.n);
-    p.out[(int64_t)k * p.n + p.q[j]] = p.w[(int64_t)p.q[k] * p.n + j];
+    const int64_t at = p.c_cm ? (int64_t)c * p.ldc + r : (int64_t)r * p.ldc + c;
+    const double base = p.base ? p.base[p.base_cm ? (int64_t)c * p.ldbase + r : (int64_t)r * p.ldbase + c] : 0.0;
+    p.C[at] = p.beta * base + p.alpha * acc[v];
   }
 }
 
@@ -240,14 +231,25 @@ bool chain_order(int64_t n, const std::vector<int64_t>& ap, const std::vector<in
   return true;
 }
 
-// A block is chained where the estimated time of its chain is below 0.8 of the dense inversion's: the
-// estimate (us) for one s-row matrix, the register-resident kernel (80 rows 45 us, 160 rows 123 us) or 16-column
-// panels with their updates (20 + 6 us and the outer updates: 888 rows 1.8 ms); 35 us a step for the
-// products and the launches.
-double invert_us(double s) { return s <= VK_ITEM_MAX ? 20.0 + 0.55 * s : 30.0 * std::ceil(s / 16.0) + 40.0; }
+// pieces of the elimination of an s-row chain block: as few as the register-resident kernel takes, of equal
+// width rounded up to whole 16-row tiles
+int64_t piece_width(int64_t s) {
+  const int64_t p = (s + VK_ITEM_MAX - 1) / VK_ITEM_MAX;
+  return std::min<int64_t>(((s + p - 1) / p + 15) / 16 * 16, s);
+}
 
-// doubles reserved for a block: a chain of blocks of s rows takes about 6 s n
-int64_t reserve(int64_t n) { return n < VK_CHAIN_MIN_N ? 0 : (n <= 1024 ? 2 : 1) * n * n; }
+// A block is chained where the estimated time of its chain is below 0.8 of the dense inversion's.  The
+// estimates (us): a piece in the register-resident kernel (64 rows 25, 128 rows 65, 176 rows 118) and its
+// four launches; 35 a step for the products; the dense inversion's 16-column panels with their updates
+// (20 + 6 and the outer updates: 888 rows 1.8 ms).
+double chain_us(int64_t s) {
+  const int64_t w = piece_width(s), p = (s + w - 1) / w;
+  return p * (w <= 128 ? 0.5 * w : 0.67 * w) + (p > 1 ? 35.0 * p : 0.0);
+}
+double dense_us(double n) { return 30.0 * std::ceil(n / 16.0) + 40.0; }
+
+// doubles reserved for a block: a chain of blocks of s rows takes about 6 s n, and pays off up to about n = 5 s
+int64_t reserve(int64_t n) { return n < VK_CHAIN_MIN_N ? 0 : (n <= 1024 ? 2 * n * n : n * n + n * n / 2); }
 
 int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
 
@@ -294,15 +296,17 @@ bool vk_chain_plan(vk_level& L) {
   std::vector<int32_t> cb(rows, -1), ri(rows), rmap(rows), cmap(rows);
   std::vector<vk_chain_block> blocks;
   std::vector<vk_chain_dense>& dense = T.dense;
+  struct piece_lists {
+    std::vector<vk_dense_item> inv;
+    std::vector<vk_gemm_item> qr, up, put;
+  };
   struct step_lists {
-    std::vector<vk_dense_item> small;
-    std::vector<int> gj;  // chain blocks
+    std::vector<piece_lists> pieces;
     std::vector<vk_gemm_item> cp, u1, u2;
   };
   std::vector<step_lists> steps;
   std::vector<vk_gemm_item> zw;
   std::vector<std::vector<vk_gemm_item>> ga, gb;
-  std::vector<double*> dinv;
   int64_t used = 0;
   auto take = [&](int64_t n) {
     double* p = buf + used;
@@ -324,7 +328,8 @@ bool vk_chain_plan(vk_level& L) {
     g.ldbase = (int32_t)ldbase;
     g.C = C;
     g.ldc = (int32_t)ldc;
-    g.col_major = cm;
+    g.c_cm = g.base_cm = cm;
+    g.beta = 1.0;
     return g;
   };
   struct block_plan {
@@ -373,17 +378,18 @@ bool vk_chain_plan(vk_level& L) {
     const int nb = (int)p.size.size();
     if (*std::max_element(p.size.begin(), p.size.end()) > 1024 || *std::min_element(p.size.begin(), p.size.end()) < 16)
       continue;
-    double us = invert_us((double)p.size[p.c]) + 60.0;
+    double us = chain_us(p.size[p.c]) + 60.0;
     for (int k = 0; k < std::max(p.c, nb - 1 - p.c); ++k) {
-      const double a = k < p.c ? invert_us((double)p.size[k]) : 0.0, z = nb - 1 - k > p.c ? invert_us((double)p.size[nb - 1 - k]) : 0.0;
+      const double a = k < p.c ? chain_us(p.size[k]) : 0.0, z = nb - 1 - k > p.c ? chain_us(p.size[nb - 1 - k]) : 0.0;
       us += std::max(a, z) + 35.0;
     }
     int64_t need = 0;
     for (int i = 0; i < nb; ++i) {
-      need += 2 * up32(p.size[i] * p.size[i]);
+      const int64_t w = piece_width(p.size[i]);  // the inverse, or a piece's inverse and products
+      need += up32(p.size[i] * p.size[i]) + (w == p.size[i] ? up32(p.size[i] * p.size[i]) : up32(w * w) + 2 * up32(w * p.size[i]));
       if (i + 1 < nb) need += 4 * up32(p.size[i] * p.size[i + 1]);
     }
-    if (us > 0.8 * invert_us((double)n) || need > reserve(n)) continue;
+    if (us > 0.8 * dense_us((double)n) || need > reserve(n)) continue;
     p.ok = true;
   }
   int64_t n_chained = 0;
@@ -422,6 +428,7 @@ bool vk_chain_plan(vk_level& L) {
       q.s = (int32_t)p.size[i];
       q.s_prev = i > 0 ? (int32_t)p.size[i - 1] : 0;
       q.s_next = i + 1 < nb ? (int32_t)p.size[i + 1] : 0;
+      q.d_cm = piece_width(p.size[i]) == p.size[i];
       q.D = take(p.size[i] * p.size[i]);
       q.U = i + 1 < nb ? take(p.size[i] * p.size[i + 1]) : nullptr;
       q.L = i > 0 ? take(p.size[i] * p.size[i - 1]) : nullptr;
@@ -439,13 +446,13 @@ bool vk_chain_plan(vk_level& L) {
     for (int i = 0; i < nb; ++i) off[i + 1] = off[i] + p.size[i];
     std::vector<double*> inv(nb), X(nb, nullptr), Z(nb, nullptr);
     for (int i = 0; i < nb; ++i) {
-      inv[i] = take(sz(i) * sz(i));
+      // a block of one piece is inverted out of place, a wider one in place, piece by piece
+      inv[i] = piece_width(sz(i)) == sz(i) ? take(sz(i) * sz(i)) : blocks[f + i].D;
       const int j = i < c ? i + 1 : (i > c ? i - 1 : -1);  // the next block inwards
       if (j >= 0) {
         X[i] = take(sz(i) * sz(j));  // X_i or Y_i
         Z[i] = take(sz(j) * sz(i));  // Z_i or W_i
       }
-      dinv.push_back(inv[i]);
     }
     const int ns = std::max(c, nb - 1 - c) + 1;
     if ((int)steps.size() < ns) steps.resize(ns);
@@ -453,11 +460,44 @@ bool vk_chain_plan(vk_level& L) {
       ga.resize(ns - 1);
       gb.resize(ns - 1);
     }
+    // Block Gauss-Jordan over the pieces K of S (s x s, row-major, in place), P = S_KK^{-1} (column-major):
+    //   Q = S_.K P, R = P S_K.;  S_.. -= Q S_K. off row and column K;  S_K. = R, S_.K = -Q, S_KK = P.
     auto invert = [&](step_lists& S, int i) {
-      const double s = (double)sz(i);
-      T.flops += 2.0 * s * s * s;
-      if (sz(i) <= VK_ITEM_MAX) S.small.push_back(vk_dense_item{blocks[f + i].D, inv[i], (int32_t)sz(i)});
-      else S.gj.push_back(f + i);
+      const int64_t s = sz(i), w = piece_width(s);
+      T.flops += 2.0 * (double)s * s * s;
+      const int np = (int)((s + w - 1) / w);
+      if ((int)S.pieces.size() < np) S.pieces.resize(np);
+      double* D = blocks[f + i].D;
+      if (np == 1) {
+        S.pieces[0].inv.push_back(vk_dense_item{D, inv[i], (int32_t)s, (int32_t)s});
+        return;
+      }
+      double *P = take(w * w), *Q = take(w * s), *R = take(w * s);
+      for (int q = 0; q < np; ++q) {
+        piece_lists& C = S.pieces[q];
+        const int64_t k0 = q * w, k1 = std::min(k0 + w, s), h = k1 - k0;
+        C.inv.push_back(vk_dense_item{D + k0 * s + k0, P, (int32_t)h, (int32_t)s});
+        const int64_t e0[2] = {0, k1}, e1[2] = {k0, s};  // the rows and columns beside the piece
+        for (int a = 0; a < 2; ++a) {
+          const int64_t n = e1[a] - e0[a];
+          if (n == 0) continue;
+          vk_gemm_item g = item(n, h, h, 1.0, D + e0[a] * s + k0, s, P, h, nullptr, 0, Q + e0[a] * h, h, false);
+          g.b_cm = 1;
+          C.qr.push_back(g);
+          g = item(h, n, h, 1.0, P, h, D + k0 * s + e0[a], s, nullptr, 0, R + e0[a], s, false);
+          g.a_cm = 1;
+          C.qr.push_back(g);
+          for (int z = 0; z < 2; ++z)
+            if (e1[z] > e0[z])
+              C.up.push_back(item(n, e1[z] - e0[z], h, -1.0, Q + e0[a] * h, h, D + k0 * s + e0[z], s, D + e0[a] * s + e0[z], s,
+                                  D + e0[a] * s + e0[z], s, false));
+          C.put.push_back(item(h, n, 0, 0.0, P, h, P, h, R + e0[a], s, D + k0 * s + e0[a], s, false));
+          C.put.push_back(item(n, h, 0, 0.0, P, h, P, h, Q + e0[a] * h, h, D + e0[a] * s + k0, s, false));
+          C.put.back().beta = -1.0;
+        }
+        C.put.push_back(item(h, h, 0, 0.0, P, h, P, h, P, h, D + k0 * s + k0, s, false));
+        C.put.back().base_cm = 1;
+      }
     };
     for (int k = 0; k < ns; ++k) {
       step_lists& S = steps[k];
@@ -475,7 +515,7 @@ bool vk_chain_plan(vk_level& L) {
         const double* back = side == 0 ? blocks[f + j].L : blocks[f + j].U;  // j -> i
         S.cp.push_back(item(sz(i), sz(j), sz(i), 1.0, inv[i], sz(i), out, sz(j), nullptr, 0, X[i], sz(j), false));
         const vk_gemm_item u = item(sz(j), sz(j), sz(i), -1.0, back, sz(i), X[i], sz(j), blocks[f + j].D, sz(j),
-                                    blocks[f + j].D, sz(j), true);
+                                    blocks[f + j].D, sz(j), blocks[f + j].d_cm != 0);
         // both chains can reach the middle block in one step: its updates run one after the other
         if (j == c && !first_update) S.u2.push_back(u);
         else S.u1.push_back(u);
@@ -551,25 +591,17 @@ bool vk_chain_plan(vk_level& L) {
   T.rows = rows;
   for (step_lists& S : steps) {
     vk_chain_step st;
-    // the widest first: the launch's workgroups of the longest chains start first
-    std::stable_sort(S.small.begin(), S.small.end(), [](const vk_dense_item& a, const vk_dense_item& b) { return a.n > b.n; });
-    st.n_small = (int)S.small.size();
-    st.small_max = st.n_small ? S.small[0].n : 0;
-    st.small = reinterpret_cast<vk_dense_item*>(put(S.small.data(), S.small.size() * sizeof(vk_dense_item)));
-    if (!S.gj.empty()) {
-      std::vector<int64_t> gr{0}, gw;
-      std::vector<vk_chain_export> ex;
-      for (int i : S.gj) {
-        const int64_t s = blocks[i].s;
-        gw.push_back(blocks[i].D - buf);
-        ex.push_back(vk_chain_export{blocks[i].D, L.cb_q + gr.back(), dinv[i], (int32_t)s});
-        gr.push_back(gr.back() + s);
-        st.gj_max = std::max(st.gj_max, s);
-      }
-      st.gj_rows = gr;
-      st.d_gj_rows = reinterpret_cast<int64_t*>(put(gr.data(), gr.size() * 8));
-      st.d_gj_woff = reinterpret_cast<int64_t*>(put(gw.data(), gw.size() * 8));
-      st.gj_export = reinterpret_cast<vk_chain_export*>(put(ex.data(), ex.size() * sizeof(vk_chain_export)));
+    for (piece_lists& C : S.pieces) {
+      vk_chain_piece q;
+      // the widest first: the launch's longest chains start first
+      std::stable_sort(C.inv.begin(), C.inv.end(), [](const vk_dense_item& a, const vk_dense_item& b) { return a.n > b.n; });
+      q.n_items = (int)C.inv.size();
+      q.n_max = q.n_items ? C.inv[0].n : 0;
+      q.items = reinterpret_cast<vk_dense_item*>(put(C.inv.data(), C.inv.size() * sizeof(vk_dense_item)));
+      q.qr = put_gemm(C.qr);
+      q.up = put_gemm(C.up);
+      q.put = put_gemm(C.put);
+      st.pieces.push_back(q);
     }
     st.cp = put_gemm(S.cp);
     st.u1 = put_gemm(S.u1);
@@ -640,15 +672,12 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
                                                                    T.blocks, T.d_dense, status);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (const vk_chain_step& S : T.steps) {
-    // a chain block without a pivot only marks `scratch`: the check decides
-    if ((e = launch_invert_items(s, S.n_small, S.small_max, S.small, scratch)) != hipSuccess) return e;
-    if (S.gj_rows.size() > 1) {
-      const vk_level V = virtual_level(T.buf, S.gj_rows, S.d_gj_rows, S.d_gj_woff);
-      if ((e = launch_block_invert_dense_any(s, V, scratch)) != hipSuccess) return e;
-      chain_export_kernel<<<dim3((unsigned)std::min<int64_t>((S.gj_max * S.gj_max + 255) / 256, 1024),
-                                 (unsigned)(S.gj_rows.size() - 1)),
-                            256, 0, s>>>(S.gj_export);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (const vk_chain_piece& C : S.pieces) {
+      // a chain block without a pivot only marks `scratch`: the check decides
+      if ((e = launch_invert_items(s, C.n_items, C.n_max, C.items, scratch)) != hipSuccess) return e;
+      if ((e = gemm_list(s, C.qr)) != hipSuccess) return e;
+      if ((e = gemm_list(s, C.up)) != hipSuccess) return e;
+      if ((e = gemm_list(s, C.put)) != hipSuccess) return e;
     }
     if ((e = gemm_list(s, S.cp)) != hipSuccess) return e;
     if ((e = gemm_list(s, S.u1)) != hipSuccess) return e;

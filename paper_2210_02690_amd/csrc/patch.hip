@@ -1213,13 +1213,14 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
     // the stored matrix read by rows (a column-major matrix transposed: so is its inverse)
     if (w < T) {
       const double* A = items[K].a;
+      const int64_t lda = items[K].lda;
 #pragma unroll
       for (int J = 0; J < T; ++J)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int i = 16 * w + 4 * v + l4, j = 16 * J + l16;
           const bool ok = i < N && j < N;
-          const double x = A[ok ? (int64_t)i * N + j : 0];
+          const double x = A[ok ? i * lda + j : 0];
           acc[J][v] = ok ? x : 0.0;
         }
     }

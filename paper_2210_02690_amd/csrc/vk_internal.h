@@ -164,51 +164,47 @@ struct vk_bt {
 };
 
 // A dense FP64 matrix to be inverted by the register-resident matrix-core kernel (n <= VK_ITEM_MAX): a is
-// column-major, out receives the inverse row-major; n <= 0: nothing.
+// column-major with leading dimension lda (row-major), out receives the inverse row-major
+// (column-major), n x n; n <= 0: nothing.
 #define VK_ITEM_MAX 176
 struct vk_dense_item {
   const double* a;
   double* out;
-  int32_t n;
+  int32_t n, lda;
 };
 
 // Dense inverses of directly solved blocks through a chain of small blocks (chain.hip): the plan is
 // made on the host once per pattern and workspace; buffers and tables lie in reserved workspace.
 #define VK_CHAIN_MIN_N 384     // narrower blocks are inverted densely
 #define VK_CHAIN_MIN_BLOCK 64  // consecutive level sets are grouped into chain blocks of at least this size
-struct vk_chain_block {  // D column-major s x s, U row-major s x s_next, L row-major s x s_prev
+struct vk_chain_block {  // D s x s (row-major, or column-major: see d_cm), U row-major s x s_next, L row-major s x s_prev
   double *D, *U, *L;
   int64_t r0, r1;  // rows of the directly solved block it belongs to
-  int32_t s, s_prev, s_next;
+  int32_t s, s_prev, s_next, d_cm;
 };
 struct vk_chain_dense {  // a densely inverted block of a level with chains
   double* w;
   int64_t r0, n;
 };
-struct vk_gemm_item {  // C = base + alpha A B
+struct vk_gemm_item {  // C = beta base + alpha A B
   const double *A, *B, *base;
   double* C;
-  double alpha;
-  int32_t m, n, k, lda, ldb, ldbase, ldc, col_major;
+  double alpha, beta;
+  int32_t m, n, k, lda, ldb, ldbase, ldc;
+  int32_t a_cm, b_cm, c_cm, base_cm;  // column-major (else row-major)
 };
 struct vk_gemm_list {
   vk_gemm_item* items = nullptr;  // device
   int count = 0;
   int64_t tiles = 0;  // 32 x 32 tiles of the largest item
 };
-struct vk_chain_export {
-  const double* w;
-  const int32_t* q;
-  double* out;
-  int32_t n;
+struct vk_chain_piece {  // one piece of every chain block of a step: inversions, then products
+  int n_items = 0, n_max = 0;
+  vk_dense_item* items = nullptr;  // device
+  vk_gemm_list qr, up, put;
 };
 struct vk_chain_step {
-  int n_small = 0, small_max = 0;
-  vk_dense_item* small = nullptr;   // device
-  std::vector<int64_t> gj_rows;     // blocks wider than VK_ITEM_MAX: row offsets
-  int64_t gj_max = 0;
-  int64_t *d_gj_rows = nullptr, *d_gj_woff = nullptr;
-  vk_chain_export* gj_export = nullptr;  // device
+  std::vector<vk_chain_piece> pieces;
   vk_gemm_list cp, u1, u2;
 };
 struct vk_chain_rest {  // densely inverted blocks of one width class

@@ -51,9 +51,9 @@ def _vk():
     return vk
 
 
-# chain blocks of 64 to 85 rows (matrix-core kernel of several tile counts), 128 to 176 (its widest), and
-# beyond 176 (blocked Gauss-Jordan); 384: the narrowest block that is chained
-@pytest.mark.parametrize("n,band", [(384, 9), (500, 17), (889, 33), (1000, 47), (1301, 85), (2000, 88), (2000, 150)])
+# chain blocks of 64 to 176 rows (matrix-core kernel of several tile counts), and beyond 176 (two and more
+# pieces); 384: the narrowest block that is chained
+@pytest.mark.parametrize("n,band", [(384, 9), (500, 17), (889, 33), (1000, 47), (1301, 85), (2000, 88), (2000, 150), (2000, 190), (2600, 310)])
 def test_chain_inverse(n, band):
     vk = _vk()
     print(f"chain inverse n {n} band {band}", flush=True)
