@@ -376,7 +376,7 @@ bool vk_chain_plan(vk_level& L) {
     block_plan& p = plans[b];
     if (!chain_order(n, ap, aj, p.blk, p.size, &p.c)) continue;
     const int nb = (int)p.size.size();
-    if (*std::max_element(p.size.begin(), p.size.end()) > 1024 || *std::min_element(p.size.begin(), p.size.end()) < 16)
+    if (*std::max_element(p.size.begin(), p.size.end()) > 2048 || *std::min_element(p.size.begin(), p.size.end()) < 16)
       continue;
     double us = chain_us(p.size[p.c]) + 60.0;
     for (int k = 0; k < std::max(p.c, nb - 1 - p.c); ++k) {

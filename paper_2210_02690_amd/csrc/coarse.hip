@@ -700,7 +700,7 @@ __global__ void block_export_kernel(int64_t n, const double* __restrict__ W, con
 // TN: panels of TP columns with tournament pivoting (CTT and R unused)
 template <int CTT, int R, int NB, int NBO, bool TN = false>
 hipError_t run_blocked(hipStream_t s, const vk_level& L, int32_t* status, int32_t bad_base = -1,
-                       const vk_lookahead* la = nullptr) {
+                       const vk_lookahead* la = nullptr, bool transpose = true) {
   static_assert(NBO % NB == 0 && NB <= VK_GJ_NBI_MAX && NBO % 64 == 0 && NBO <= VK_GJ_NBO,
                 "inner panels must tile the outer block, whose columns come in whole 64-column tiles");
   static_assert(!TN || NB == TP, "tournament panels are TP columns wide");
@@ -758,6 +758,7 @@ hipError_t run_blocked(hipStream_t s, const vk_level& L, int32_t* status, int32_
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (bulk_pending && (e = hipStreamWaitEvent(s, la->bulk_done, 0)) != hipSuccess) return e;
+  if (!transpose) return hipSuccess;
   const unsigned tiles = (unsigned)((n + 31) / 32);
   block_transpose_kernel<<<dim3(tiles, tiles, nbk), 256, 0, s>>>(L.d_cb_rows, L.d_cb_woff, L.cb_a);
   return hipGetLastError();
@@ -830,7 +831,7 @@ hipError_t launch_blocks_invert_dense(hipStream_t s, const vk_level& L, int32_t*
   if (e != hipSuccess) return e;
   // blocks of at most 512 rows: 256 threads x 2 rows hold a 16-column panel; 64-column outer
   // blocks (the buffers of the blocked patch inversion are sized for them)
-  return run_blocked<256, 2, 16, 64>(s, L, status, bad_base);
+  return run_blocked<256, 2, 16, 64>(s, L, status, bad_base, nullptr, false);
 }
 
 hipError_t launch_block_apply(hipStream_t s, const vk_level& L, const double* x, double* y) {

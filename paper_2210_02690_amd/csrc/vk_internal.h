@@ -459,7 +459,8 @@ int64_t vk_coarse_max_n();
 hipError_t launch_block_invert(hipStream_t s, const vk_level& L, int32_t* status, double** result,
                                const vk_lookahead* la = nullptr, int64_t min_tourney = VK_TOURNEY_MIN_N);
 // Blocked Gauss-Jordan inversion of L's blocks (cb_rows, cb_max <= 512), whose dense column-major
-// matrices are already in L.cb_a; a failing pivot sets status[0] to min(bad_base + block).
+// matrices are already in L.cb_a; a failing pivot sets status[0] to min(bad_base + block).  The eliminated
+// blocks stay column-major.
 hipError_t launch_blocks_invert_dense(hipStream_t s, const vk_level& L, int32_t* status, int32_t bad_base);
 hipError_t launch_block_apply(hipStream_t s, const vk_level& L, const double* x, double* y);
 // Gauss-Jordan inversion of L's blocks whose dense column-major matrices are already in L.cb_a
