@@ -1800,8 +1800,8 @@ __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
 // Tiles per dimension of the matrix-core kernels for patches n wide, 0 where none is compiled: any width
 // up to 64 on one wavefront (T = 4 is the widest whose tiles leave room for a second patch per SIMD),
 // the widths of the repository's 3D, dG(3), dG(4) and Q4 patches up to 176 on a workgroup (12 tile rows
-// and their panels do not fit a workgroup's registers).  Against the vector kernels: 28 288 patches 84
-// wide 8.8 -> 3.9 ms, 1 408 patches 120 wide (FP64 storage) 956 -> 589 us.
+// and their panels do not fit a workgroup's registers).  Against the vector kernels: 28 288 patches 85
+// wide 8.8 -> 2.9 ms, 1 408 patches 120 wide (FP64 storage) 956 -> 454 us.
 inline int mfma_tiles(int n) {
   return n <= 64 || n == 84 || n == 85 || n == 105 || n == 120 || n == 170 ? (n + 15) / 16 : 0;
 }
