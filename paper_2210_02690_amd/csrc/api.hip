@@ -165,8 +165,7 @@ size_t plan_workspace(vk_ctx* ctx, vk_prec prec, int32_t restart, char* base) {
         L.chain.buf = cv.take<double>(L.chain.cap);
         L.chain.table = cv.take<char>(L.chain.table_cap);
       }
-      // (a chain's elimination step inverts up to two blocks of each block at once)
-      L.cb_gi = cv.take<double>((int64_t)nbk * (L.chain.cap > 0 ? 2 : 1) * VK_GJ_NBI_MAX * VK_GJ_NBO);
+      L.cb_gi = cv.take<double>((int64_t)nbk * VK_GJ_NBI_MAX * VK_GJ_NBO);
       L.cb_go = cv.take<double>((int64_t)VK_GJ_NBO * (L.cb_rows[nbk] - L.cb_rows[0]));
       L.d_cb_rows = cv.take<int64_t>(nbk + 1);
       L.d_cb_woff = cv.take<int64_t>(nbk);

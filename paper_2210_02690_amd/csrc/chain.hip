@@ -16,12 +16,13 @@
 //   G_ii = S_i^{-1} - X_i G_{i+1,i},  G_jj = T_j^{-1} - Y_j G_{j-1,j},  G_ij = -X_i G_{i+1,j},
 //   G_ji = -Y_j G_{j-1,i},   Z_i = L_{i+1} S_i^{-1},  W_j = U_{j-1} T_j^{-1},
 // two launches of matrix-core products a step.  The solve stays one product with the dense inverse.
-// Measured, dense -> chain: 592 unknowns (88 x 16, k = 1) 1.14 -> 0.37 ms, 888 (176 x 32, k = 2) 1.79 -> 0.77 ms,
-// 2 060 (88 x 16, Q4) 7.15 -> 2.65 ms, the blocks of 64 systems 17 -> 11.6 ms.  What bounds it now is
-// the chain of pivot steps inside the S_i (0.5 us each up to 176 rows, 1.7 us in the blocked kernels).
+// Measured, dense -> chain: 592 unknowns (88 x 16, k = 1) 1.14 -> 0.37 ms, 888 (176 x 32, k = 2) 1.79 -> 0.52 ms,
+// 2 060 (88 x 16, Q4) 7.15 -> 1.43 ms, 3 213 (48 x 8 x 8, k = 2) 13.5 -> 4.0 ms, the blocks of 64 systems 17 ->
+// 6.5 ms.  What bounds it now is the chain of pivot steps inside the S_i, 0.5 us each, and for single
+// blocks the launches between them.
 //
-// Pivots are sought inside a chain block only, so a regular matrix can meet a singular or badly
-// conditioned chain block.  Each inverse is therefore checked (max |v - J G v| for a fixed v); a
+// Pivots are sought inside a piece only, so a regular matrix can meet a singular or badly
+// conditioned one.  Each inverse is therefore checked (max |v - J G v| for a fixed v); a
 // level that fails is inverted densely before the solve goes on, and stays dense.
 #include <algorithm>
 #include <climits>
@@ -33,8 +34,9 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront per row: a chained row's entries go to D, U or L of its chain block, a row of a dense block to the block (column-major).  cb: the row's chain block, or -1 - b
-// for dense block b; ri: the row's index in it.
+// One wavefront per row: a chained row's entries go to D, U or L of its chain block, a row of a dense block to
+// the block (column-major).  cb: the row's chain block, or -1 - b for dense block b; ri: the row's index in
+// it.
 __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_t n_rows, const int64_t* __restrict__ row_ptr,
                                                            const int32_t* __restrict__ col,
                                                            const double* __restrict__ val,
@@ -143,11 +145,11 @@ __global__ void chain_probe_kernel(int64_t n, double* v) {
 }
 
 // flags the level when some chained row's |v - J G v| is not small (entries of v are 0.6 to 2.5; a good
-// inverse leaves 1e-15 times the condition number)
+// inverse leaves 1e-16 times the condition number, 1e-11 for a coarse level of condition 1e5)
 __global__ void chain_check_kernel(int64_t first, int64_t n, const int32_t* __restrict__ cb, const double* __restrict__ jz,
                                    int32_t* flag) {
   for (int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    if (cb[i] >= 0 && !(fabs(jz[i] - probe_value(i)) <= 1e-8)) atomicOr(flag, 1);
+    if (cb[i] >= 0 && !(fabs(jz[i] - probe_value(i)) <= 1e-9)) atomicOr(flag, 1);
 }
 
 // breadth-first levels from `start`; the number reached, and the lowest vertex of the last level
