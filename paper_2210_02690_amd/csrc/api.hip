@@ -164,6 +164,7 @@ size_t plan_workspace(vk_ctx* ctx, vk_prec prec, int32_t restart, char* base) {
       if (L.chain.cap > 0) {
         L.chain.buf = cv.take<double>(L.chain.cap);
         L.chain.table = cv.take<char>(L.chain.table_cap);
+        L.chain.jval = cv.take<double>(L.cb_nnz);
       }
       L.cb_gi = cv.take<double>((int64_t)nbk * VK_GJ_NBI_MAX * VK_GJ_NBO);
       L.cb_go = cv.take<double>((int64_t)VK_GJ_NBO * (L.cb_rows[nbk] - L.cb_rows[0]));
@@ -536,7 +537,8 @@ vk_status replay(vk_ctx* ctx, size_t slot, const int64_t (&key)[6], F&& enqueue)
 }
 
 // Levels whose chained inverses failed their check are inverted densely, once and for all, before
-// anything uses them (a host wait for the block inversions, on levels with chains only).
+// anything uses them (a host wait for the block inversions, on levels with chains only), from the
+// values of J that the setup read: the caller's may have changed since.
 vk_status chain_settle(vk_ctx* ctx) {
   bool any = false;
   for (const vk_level& L : ctx->lv) any = any || L.chain.active;
@@ -553,22 +555,30 @@ vk_status chain_settle(vk_ctx* ctx) {
     if (!L.chain.active || bad[l] == 0) continue;
     L.chain.active = false;
     ++ctx->gen;
-    VK_TRY(launch_block_invert(ctx->side, L, ctx->status, &L.cb_W, &ctx->la, ctx->coarse_min_tourney));
+    vk_level S = L;
+    S.J = vk_chain_J(L);
+    VK_TRY(launch_block_invert(ctx->side, S, ctx->status, &L.cb_W, &ctx->la, ctx->coarse_min_tourney));
     VK_TRY(hipEventRecord(ctx->join_ev, ctx->side));
   }
   return VK_OK;
 }
 
-// Make the context stream wait for the block inversions of the last setup (no host wait but
-// chain_settle's).
-// With check_now the stream is synchronised and their status words are checked at once.
+// Order the context stream after the block inversions of the last setup (no host wait).
+vk_status coarse_join(vk_ctx* ctx) {
+  if (!ctx->coarse_pending) return VK_OK;
+  VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->join_ev, 0));
+  for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->xjoin[i], 0));
+  ctx->coarse_pending = false;
+  return VK_OK;
+}
+
+// The same for a solve: chained inverses that failed their check are replaced first (chain_settle).
+// With check_now the stream is synchronised and the status words are checked at once.
 vk_status coarse_check(vk_ctx* ctx);
 vk_status coarse_wait(vk_ctx* ctx, bool check_now) {
   if (ctx->coarse_pending) {
     VK_CHECK(chain_settle(ctx));
-    VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->join_ev, 0));
-    for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->stream, ctx->xjoin[i], 0));
-    ctx->coarse_pending = false;
+    VK_CHECK(coarse_join(ctx));
     ctx->coarse_check_due = true;
   }
   if (check_now) return coarse_check(ctx);
@@ -812,6 +822,13 @@ vk_status vk_set_level_groups(vk_ctx* ctx, int32_t l, const vk_csr* J, const vk_
              l, flag);
     return fail(ctx, VK_ERR_ARG, buf);
   }
+  if (vk_chain_buffer(L) > 0) {
+    int64_t e[2];
+    VK_CHECK(to_host2(ctx, &e[0], L.J.row_ptr + L.cb_rows.front(), sizeof(int64_t), &e[1],
+                      L.J.row_ptr + L.cb_rows.back(), sizeof(int64_t)));
+    L.cb_e0 = e[0];
+    L.cb_nnz = e[1] - e[0];
+  }
   L.lpr_J = vk_pick_lpr(L.J.n_rows, L.J.nnz);
   if (l > 0) {
     L.lpr_P = vk_pick_lpr(L.P.n_rows, L.P.nnz);
@@ -920,8 +937,9 @@ vk_status vanka_setup(vk_ctx* ctx, double omega, vk_mode mode, int32_t* bad_leve
   if (!(omega > 0.0) || !std::isfinite(omega)) return fail(ctx, VK_ERR_ARG, "omega must be positive");
   if (mode != VK_ADDITIVE && mode != VK_MULT_COLOURED) return fail(ctx, VK_ERR_ARG, "unknown smoother mode");
   ctx->setup_done = false;
-  // the previous setup's block inversions (and their status words) come before this one's
-  VK_CHECK(coarse_wait(ctx, false));
+  // the previous setup's block inversions (and their status words) come before this one's; if no solve
+  // has used them, what their checks found no longer matters
+  VK_CHECK(coarse_join(ctx));
   VK_CHECK(patch_settle(ctx, false));  // the last setup's coarser levels still write their status words
   ctx->coarse_check_due = false;
   // recorded graphs stay valid across setups unless omega, the mode or where an inverse lives changes

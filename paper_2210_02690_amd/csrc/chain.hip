@@ -35,14 +35,16 @@ namespace {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // One wavefront per row: a chained row's entries go to D, U or L of its chain block, a row of a dense block to
-// the block (column-major).  cb: the row's chain block, or -1 - b for dense block b; ri: the row's index in
-// it.
+// the block (column-major), and all values to jval: this kernel is the only one that reads the caller's, so
+// they may change once it has run.  cb: the row's chain block, or -1 - b for dense block b; ri: the
+// row's index in it.
 __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_t n_rows, const int64_t* __restrict__ row_ptr,
                                                            const int32_t* __restrict__ col,
                                                            const double* __restrict__ val,
                                                            const int32_t* __restrict__ cb, const int32_t* __restrict__ ri,
                                                            const vk_chain_block* __restrict__ blk,
-                                                           const vk_chain_dense* __restrict__ dense, int32_t* status) {
+                                                           const vk_chain_dense* __restrict__ dense, int64_t e_first,
+                                                           double* __restrict__ jval, int32_t* status) {
   const int64_t r = first + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (r >= n_rows) return;
@@ -52,22 +54,26 @@ __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_
     const vk_chain_dense q = dense[-1 - b];
     for (int64_t e = row_ptr[r] + lane; e < e1; e += 64) {
       const int64_t c = (int64_t)col[e] - q.r0;
+      const double x = val[e];
+      jval[e - e_first] = x;
       if (c < 0 || c >= q.n) atomicOr(&status[1], 1);
-      else q.w[c * q.n + i] = val[e];
+      else q.w[c * q.n + i] = x;
     }
     return;
   }
   const vk_chain_block q = blk[b];
   for (int64_t e = row_ptr[r] + lane; e < e1; e += 64) {
     const int64_t c = col[e];
+    const double x = val[e];
+    jval[e - e_first] = x;
     if (c < q.r0 || c >= q.r1) {
       atomicOr(&status[1], 1);
       continue;
     }
     const int bc = cb[c], j = ri[c];
-    if (bc == b) q.D[q.d_cm ? (int64_t)j * q.s + i : (int64_t)i * q.s + j] = val[e];
-    else if (bc == b + 1) q.U[(int64_t)i * q.s_next + j] = val[e];
-    else if (bc == b - 1) q.L[(int64_t)i * q.s_prev + j] = val[e];
+    if (bc == b) q.D[q.d_cm ? (int64_t)j * q.s + i : (int64_t)i * q.s + j] = x;
+    else if (bc == b + 1) q.U[(int64_t)i * q.s_next + j] = x;
+    else if (bc == b - 1) q.L[(int64_t)i * q.s_prev + j] = x;
     else atomicOr(&status[1], 2);  // the plan makes this impossible
   }
 }
@@ -272,11 +278,13 @@ size_t vk_chain_table_bytes(const vk_level& L) {
 bool vk_chain_plan(vk_level& L) {
   vk_chain& T = L.chain;
   double* const buf = T.buf;
+  double* const jval = T.jval;
   char* const table = T.table;
   const int64_t cap = T.cap;
   const size_t table_cap = T.table_cap;
   T = vk_chain();
   T.buf = buf;
+  T.jval = jval;
   T.cap = cap;
   T.table = table;
   T.table_cap = table_cap;
@@ -639,6 +647,12 @@ bool vk_chain_plan(vk_level& L) {
   return true;
 }
 
+vk_csr vk_chain_J(const vk_level& L) {
+  vk_csr A = L.J;
+  A.val = L.chain.jval - L.cb_e0;
+  return A;
+}
+
 static hipError_t gemm_list(hipStream_t s, const vk_gemm_list& l) {
   if (l.count == 0) return hipSuccess;
   chain_gemm_kernel<<<dim3((unsigned)l.tiles, (unsigned)l.count), 256, 0, s>>>(l.items);
@@ -671,7 +685,7 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
   }
   if ((e = launch_fill_i32(s, 1, INT_MAX, scratch)) != hipSuccess) return e;
   chain_gather_kernel<<<(unsigned)((T.rows - T.first + 3) / 4), 256, 0, s>>>(T.first, T.rows, L.J.row_ptr, L.J.col, L.J.val, T.cb, T.ri,
-                                                                   T.blocks, T.d_dense, status);
+                                                                   T.blocks, T.d_dense, L.cb_e0, T.jval, status);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (const vk_chain_step& S : T.steps) {
     for (const vk_chain_piece& C : S.pieces) {
@@ -703,7 +717,7 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
   chain_probe_kernel<<<g, 256, 0, s>>>(T.rows, T.v);
   if ((e = launch_fill_i32(s, 1, 0, flag)) != hipSuccess) return e;
   if ((e = launch_block_apply(s, L, T.v, T.z)) != hipSuccess) return e;
-  vk_csr A = L.J;
+  vk_csr A = vk_chain_J(L);
   A.n_rows = nr;
   A.row_ptr += T.first;
   if ((e = launch_spmv(s, A, L.lpr_J, 1.0, T.z, 0.0, nullptr, T.jz + T.first)) != hipSuccess) return e;

@@ -231,6 +231,7 @@ struct vk_chain {
   std::vector<vk_gemm_list> ga, gb;
   std::vector<vk_chain_rest> rest;
   double *v = nullptr, *z = nullptr, *jz = nullptr;
+  double* jval = nullptr;  // the setup's values of J's rows [first, rows): what the check and a dense fallback read
 };
 
 struct vk_level {
@@ -242,6 +243,7 @@ struct vk_level {
   std::vector<int64_t> cb_rows;     // directly solved diagonal blocks: row offsets (n_blocks + 1)
   int64_t cb_max = 0;               // largest block
   int64_t cb_sq = 0;                // sum of squared block sizes
+  int64_t cb_e0 = 0, cb_nnz = 0;    // J's entries in the blocks' rows (levels that can have chains only)
   int lpr_J = 4, lpr_P = 4, lpr_R = 4;
   vk_gcsr gJ;           // grouped CSR of J, used by the J products while gJ.active and use_gJ
   bool use_gJ = false;
@@ -479,6 +481,8 @@ int64_t vk_chain_buffer(const vk_level& L);
 size_t vk_chain_table_bytes(const vk_level& L);
 bool vk_chain_plan(vk_level& L);
 hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status, int32_t* scratch, int32_t* flag);
+// L's J with the values that the last launch_chain_invert read (the blocks' rows only)
+vk_csr vk_chain_J(const vk_level& L);
 hipError_t launch_block_export(hipStream_t s, const vk_level& L, int32_t block, double* out);
 // Krylov
 hipError_t launch_dot(hipStream_t s, int64_t n, const double* x, const double* y, double* partial,

@@ -1,0 +1,109 @@
+"""Which values of J, and which inverse, a level with chain inverses answers with: values that change between
+setups, chain blocks that are singular or badly conditioned although J is not.
+
+The matrices are banded and randomly permuted.  `mates`: unknowns i and i + 50 of every 100 are coupled by
+entries of 1 to 2, everything else in the band by noise of size eps.  J then has a condition number below 5,
+but the level sets cut through the pairs, so the chain's first blocks have the noise for pivots: singular
+for eps = 0, inverses of size 1 / eps otherwise.
+
+Tolerance: Gauss-Jordan with partial pivoting over all rows leaves an error of n u cond(J) relative to the
+inverse's largest entry up to its growth factor, here at most 10 (u = 2^-53)."""
+import types
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+DEV = "cuda:0"
+N, BAND, U = 700, 60, 2.0 ** -53
+
+
+def _matrix(kind, eps=0.0, n=N, seed=7):
+    rng = np.random.default_rng(seed)
+    i = np.repeat(np.arange(n), 2 * BAND + 1)
+    j = (np.arange(n)[:, None] + np.arange(-BAND, BAND + 1)[None, :]).ravel()
+    i, j = i[(j >= 0) & (j < n)], j[(j >= 0) & (j < n)]
+    p = rng.permutation(n)
+    v = rng.standard_normal(len(i))
+    if kind == "plain":
+        v += 2.0 * np.sqrt(BAND) * (i == j)
+    else:
+        v *= eps
+        mate = j == np.where(i % 100 < 50, i + 50, i - 50)
+        v[mate] += 1.0 + rng.random(mate.sum())
+    J = sp.csr_matrix((v, (p[i], p[j])), shape=(n, n))
+    J.sort_indices()
+    return J
+
+
+def _vk():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2210_02690_amd as vk
+    return vk
+
+
+def _solver(vk, J):
+    lv = types.SimpleNamespace(J=J, P=None, R=None, cell_dofs=np.zeros((1, 1), np.int32), colours=np.zeros(1, np.int32))
+    S = vk.Solver([vk.upload_level(lv, DEV)])
+    S.vk_set_workspace("f64", 5, device=DEV)
+    return S
+
+
+def _put(S, J):
+    S.levels[0]["J"]["val"].copy_(torch.from_numpy(J.data))
+    torch.cuda.synchronize()
+
+
+def _check(S, J):
+    """The V-cycle (its coarse solve alone) and the exported inverse against numpy."""
+    A = J.toarray()
+    n = len(A)
+    want = np.linalg.inv(A)
+    bound = 10 * n * U * np.linalg.cond(A) * np.abs(want).max()
+    b = np.random.default_rng(2).standard_normal(n)
+    x = torch.empty(n, dtype=torch.float64, device=DEV)
+    S.vcycle(torch.from_numpy(b).to(DEV), x, 0, 0)
+    assert np.abs(x.cpu().numpy() - want @ b).max() <= bound * np.abs(b).sum()
+    got = torch.empty((n, n), dtype=torch.float64, device=DEV)
+    S.vk_get_coarse_inverse(got)
+    assert np.abs(got.cpu().numpy() - want).max() <= bound
+
+
+def _chained(S):
+    n = S.levels[0]["J"]["n_rows"]
+    return S.vk_coarse_plan(0)[1] < 2.0 * n ** 3
+
+
+@pytest.mark.parametrize("kind", ["plain", "mates"])
+def test_solves_use_the_values_of_the_setup(kind):
+    """J overwritten after the setup (and the device synchronised), before the first solve: the setup's
+    inverse answers, whether its chain holds or a dense inverse takes its place."""
+    vk = _vk()
+    J = _matrix(kind)
+    S = _solver(vk, J)
+    S.vanka_setup(0.7, "additive")
+    torch.cuda.synchronize()
+    other = J.copy()
+    other.data = 3.0 * np.random.default_rng(11).standard_normal(len(J.data))
+    _put(S, other)
+    _check(S, J)
+    S.close()
+
+
+def test_an_unused_setup_leaves_nothing_behind():
+    """A setup whose chain failed and that no solve used does not decide how the next one inverts."""
+    vk = _vk()
+    S = _solver(vk, _matrix("mates"))
+    S.vanka_setup(0.7, "additive")
+    torch.cuda.synchronize()
+    _put(S, _matrix("plain"))
+    S.vanka_setup(0.7, "additive")
+    assert _chained(S)
+    _check(S, _matrix("plain"))
+    assert _chained(S)
+    S.close()
