@@ -342,8 +342,8 @@ double vk_spmv_bytes(vk_ctx* ctx, int32_t level);
  * get their dense inverse through the same structure with blocks of at least 64
  * unknowns, where that is estimated to be faster; such inverses are checked on
  * a fixed vector before their first use, which waits on the host for them, and
- * a level that fails the check is inverted by Gauss-Jordan, then and at later
- * setups.  Blocks without such a structure, and every block under mode 1, get
+ * a level that fails the check is inverted by Gauss-Jordan instead, from the
+ * setup's values; the next setup takes the structure again.  Blocks without such a structure, and every block under mode 1, get
  * the dense inverse by Gauss-Jordan with partial pivoting.  All
  * compute J_0^{-1} b up to rounding; a singular block is reported by the first
  * solve either way.  vk_get_coarse_inverse needs the dense inverse.  Setup must

@@ -536,12 +536,13 @@ vk_status replay(vk_ctx* ctx, size_t slot, const int64_t (&key)[6], F&& enqueue)
   return VK_OK;
 }
 
-// Levels whose chained inverses failed their check are inverted densely, once and for all, before
-// anything uses them (a host wait for the block inversions, on levels with chains only), from the
-// values of J that the setup read: the caller's may have changed since.
+// Levels whose chained inverses failed their check are inverted densely before anything uses them (a
+// host wait for the block inversions, on levels with chains only), from the values of J that the setup
+// read: the caller's may have changed since.  The next setup tries the chain again, so the values alone
+// decide how a level is inverted.
 vk_status chain_settle(vk_ctx* ctx) {
   bool any = false;
-  for (const vk_level& L : ctx->lv) any = any || L.chain.active;
+  for (const vk_level& L : ctx->lv) any = any || L.chain.holds();
   if (!any) return VK_OK;
   for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->side, ctx->xjoin[i], 0));
   int32_t bad[64];
@@ -552,8 +553,8 @@ vk_status chain_settle(vk_ctx* ctx) {
   VK_CHECK(rc);
   for (int l = 0; l < ctx->n_levels; ++l) {
     vk_level& L = ctx->lv[l];
-    if (!L.chain.active || bad[l] == 0) continue;
-    L.chain.active = false;
+    if (!L.chain.holds() || bad[l] == 0) continue;
+    L.chain.failed = true;
     ++ctx->gen;
     vk_level S = L;
     S.J = vk_chain_J(L);
@@ -1125,6 +1126,8 @@ vk_status vanka_setup(vk_ctx* ctx, double omega, vk_mode mode, int32_t* bad_leve
       if (L.bt.active) VK_TRY(launch_bt_factor(st, L, ctx->status));
       else if (L.chain.active) {
         L.cb_W = L.cb_a;
+        if (L.chain.failed) ++ctx->gen;
+        L.chain.failed = false;
         VK_TRY(launch_chain_invert(st, L, ctx->status, ctx->status + 964, ctx->status + 900 + blevels[k]));
       }
       else VK_TRY(launch_block_invert(st, L, ctx->status, &L.cb_W, k == 0 ? &ctx->la : nullptr, ctx->coarse_min_tourney));
@@ -1721,7 +1724,7 @@ int32_t vk_coarse_plan(vk_ctx* ctx, int32_t level, double* setup_flops) {
     if (setup_flops) *setup_flops = L.bt.flops;
     return L.bt.nb;
   }
-  if (L.chain.active) {
+  if (L.chain.holds()) {
     if (setup_flops) *setup_flops = L.chain.flops;
     return 0;
   }

@@ -23,7 +23,7 @@
 //
 // Pivots are sought inside a piece only, so a regular matrix can meet a singular or badly
 // conditioned one.  Each inverse is therefore checked (max |v - J G v| for a fixed v); a
-// level that fails is inverted densely before the solve goes on, and stays dense.
+// level that fails is inverted densely before the solve goes on.
 #include <algorithm>
 #include <climits>
 #include <vector>

@@ -841,8 +841,8 @@ hipError_t launch_block_apply(hipStream_t s, const vk_level& L, const double* x,
   if (nbk <= 0) return hipSuccess;
   const int64_t rows_total = L.cb_rows[nbk] - L.cb_rows[0];
   block_apply_kernel<<<(unsigned)((rows_total * 64 + 255) / 256), 256, 0, s>>>(nbk, L.d_cb_rows, L.d_cb_woff,
-                                                                              L.cb_W, L.chain.active ? L.chain.rmap : L.cb_q,
-                                                                              L.chain.active ? L.chain.cmap : L.cb_q, x, y);
+                                                                              L.cb_W, L.chain.holds() ? L.chain.rmap : L.cb_q,
+                                                                              L.chain.holds() ? L.chain.cmap : L.cb_q, x, y);
   return hipGetLastError();
 }
 
@@ -857,7 +857,7 @@ hipError_t launch_block_export(hipStream_t s, const vk_level& L, int32_t block, 
   if (g > 8192) g = 8192;
   if (g < 1) g = 1;
   const int64_t r0 = L.cb_rows[block];
-  block_export_kernel<<<(unsigned)g, 256, 0, s>>>(n, L.cb_W + woff, (L.chain.active ? L.chain.rmap : L.cb_q) + r0,
-                                                  (L.chain.active ? L.chain.cmap : L.cb_q) + r0, out);
+  block_export_kernel<<<(unsigned)g, 256, 0, s>>>(n, L.cb_W + woff, (L.chain.holds() ? L.chain.rmap : L.cb_q) + r0,
+                                                  (L.chain.holds() ? L.chain.cmap : L.cb_q) + r0, out);
   return hipGetLastError();
 }

@@ -214,6 +214,7 @@ struct vk_chain_rest {  // densely inverted blocks of one width class
 };
 struct vk_chain {
   bool planned = false, active = false;
+  bool failed = false;  // the last setup's chain failed its check: cb_a holds the dense inverse
   double* buf = nullptr;  // reserved space: cap doubles, table_cap bytes
   int64_t cap = 0;
   char* table = nullptr;
@@ -231,6 +232,7 @@ struct vk_chain {
   std::vector<vk_gemm_list> ga, gb;
   std::vector<vk_chain_rest> rest;
   double *v = nullptr, *z = nullptr, *jz = nullptr;
+  bool holds() const { return active && !failed; }  // cb_a holds the chain's inverse
   double* jval = nullptr;  // the setup's values of J's rows [first, rows): what the check and a dense fallback read
 };
 

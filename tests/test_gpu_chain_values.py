@@ -107,3 +107,47 @@ def test_an_unused_setup_leaves_nothing_behind():
     _check(S, _matrix("plain"))
     assert _chained(S)
     S.close()
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+def test_a_failed_chain_decides_for_its_own_setup_only(graphs):
+    """Values whose chain fails are inverted densely; the next values get the chain again, eagerly and
+    where V-cycles replay a graph recorded under the other inverse."""
+    vk = _vk()
+    S = _solver(vk, _matrix("plain"))
+    S.vk_set_graphs(graphs)
+    for kind in ("plain", "mates", "plain", "plain", "mates", "mates", "plain"):
+        J = _matrix(kind)
+        _put(S, J)
+        S.vanka_setup(0.7, "additive")
+        for rep in range(3):
+            _check(S, J)
+            assert _chained(S) == (kind == "plain")
+    S.close()
+
+
+def test_a_failed_chain_among_other_blocks():
+    """One block of a level fails its check beside a chained and a dense one: all three answer right, and
+    the level is chained again once its values allow it."""
+    vk = _vk()
+    rng = np.random.default_rng(3)
+    small = sp.csr_matrix(rng.standard_normal((150, 150)) + 20 * np.eye(150))
+    rows = np.array([0, N, N + 150, N + 150 + 900])
+    kinds = ("plain", "mates", "plain")
+    Js = [sp.block_diag([_matrix(k), small, _matrix("plain", n=900, seed=8)], format="csr") for k in kinds]
+    S = vk.Solver([dict(J=vk.upload_csr(Js[0], DEV), P=None, R=None, groups=[], blocks=rows)])
+    S.vk_set_workspace("f64", 5, device=DEV)
+    b = rng.standard_normal(rows[-1])
+    x = torch.empty(rows[-1], dtype=torch.float64, device=DEV)
+    for kind, J in zip(kinds, Js):
+        _put(S, J)
+        S.vanka_setup(0.7, "additive")
+        S.vcycle(torch.from_numpy(b).to(DEV), x, 0, 0)
+        assert (S.vk_coarse_plan(0)[1] < 2.0 * (np.diff(rows).astype(float) ** 3).sum()) == (kind == "plain")
+        got = x.cpu().numpy()
+        for r0, r1 in zip(rows[:-1], rows[1:]):
+            A = J[r0:r1, r0:r1].toarray()
+            want = np.linalg.inv(A)
+            bound = 10 * (r1 - r0) * U * np.linalg.cond(A) * np.abs(want).max()
+            assert np.abs(got[r0:r1] - want @ b[r0:r1]).max() <= bound * np.abs(b[r0:r1]).sum()
+    S.close()
