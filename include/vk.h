@@ -340,9 +340,12 @@ double vk_spmv_bytes(vk_ctx* ctx, int32_t level);
  * vk_set_workspace (the pattern is copied to the host once).  Directly solved
  * blocks of 384 to 4096 unknowns (any number a level, vk_set_coarse_pivoting 0)
  * get their dense inverse through the same structure with blocks of at least 64
- * unknowns, where that is estimated to be faster; such inverses are checked on
- * a fixed vector before their first use, which waits on the host for them, and
- * a level that fails the check is inverted by Gauss-Jordan instead, from the
+ * unknowns, where that is estimated to be faster.  Such an inverse G is checked
+ * before its first use, which waits on the host for it: for a fixed vector v the
+ * error |G (J_0 v) - v| may not exceed 16 u (u = 2^-53) times the largest entry
+ * of |G| |J_0| |v| in its block, about what Gauss-Jordan with pivoting over the
+ * whole block leaves.  One that exceeds it is refined, G + G (I - J_0 G), up to
+ * 64 u, or else its level is inverted by Gauss-Jordan, both with the
  * setup's values; the next setup takes the structure again.  Blocks without such a structure, and every block under mode 1, get
  * the dense inverse by Gauss-Jordan with partial pivoting.  All
  * compute J_0^{-1} b up to rounding; a singular block is reported by the first

@@ -536,8 +536,8 @@ vk_status replay(vk_ctx* ctx, size_t slot, const int64_t (&key)[6], F&& enqueue)
   return VK_OK;
 }
 
-// Levels whose chained inverses failed their check are inverted densely before anything uses them (a
-// host wait for the block inversions, on levels with chains only), from the values of J that the setup
+// Levels whose chained inverses failed their check are refined, or else inverted densely, before anything
+// uses them (a host wait for the block inversions, on levels with chains only), from the values of J that the setup
 // read: the caller's may have changed since.  The next setup tries the chain again, so the values alone
 // decide how a level is inverted.
 vk_status chain_settle(vk_ctx* ctx) {
@@ -546,11 +546,24 @@ vk_status chain_settle(vk_ctx* ctx) {
   if (!any) return VK_OK;
   for (int i = 0; i < ctx->n_xside; ++i) VK_TRY(hipStreamWaitEvent(ctx->side, ctx->xjoin[i], 0));
   int32_t bad[64];
-  const hipStream_t user = ctx->stream;
-  ctx->stream = ctx->side;
-  const vk_status rc = to_host(ctx, bad, ctx->status + 900, sizeof(bad));
-  ctx->stream = user;
-  VK_CHECK(rc);
+  auto read = [&]() -> vk_status {
+    const hipStream_t user = ctx->stream;
+    ctx->stream = ctx->side;
+    const vk_status rc = to_host(ctx, bad, ctx->status + 900, sizeof(bad));
+    ctx->stream = user;
+    return rc;
+  };
+  VK_CHECK(read());
+  bool refined = false;
+  for (int l = 0; l < ctx->n_levels; ++l) {
+    if (!ctx->lv[l].chain.holds() || bad[l] != 1) continue;
+    VK_TRY(launch_chain_refine(ctx->side, ctx->lv[l], ctx->status + 900 + l));
+    refined = true;
+  }
+  if (refined) {
+    VK_TRY(hipEventRecord(ctx->join_ev, ctx->side));
+    VK_CHECK(read());
+  }
   for (int l = 0; l < ctx->n_levels; ++l) {
     vk_level& L = ctx->lv[l];
     if (!L.chain.holds() || bad[l] == 0) continue;

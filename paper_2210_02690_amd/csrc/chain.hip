@@ -22,8 +22,8 @@
 // blocks the launches between them.
 //
 // Pivots are sought inside a piece only, so a regular matrix can meet a singular or badly
-// conditioned one.  Each inverse is therefore checked (max |v - J G v| for a fixed v); a
-// level that fails is inverted densely before the solve goes on.
+// conditioned one.  Each inverse is therefore checked; one that fails is refined by a step of Newton's
+// iteration for inverses, or, where that does not do, its level is inverted densely before the solve goes on.
 #include <algorithm>
 #include <climits>
 #include <vector>
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void chain_gemm_kernel(const vk_gemm_item* __r
   __shared__ double As[32 * LA];
   __shared__ double Bs[KC * LB];
   const int tn = (p.n + 31) / 32, m0 = (int)blockIdx.x / tn * 32, n0 = (int)blockIdx.x % tn * 32;
-  if (m0 >= p.m) return;  // uniform: the grid covers the largest item
+  if (m0 >= p.m || (p.on && *p.on == 0)) return;  // uniform: the grid covers the largest item
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
   const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
@@ -143,19 +143,144 @@ __global__ void chain_dense_maps_kernel(const vk_chain_dense* __restrict__ real,
   if (i < d.n) rmap[d.r0 + i] = cmap[d.r0 + i] = q[rows[blockIdx.y] + i];
 }
 
+// The check of a chained inverse G: the error |G (J v) - v| of a solve whose solution v is known,
+// relative to the largest entry of |G| |J| |v|, per directly solved block.  In units of u = 2^-53 dense
+// Gauss-Jordan with pivoting over all rows leaves 0.3 to 13 there (coarse levels of 592 and 888
+// unknowns, peak velocities 0.3 to 1 000, time steps 0.01 and 100; up to 7 000 at 1e-5), an ordinary chain
+// 0.4 to 10 (10 to 600), with solutions as accurate.  A chain whose pieces are badly conditioned
+// leaves 20 to 1e8 and solutions worse by as much: 20, 50 and 87 for three strongly convective matrices, 6,
+// 5 and 10 times the dense inverse's error.  So up to CHECK_LIMIT a chain is accepted.  Beyond, one
+// step G + G (I - J G) squares the defect, after which solutions have one to two digits more than the
+// dense inverse's and the measure is 0.1 to 26 (rounding of J v): hence REFINED_LIMIT.  An error above REFINE_MAX
+// is not worth the step.  (|v - J G v| would not do: dense Gauss-Jordan leaves 4 to 600 there without
+// any loss in its solutions.)
+constexpr double CHECK_LIMIT = 16.0, REFINED_LIMIT = 64.0, REFINE_MAX = 1e-3;
+
 __device__ inline double probe_value(int64_t i) { return 1.0 + 0.125 * (double)(i % 13) - 0.0625 * (double)(i % 7); }
 
-__global__ void chain_probe_kernel(int64_t n, double* v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    v[i] = probe_value(i);
+// w = J v and wa = |J| v on the chained rows, a wavefront per row
+__global__ __launch_bounds__(256) void chain_probe_kernel(int64_t first, int64_t n_rows, const int64_t* __restrict__ row_ptr,
+                                                          const int32_t* __restrict__ col, const double* __restrict__ jval,
+                                                          int64_t e_first, const int32_t* __restrict__ cb,
+                                                          const vk_chain_block* __restrict__ blk, double* __restrict__ w,
+                                                          double* __restrict__ wa) {
+  const int64_t r = first + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (r >= n_rows || cb[r] < 0) return;
+  const int64_t r0 = blk[cb[r]].r0;
+  double s = 0.0, a = 0.0;
+  for (int64_t e = row_ptr[r] + lane; e < row_ptr[r + 1]; e += 64) {
+    const double x = jval[e - e_first], v = probe_value(col[e] - r0);
+    s = fma(x, v, s);
+    a = fma(fabs(x), v, a);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    s += __shfl_xor(s, o, 64);
+    a += __shfl_xor(a, o, 64);
+  }
+  if (lane == 0) {
+    w[r] = s;
+    wa[r] = a;
+  }
 }
 
-// flags the level when some chained row's |v - J G v| is not small (entries of v are 0.6 to 2.5; a good
-// inverse leaves 1e-16 times the condition number, 1e-11 for a coarse level of condition 1e5)
-__global__ void chain_check_kernel(int64_t first, int64_t n, const int32_t* __restrict__ cb, const double* __restrict__ jz,
-                                   int32_t* flag) {
-  for (int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    if (cb[i] >= 0 && !(fabs(jz[i] - probe_value(i)) <= 1e-9)) atomicOr(flag, 1);
+// rs[2 k], rs[2 k + 1]: the largest |G w - v| and |G| wa of the k-th chained block, as bits (of
+// nonnegative numbers: they order alike, NaN above all).  A wavefront per row, four rows' maxima together.
+__global__ __launch_bounds__(256) void chain_error_kernel(int64_t first, int64_t n_rows, const int32_t* __restrict__ cb,
+                                                          const vk_chain_block* __restrict__ blk,
+                                                          const int32_t* __restrict__ rmap, const int32_t* __restrict__ cmap,
+                                                          const double* __restrict__ w, const double* __restrict__ wa,
+                                                          unsigned long long* rs) {
+  __shared__ unsigned long long m0[4], m1[4];
+  __shared__ int at[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t r = first + (int64_t)blockIdx.x * 4 + wave;
+  const bool ok = r < n_rows && cb[r < n_rows ? r : first] >= 0;  // uniform in the wavefront
+  if (lane == 0) at[wave] = -1;
+  if (ok) {
+    const vk_chain_block q = blk[cb[r]];
+    const int64_t n = q.r1 - q.r0;
+    const double* g = q.W + (int64_t)rmap[r] * n;
+    const int32_t* cm = cmap + q.r0;
+    const double *x = w + q.r0, *xa = wa + q.r0;
+    double s = 0.0, a = 0.0;
+#pragma unroll 4
+    for (int64_t j = lane; j < n; j += 64) {
+      s = fma(g[j], x[cm[j]], s);
+      a = fma(fabs(g[j]), xa[cm[j]], a);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      s += __shfl_xor(s, o, 64);
+      a += __shfl_xor(a, o, 64);
+    }
+    if (lane == 0) {
+      at[wave] = q.chained;
+      m0[wave] = (unsigned long long)__double_as_longlong(fabs(s - probe_value(r - q.r0)));
+      m1[wave] = (unsigned long long)__double_as_longlong(fabs(a));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int i = 0; i < 4; ++i) {
+    if (at[i] < 0) continue;
+    if (i < 3 && at[i + 1] == at[i]) {
+      m0[i + 1] = max(m0[i + 1], m0[i]);
+      m1[i + 1] = max(m1[i + 1], m1[i]);
+      continue;
+    }
+    atomicMax(&rs[2 * at[i]], m0[i]);
+    atomicMax(&rs[2 * at[i] + 1], m1[i]);
+  }
+}
+
+__global__ __launch_bounds__(256) void chain_judge_kernel(int n_chained, const unsigned long long* __restrict__ rs, double limit,
+                                                          int32_t* bad, int32_t* flag) {
+  __shared__ int worst;
+  if (threadIdx.x == 0) worst = 0;
+  __syncthreads();
+  for (int k = threadIdx.x; k < n_chained; k += blockDim.x) {
+    const double r = __longlong_as_double((long long)rs[2 * k]), a = __longlong_as_double((long long)rs[2 * k + 1]);
+    const bool ok = r <= limit * 0x1p-53 * a && a < __builtin_huge_val();
+    bad[k] = ok ? 0 : (r <= REFINE_MAX ? 1 : 2);
+    if (!ok) atomicMax(&worst, bad[k]);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = worst;
+}
+
+// The defect R = I - J G of every chained block that the check did not accept, in the chain's order: a workgroup per row of J, its
+// entries through LDS, a thread per column.
+__global__ __launch_bounds__(256) void chain_defect_kernel(int64_t first, const int64_t* __restrict__ row_ptr,
+                                                           const int32_t* __restrict__ col, const double* __restrict__ jval,
+                                                           int64_t e_first, const int32_t* __restrict__ cb,
+                                                           const vk_chain_block* __restrict__ blk,
+                                                           const int32_t* __restrict__ rmap, const int32_t* __restrict__ cmap,
+                                                           const int32_t* __restrict__ bad) {
+  __shared__ double sv[256];
+  __shared__ const double* sw[256];
+  const int64_t r = first + blockIdx.x;
+  if (cb[r] < 0) return;  // uniform
+  const vk_chain_block q = blk[cb[r]];
+  if (bad[q.chained] == 0) return;
+  const int64_t n = q.r1 - q.r0, e1 = row_ptr[r + 1];
+  const int tid = threadIdx.x;
+  for (int64_t j0 = 0; j0 < n; j0 += 256) {
+    const int64_t j = j0 + tid;
+    double acc = 0.0;
+    for (int64_t eb = row_ptr[r]; eb < e1; eb += 256) {
+      const int cnt = (int)(e1 - eb < 256 ? e1 - eb : 256);
+      __syncthreads();
+      if (tid < cnt) {
+        sv[tid] = jval[eb + tid - e_first];
+        sw[tid] = q.W + (int64_t)rmap[col[eb + tid]] * n;
+      }
+      __syncthreads();
+      if (j < n)
+#pragma unroll 4
+        for (int k = 0; k < cnt; ++k) acc = fma(sv[k], sw[k][j], acc);
+    }
+    if (j < n) q.R[(int64_t)rmap[r] * n + j] = (cmap[q.r0 + j] == (int32_t)(r - q.r0) ? 1.0 : 0.0) - acc;
+  }
 }
 
 // breadth-first levels from `start`; the number reached, and the lowest vertex of the last level
@@ -256,7 +381,8 @@ double chain_us(int64_t s) {
 }
 double dense_us(double n) { return 30.0 * std::ceil(n / 16.0) + 40.0; }
 
-// doubles reserved for a block: a chain of blocks of s rows takes about 6 s n, and pays off up to about n = 5 s
+// doubles reserved for a block: a chain of blocks of s rows takes about 6 s n, and pays off up to about n = 5 s;
+// a refinement takes 1.5 n^2
 int64_t reserve(int64_t n) { return n < VK_CHAIN_MIN_N ? 0 : (n <= 1024 ? 2 * n * n : n * n + n * n / 2); }
 
 int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
@@ -265,8 +391,11 @@ int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
 
 int64_t vk_chain_buffer(const vk_level& L) {
   if (L.cb_rows.size() < 2 || L.cb_max < VK_CHAIN_MIN_N || L.cb_max > VK_TOURNEY_MIN_N) return 0;
-  int64_t need = 3 * up32(L.J.n_rows) + 32;
-  for (size_t b = 0; b + 1 < L.cb_rows.size(); ++b) need += reserve(L.cb_rows[b + 1] - L.cb_rows[b]);
+  int64_t need = 2 * up32(L.J.n_rows) + 2 * up32(2 * (int64_t)(L.cb_rows.size() - 1));
+  for (size_t b = 0; b + 1 < L.cb_rows.size(); ++b) {
+    const int64_t n = L.cb_rows[b + 1] - L.cb_rows[b];
+    if (n >= VK_CHAIN_MIN_N) need += reserve(n) + n + 64;
+  }
   return need;
 }
 
@@ -405,6 +534,16 @@ bool vk_chain_plan(vk_level& L) {
   int64_t n_chained = 0;
   for (int b = 0; b < nblk; ++b) n_chained += plans[b].ok;
   if (n_chained == 0) return false;
+  T.n_chained = (int)n_chained;
+  T.w = take(L.J.n_rows);
+  T.wa = take(L.J.n_rows);
+  T.rs = reinterpret_cast<unsigned long long*>(take(2 * n_chained));
+  T.bad = reinterpret_cast<int32_t*>(take(n_chained));
+  T.zero = buf + used;
+  const int64_t used0 = used;
+  int64_t r_used = used;  // a refinement's buffers take the chain's place
+  std::vector<vk_gemm_item> r_mul[2], r_put[2];
+  int chained = 0;
   std::vector<int> first(nblk, 0);
   for (int b = 0; b < nblk; ++b) {
     const int64_t r0 = L.cb_rows[b], n = L.cb_rows[b + 1] - r0;
@@ -420,6 +559,15 @@ bool vk_chain_plan(vk_level& L) {
     const block_plan& p = plans[b];
     const int nb = (int)p.size.size(), f = (int)blocks.size();
     first[b] = f;
+    double *const G = L.cb_a + woff[b], *const R = buf + r_used, *const H = R + up32(n * n);
+    const int64_t half = (n + 1) / 2;
+    r_used += up32(n * n) + up32(half * n);
+    for (int k = 0; k < 2; ++k) {  // rows [g0, g0 + m) of G + G R by way of H
+      const int64_t g0 = k * half, m = k == 0 ? half : n - half;
+      r_mul[k].push_back(item(m, n, n, 1.0, G + g0 * n, n, R, n, G + g0 * n, n, H, n, false));
+      r_put[k].push_back(item(m, n, 0, 0.0, H, n, H, n, H, n, G + g0 * n, n, false));
+      r_mul[k].back().on = r_put[k].back().on = T.bad + chained;
+    }
     std::vector<int64_t> off(nb + 1, 0);
     for (int i = 0; i < nb; ++i) off[i + 1] = off[i] + p.size[i];
     std::vector<int64_t> pos(off.begin(), off.end() - 1);
@@ -435,6 +583,9 @@ bool vk_chain_plan(vk_level& L) {
       vk_chain_block q{};
       q.r0 = r0;
       q.r1 = r0 + n;
+      q.W = G;
+      q.R = R;
+      q.chained = chained;
       q.s = (int32_t)p.size[i];
       q.s_prev = i > 0 ? (int32_t)p.size[i - 1] : 0;
       q.s_next = i + 1 < nb ? (int32_t)p.size[i + 1] : 0;
@@ -444,8 +595,9 @@ bool vk_chain_plan(vk_level& L) {
       q.L = i > 0 ? take(p.size[i] * p.size[i - 1]) : nullptr;
       blocks.push_back(q);
     }
+    ++chained;
   }
-  T.n_zero = used;
+  T.n_zero = used - used0;
   for (int b = 0; b < nblk; ++b) {
     if (!plans[b].ok) continue;
     const block_plan& p = plans[b];
@@ -564,10 +716,7 @@ bool vk_chain_plan(vk_level& L) {
       }
     }
   }
-  T.v = take(L.J.n_rows);
-  T.z = take(L.J.n_rows);
-  T.jz = take(L.J.n_rows);
-  if (used > cap) return false;
+  if (used > cap || r_used > cap) return false;
   // upload the tables
   size_t tused = 0;
   bool ok = true;
@@ -619,6 +768,10 @@ bool vk_chain_plan(vk_level& L) {
     T.steps.push_back(st);
   }
   T.zw = put_gemm(zw);
+  for (int k = 0; k < 2; ++k) {
+    T.r_mul[k] = put_gemm(r_mul[k]);
+    T.r_put[k] = put_gemm(r_put[k]);
+  }
   for (size_t t = 0; t < ga.size(); ++t) {
     T.ga.push_back(put_gemm(ga[t]));
     T.gb.push_back(put_gemm(gb[t]));
@@ -659,6 +812,21 @@ static hipError_t gemm_list(hipStream_t s, const vk_gemm_list& l) {
   return hipGetLastError();
 }
 
+// *flag = 0 where every chained block's inverse is within `limit`
+static hipError_t chain_check(hipStream_t s, const vk_level& L, double limit, int32_t* flag) {
+  const vk_chain& T = L.chain;
+  const int64_t nr = T.rows - T.first;
+  hipError_t e;
+  if ((e = launch_fill(s, 2 * (int64_t)T.n_chained, 0.0, reinterpret_cast<double*>(T.rs))) != hipSuccess) return e;
+  const unsigned g = (unsigned)((nr + 3) / 4);
+  chain_probe_kernel<<<g, 256, 0, s>>>(T.first, T.rows, L.J.row_ptr, L.J.col, T.jval, L.cb_e0, T.cb, T.blocks, T.w, T.wa);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  chain_error_kernel<<<g, 256, 0, s>>>(T.first, T.rows, T.cb, T.blocks, T.rmap, T.cmap, T.w, T.wa, T.rs);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  chain_judge_kernel<<<1, 256, 0, s>>>(T.n_chained, T.rs, limit, T.bad, flag);
+  return hipGetLastError();
+}
+
 hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status, int32_t* scratch, int32_t* flag) {
   const vk_chain& T = L.chain;
   hipError_t e;
@@ -675,7 +843,7 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
     V.cb_go = L.cb_go;
     return V;
   };
-  if ((e = launch_fill(s, T.n_zero, 0.0, T.buf)) != hipSuccess) return e;
+  if ((e = launch_fill(s, T.n_zero, 0.0, T.zero)) != hipSuccess) return e;
   for (size_t i = 0; i < T.dense.size();) {  // runs of adjacent dense blocks
     size_t j = i;
     int64_t len = 0;
@@ -711,16 +879,18 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
         R.d_real, R.d_rows, L.cb_q, T.rmap, T.cmap);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // the check: v - J (G v) on the chained rows
-  const int64_t nr = T.rows - T.first;
-  const unsigned g = (unsigned)std::min<int64_t>((nr + 255) / 256, 1024);
-  chain_probe_kernel<<<g, 256, 0, s>>>(T.rows, T.v);
-  if ((e = launch_fill_i32(s, 1, 0, flag)) != hipSuccess) return e;
-  if ((e = launch_block_apply(s, L, T.v, T.z)) != hipSuccess) return e;
-  vk_csr A = vk_chain_J(L);
-  A.n_rows = nr;
-  A.row_ptr += T.first;
-  if ((e = launch_spmv(s, A, L.lpr_J, 1.0, T.z, 0.0, nullptr, T.jz + T.first)) != hipSuccess) return e;
-  chain_check_kernel<<<g, 256, 0, s>>>(T.first, T.rows, T.cb, T.jz, flag);
-  return hipGetLastError();
+  return chain_check(s, L, CHECK_LIMIT, flag);
+}
+
+hipError_t launch_chain_refine(hipStream_t s, const vk_level& L, int32_t* flag) {
+  const vk_chain& T = L.chain;
+  hipError_t e;
+  chain_defect_kernel<<<(unsigned)(T.rows - T.first), 256, 0, s>>>(T.first, L.J.row_ptr, L.J.col, T.jval, L.cb_e0, T.cb, T.blocks,
+                                                                T.rmap, T.cmap, T.bad);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  for (int k = 0; k < 2; ++k) {
+    if ((e = gemm_list(s, T.r_mul[k])) != hipSuccess) return e;
+    if ((e = gemm_list(s, T.r_put[k])) != hipSuccess) return e;
+  }
+  return chain_check(s, L, REFINED_LIMIT, flag);
 }

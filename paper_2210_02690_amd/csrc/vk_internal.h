@@ -180,7 +180,9 @@ struct vk_dense_item {
 struct vk_chain_block {  // D s x s (row-major, or column-major: see d_cm), U row-major s x s_next, L row-major s x s_prev
   double *D, *U, *L;
   int64_t r0, r1;  // rows of the directly solved block it belongs to
+  double *W, *R;   // that block's inverse (in cb_a) and, for a refinement, its defect I - J G
   int32_t s, s_prev, s_next, d_cm;
+  int32_t chained;  // that block's number among the chained ones
 };
 struct vk_chain_dense {  // a densely inverted block of a level with chains
   double* w;
@@ -192,6 +194,7 @@ struct vk_gemm_item {  // C = beta base + alpha A B
   double alpha, beta;
   int32_t m, n, k, lda, ldb, ldbase, ldc;
   int32_t a_cm, b_cm, c_cm, base_cm;  // column-major (else row-major)
+  const int32_t* on;                  // where given and 0: nothing is done
 };
 struct vk_gemm_list {
   vk_gemm_item* items = nullptr;  // device
@@ -220,7 +223,9 @@ struct vk_chain {
   char* table = nullptr;
   size_t table_cap = 0;
   int64_t first = 0, rows = 0;  // the blocks' rows [first, rows)
-  int64_t n_zero = 0;           // leading doubles of buf cleared before the gather
+  double* zero = nullptr;       // n_zero doubles of buf cleared before the gather
+  int64_t n_zero = 0;
+  int n_chained = 0;
   double flops = 0.0;
   int32_t *cb = nullptr, *ri = nullptr;      // per row: chain block (-1 - b: dense block b), index in it
   int32_t *rmap = nullptr, *cmap = nullptr;  // row k of the inverse is row rmap[k] of cb_a, its column j belongs to cmap[j]
@@ -231,7 +236,10 @@ struct vk_chain {
   vk_gemm_list zw;
   std::vector<vk_gemm_list> ga, gb;
   std::vector<vk_chain_rest> rest;
-  double *v = nullptr, *z = nullptr, *jz = nullptr;
+  double *w = nullptr, *wa = nullptr;  // the check's J v and |J| v, and per chained block two maxima
+  unsigned long long* rs = nullptr;
+  int32_t* bad = nullptr;  // per chained block: the check's outcome (0: accepted)
+  vk_gemm_list r_mul[2], r_put[2];  // a refinement's products, the rows of an inverse in two halves
   bool holds() const { return active && !failed; }  // cb_a holds the chain's inverse
   double* jval = nullptr;  // the setup's values of J's rows [first, rows): what the check and a dense fallback read
 };
@@ -477,12 +485,14 @@ bool vk_bt_plan(vk_level& L);
 hipError_t launch_bt_factor(hipStream_t s, const vk_level& L, int32_t* status);
 hipError_t launch_bt_solve(hipStream_t s, const vk_level& L, const double* b, double* x);
 // chain.hip: reserved workspace (doubles; bytes of tables), plan (host, once per pattern and
-// workspace; false: every block stays with the dense inversion) and the inversion.  *flag becomes
-// nonzero if a chained block's inverse fails its check; scratch takes chain blocks' pivot failures.
+// workspace; false: every block stays with the dense inversion) and the inversion.  *flag becomes 1 if
+// a chained block's inverse fails its check, 2 if a refinement (after which it is 0, or 1 or 2 as
+// before) cannot mend it; scratch takes chain blocks' pivot failures.
 int64_t vk_chain_buffer(const vk_level& L);
 size_t vk_chain_table_bytes(const vk_level& L);
 bool vk_chain_plan(vk_level& L);
 hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status, int32_t* scratch, int32_t* flag);
+hipError_t launch_chain_refine(hipStream_t s, const vk_level& L, int32_t* flag);
 // L's J with the values that the last launch_chain_invert read (the blocks' rows only)
 vk_csr vk_chain_J(const vk_level& L);
 hipError_t launch_block_export(hipStream_t s, const vk_level& L, int32_t block, double* out);

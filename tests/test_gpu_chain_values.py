@@ -33,7 +33,8 @@ def _matrix(kind, eps=0.0, n=N, seed=7):
         v += 2.0 * np.sqrt(BAND) * (i == j)
     else:
         v *= eps
-        mate = j == np.where(i % 100 < 50, i + 50, i - 50)
+        other = np.where(i % 100 < 50, i + 50, i - 50)
+        mate = j == np.where(other < n, other, i)
         v[mate] += 1.0 + rng.random(mate.sum())
     J = sp.csr_matrix((v, (p[i], p[j])), shape=(n, n))
     J.sort_indices()
@@ -72,6 +73,17 @@ def _check(S, J):
     got = torch.empty((n, n), dtype=torch.float64, device=DEV)
     S.vk_get_coarse_inverse(got)
     assert np.abs(got.cpu().numpy() - want).max() <= bound
+
+
+def _check_known_solution(S, J):
+    """|x - v| <= 64 u max |G| |J| |v| for J x = J v, the bound a refined inverse is accepted with."""
+    n = J.shape[0]
+    v = 1.0 + np.random.default_rng(5).random(n)
+    x = torch.empty(n, dtype=torch.float64, device=DEV)
+    S.vcycle(torch.from_numpy(J @ v).to(DEV), x, 0, 0)
+    G = torch.empty((n, n), dtype=torch.float64, device=DEV)
+    S.vk_get_coarse_inverse(G)
+    assert np.abs(x.cpu().numpy() - v).max() <= 64 * U * (np.abs(G.cpu().numpy()) @ (np.abs(J) @ v)).max()
 
 
 def _chained(S):
@@ -150,4 +162,67 @@ def test_a_failed_chain_among_other_blocks():
             want = np.linalg.inv(A)
             bound = 10 * (r1 - r0) * U * np.linalg.cond(A) * np.abs(want).max()
             assert np.abs(got[r0:r1] - want @ b[r0:r1]).max() <= bound * np.abs(b[r0:r1]).sum()
+    S.close()
+
+
+@pytest.mark.parametrize("eps,chained", [(0.05, True), (1e-2, True), (1e-4, True), (1e-6, True), (1e-9, False)])
+def test_badly_conditioned_chain_blocks(eps, chained):
+    """Noise for pivots costs a chain log10(1 / eps) and more digits: one refinement gives them back (up to
+    eps = 1e-6), or the dense inverse takes its place.  Either way the result is as accurate as
+    pivoting over all rows makes it."""
+    vk = _vk()
+    S = _solver(vk, _matrix("mates", eps))
+    J = _matrix("mates", eps)
+    for seed in (7, 8):
+        _put(S, J)
+        S.vanka_setup(0.7, "additive")
+        _check(S, J)
+        _check_known_solution(S, J)
+        assert _chained(S) == chained
+        J.data = J.data * (1.0 + 0.25 * np.random.default_rng(seed).random(len(J.data)))  # others of their kind
+    S.close()
+
+
+def test_refined_blocks_of_several_sizes():
+    """A refinement beside ordinary chains and beyond 1 024 unknowns (odd sizes: uneven halves)."""
+    vk = _vk()
+    sizes = (700, 1301, 501)
+    rows = np.concatenate([[0], np.cumsum(sizes)])
+    J = sp.block_diag([_matrix("mates", 1e-3, n=sizes[0]), _matrix("mates", 1e-2, n=sizes[1], seed=9),
+                       _matrix("plain", n=sizes[2], seed=8)], format="csr")
+    S = vk.Solver([dict(J=vk.upload_csr(J, DEV), P=None, R=None, groups=[], blocks=rows)])
+    S.vk_set_workspace("f64", 5, device=DEV)
+    S.vanka_setup(0.7, "additive")
+    b = np.random.default_rng(4).standard_normal(rows[-1])
+    x = torch.empty(rows[-1], dtype=torch.float64, device=DEV)
+    S.vcycle(torch.from_numpy(b).to(DEV), x, 0, 0)
+    assert S.vk_coarse_plan(0)[1] < 2.0 * (np.diff(rows).astype(float) ** 3).sum()
+    for r0, r1 in zip(rows[:-1], rows[1:]):
+        A = J[r0:r1, r0:r1].toarray()
+        want = np.linalg.inv(A)
+        bound = 10 * (r1 - r0) * U * np.linalg.cond(A) * np.abs(want).max()
+        assert np.abs(x.cpu().numpy()[r0:r1] - want @ b[r0:r1]).max() <= bound * np.abs(b[r0:r1]).sum()
+    S.close()
+
+
+def _channel(shape, length, k, nu=1e-3, tau=0.01, seed=1):
+    from synth.assemble import assemble_jacobian
+    from synth.mesh import StructuredMesh
+    from synth.problems import inflow_state
+    m = StructuredMesh(shape, (length, 0.41), k, 2)
+    J = assemble_jacobian(m, inflow_state(m, 0.3, np.random.default_rng(seed)), nu, tau).tocsr()
+    J.sort_indices()
+    return J
+
+
+@pytest.mark.parametrize("tau", [1e-5, 1e-2, 1e2])
+def test_chain_of_flow_matrices_whatever_the_time_step(tau):
+    """Coarse channel matrices keep their chain at every condition number (1e11 at tau = 1e-5, where any
+    inverse in 64 bits leaves |b - J x| of 1e-9 and more), and solve as accurately."""
+    vk = _vk()
+    J = _channel((11, 2), 2.255, 1, tau=tau)
+    S = _solver(vk, J)
+    S.vanka_setup(0.7, "additive")
+    _check_known_solution(S, J)
+    assert _chained(S)
     S.close()
