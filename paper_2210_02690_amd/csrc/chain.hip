@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void chain_gather_kernel(int64_t first, int64_
       continue;
     }
     const int bc = cb[c], j = ri[c];
-    if (bc == b) q.D[q.d_cm ? (int64_t)j * q.s + i : (int64_t)i * q.s + j] = x;
+    if (bc == b) q.D[(int64_t)i * q.s + j] = x;
     else if (bc == b + 1) q.U[(int64_t)i * q.s_next + j] = x;
     else if (bc == b - 1) q.L[(int64_t)i * q.s_prev + j] = x;
     else atomicOr(&status[1], 2);  // the plan makes this impossible
@@ -589,7 +589,6 @@ bool vk_chain_plan(vk_level& L) {
       q.s = (int32_t)p.size[i];
       q.s_prev = i > 0 ? (int32_t)p.size[i - 1] : 0;
       q.s_next = i + 1 < nb ? (int32_t)p.size[i + 1] : 0;
-      q.d_cm = piece_width(p.size[i]) == p.size[i];
       q.D = take(p.size[i] * p.size[i]);
       q.U = i + 1 < nb ? take(p.size[i] * p.size[i + 1]) : nullptr;
       q.L = i > 0 ? take(p.size[i] * p.size[i - 1]) : nullptr;
@@ -607,9 +606,11 @@ bool vk_chain_plan(vk_level& L) {
     std::vector<int64_t> off(nb + 1, 0);
     for (int i = 0; i < nb; ++i) off[i + 1] = off[i] + p.size[i];
     std::vector<double*> inv(nb), X(nb, nullptr), Z(nb, nullptr);
+    std::vector<int32_t> cm(nb);  // the inverse is column-major
     for (int i = 0; i < nb; ++i) {
       // a block of one piece is inverted out of place, a wider one in place, piece by piece
-      inv[i] = piece_width(sz(i)) == sz(i) ? take(sz(i) * sz(i)) : blocks[f + i].D;
+      cm[i] = piece_width(sz(i)) == sz(i);
+      inv[i] = cm[i] ? take(sz(i) * sz(i)) : blocks[f + i].D;
       const int j = i < c ? i + 1 : (i > c ? i - 1 : -1);  // the next block inwards
       if (j >= 0) {
         X[i] = take(sz(i) * sz(j));  // X_i or Y_i
@@ -676,20 +677,23 @@ bool vk_chain_plan(vk_level& L) {
         const double* out = side == 0 ? blocks[f + i].U : blocks[f + i].L;  // i -> j
         const double* back = side == 0 ? blocks[f + j].L : blocks[f + j].U;  // j -> i
         S.cp.push_back(item(sz(i), sz(j), sz(i), 1.0, inv[i], sz(i), out, sz(j), nullptr, 0, X[i], sz(j), false));
+        S.cp.back().a_cm = cm[i];
         const vk_gemm_item u = item(sz(j), sz(j), sz(i), -1.0, back, sz(i), X[i], sz(j), blocks[f + j].D, sz(j),
-                                    blocks[f + j].D, sz(j), blocks[f + j].d_cm != 0);
+                                    blocks[f + j].D, sz(j), false);
         // both chains can reach the middle block in one step: its updates run one after the other
         if (j == c && !first_update) S.u2.push_back(u);
         else S.u1.push_back(u);
         if (j == c) first_update = false;
         T.flops += 2.0 * sz(i) * sz(i) * sz(j) + 2.0 * sz(j) * sz(j) * sz(i);
         zw.push_back(item(sz(j), sz(i), sz(i), 1.0, back, sz(i), inv[i], sz(i), nullptr, 0, Z[i], sz(i), false));
+        zw.back().b_cm = cm[i];
       }
     }
     // the whole inverse, outwards from the middle
     double* G = L.cb_a + woff[b];
     auto g = [&](int64_t r, int64_t q) { return G + r * n + q; };
     zw.push_back(item(sz(c), sz(c), 0, 0.0, inv[c], sz(c), inv[c], sz(c), inv[c], sz(c), g(off[c], off[c]), n, false));
+    zw.back().base_cm = cm[c];
     for (int t = 1; t < ns; ++t) {
       const int i = c - t, j = c + t;
       const int64_t a0 = off[std::max(i + 1, 0)], a1 = off[std::min(j, nb)], M = a1 - a0;
@@ -699,6 +703,7 @@ bool vk_chain_plan(vk_level& L) {
         A.push_back(item(M, sz(i), sz(i + 1), -1.0, g(a0, off[i + 1]), n, Z[i], sz(i), nullptr, 0, g(a0, off[i]), n, false));
         B.push_back(item(sz(i), sz(i), sz(i + 1), -1.0, X[i], sz(i + 1), g(off[i + 1], off[i]), n, inv[i], sz(i),
                          g(off[i], off[i]), n, false));
+        B.back().base_cm = cm[i];
         T.flops += 4.0 * sz(i) * sz(i + 1) * M;
       }
       if (j < nb) {
@@ -706,6 +711,7 @@ bool vk_chain_plan(vk_level& L) {
         A.push_back(item(M, sz(j), sz(j - 1), -1.0, g(a0, off[j - 1]), n, Z[j], sz(j), nullptr, 0, g(a0, off[j]), n, false));
         B.push_back(item(sz(j), sz(j), sz(j - 1), -1.0, X[j], sz(j - 1), g(off[j - 1], off[j]), n, inv[j], sz(j),
                          g(off[j], off[j]), n, false));
+        B.back().base_cm = cm[j];
         T.flops += 4.0 * sz(j) * sz(j - 1) * M;
       }
       if (i >= 0 && j < nb) {

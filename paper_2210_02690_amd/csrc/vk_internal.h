@@ -164,8 +164,9 @@ struct vk_bt {
 };
 
 // A dense FP64 matrix to be inverted by the register-resident matrix-core kernel (n <= VK_ITEM_MAX): a is
-// column-major with leading dimension lda (row-major), out receives the inverse row-major
-// (column-major), n x n; n <= 0: nothing.
+// row-major with leading dimension lda, out receives the inverse column-major, n x n; n <= 0: nothing.
+// (A column-major a gives the row-major inverse, but the elimination is then the transposed one, which keeps
+// J G close to I and not, as the other inversions do and solves need, G J.)
 #define VK_ITEM_MAX 176
 struct vk_dense_item {
   const double* a;
@@ -177,11 +178,11 @@ struct vk_dense_item {
 // made on the host once per pattern and workspace; buffers and tables lie in reserved workspace.
 #define VK_CHAIN_MIN_N 384     // narrower blocks are inverted densely
 #define VK_CHAIN_MIN_BLOCK 64  // consecutive level sets are grouped into chain blocks of at least this size
-struct vk_chain_block {  // D s x s (row-major, or column-major: see d_cm), U row-major s x s_next, L row-major s x s_prev
+struct vk_chain_block {  // row-major: D s x s, U s x s_next, L s x s_prev
   double *D, *U, *L;
   int64_t r0, r1;  // rows of the directly solved block it belongs to
   double *W, *R;   // that block's inverse (in cb_a) and, for a refinement, its defect I - J G
-  int32_t s, s_prev, s_next, d_cm;
+  int32_t s, s_prev, s_next;
   int32_t chained;  // that block's number among the chained ones
 };
 struct vk_chain_dense {  // a densely inverted block of a level with chains
