@@ -160,7 +160,7 @@ vk_status vk_set_workspace(vk_ctx* ctx, void* dev, size_t bytes, vk_prec prec, i
  * level l >= 1 gather J_K = J_l restricted to dof(K, .) x dof(K, .), entries
  * not stored in J_l being zero, invert it in FP64 by Gauss-Jordan elimination
  * with partial pivoting (first row of maximal |pivot|, the LU pivot sequence;
- * the matrix-core kernels count candidates within a
+ * the matrix-core kernel of the 170-wide patches counts candidates within a
  * relative 2^-13 of the largest as tied) and store A_K in `prec`; compute 1/p_mu, p_mu = number of cells containing
  * DoF mu (Eq. 3.5b); and form the FP64 inverse of J_0 for the coarsest-level
  * direct solve (vk_set_coarse_solver; blocked Gauss-Jordan with partial pivoting:
@@ -292,8 +292,9 @@ vk_status vk_set_sweep_variant(vk_ctx* ctx, int32_t variant);
  * with vector FP64 for n_K = 84, 85, 105, 120, 170, 180); 3 is 2 but for
  * n_K = 170, which takes the matrix-core kernel with its patches gathered by a
  * search of their CSR rows instead of the map.  All compute the Gauss-Jordan
- * inverse with partial pivoting (the matrix-core kernels compare pivots up to a
- * relative 2^-13, see vanka_setup); setup must run again after a change. */
+ * inverse with partial pivoting (the matrix-core kernel of n_K = 170 compares
+ * pivots up to a relative 2^-13, see vanka_setup); setup must run again after a
+ * change. */
 vk_status vk_set_setup_variant(vk_ctx* ctx, int32_t variant);
 
 /* Pivot choice of the directly solved blocks' Gauss-Jordan inversion (the

@@ -1075,6 +1075,62 @@ __device__ inline double recip_f64(double a) {
   return r;
 }
 
+// The first row of largest |x| among a wavefront's rows r * 64 + lane with um[r] all ones (0: not a candidate),
+// as row block ps and lane pl, and 1 / x there; false (inv = 0) where no candidate is nonzero or the largest
+// is not finite.  One integer wavefront maximum over the high words settles nearly every step; their low words
+// are compared only where several rows share it.
+template <int R>
+__device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t (&um)[R], int& ps, int& pl, double& inv) {
+  uint32_t key[R], lk = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    key[r] = (((uint32_t)(__builtin_bit_cast(uint64_t, x[r]) >> 32) & 0x7FFFFFFFu) + 1u) & um[r];
+    lk = max(lk, key[r]);
+  }
+  const uint32_t mk = wave_max_u32(lk);
+  unsigned long long at[R];
+  int n_at = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    at[r] = __ballot(key[r] == mk);
+    n_at += __popcll(at[r]);
+  }
+  if (n_at != 1 || mk <= 1) {  // uniform
+    uint32_t low[R], ll = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      low[r] = key[r] == mk ? (uint32_t)__builtin_bit_cast(uint64_t, x[r]) : 0u;
+      ll = max(ll, low[r]);
+    }
+    const uint32_t ml = wave_max_u32(ll);
+    if (mk == 0 || (mk == 1 && ml == 0)) {
+      ps = pl = 0;
+      inv = 0.0;
+      return false;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) at[r] = __ballot(key[r] == mk && low[r] == ml);
+  }
+  ps = 0;
+  unsigned long long m = at[0];
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    const bool next = m == 0;
+    m = next ? at[r] : m;
+    ps = next ? r : ps;
+  }
+  pl = __builtin_ctzll(m);
+  double y = x[0];
+#pragma unroll
+  for (int r = 1; r < R; ++r) y = ps == r ? x[r] : y;
+  y = readlane_f64(y, pl);
+  const uint32_t ex = (mk - 1) >> 20;
+  const bool finite = ex != 0x7FFu;
+  // the refined reciprocal where neither it nor its hardware seed leaves the normal range
+  inv = ex - 2u < 0x7FBu ? recip_f64(y) : (finite ? 1.0 / y : 0.0);
+  return finite;
+}
+
 // ---------------------------------------------------------------------------
 // Wide patches (n_K = 84, 85, 105, 120 and 170) and the small blocks of a chain inverse on the FP64 matrix
 // cores: blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
@@ -1099,11 +1155,11 @@ __device__ inline double recip_f64(double a) {
 // wavefront has one to itself; the tile wavefronts find their pivot rows in a per-row table.
 // Measured (per matrix of 512): 170 rows 0.60 -> 0.50 us, 128 rows 0.36 -> 0.27 us, 80 rows 0.12 ->
 // 0.10 us; a single one of 170 rows 143 -> 116 us.
-// Pivot choice: the largest |a| among the rows not yet pivotal, compared on a 32-bit key (|a|'s
-// exponent and 13 leading mantissa bits, then 255 - row), so one integer wavefront maximum gives
-// the row as well: candidates within a relative 2^-13 count as ties and the lowest row wins (the
-// first maximal row of the LU pivot sequence whenever the maximum is unique to that precision;
-// the multipliers stay below 1 + 2^-13 in magnitude).
+// Pivot choice: the first row of largest |a| among the rows not yet pivotal (find_pivot), but with KEYED (n_K =
+// 170) compared on a 32-bit key (|a|'s exponent and 13 leading mantissa bits, then 255 - row), so one
+// integer wavefront maximum gives the row as well: candidates within a relative 2^-13 count as ties and
+// the lowest row wins (the first maximal row of the LU pivot sequence whenever the maximum is unique
+// to that precision; the multipliers stay below 1 + 2^-13 in magnitude).
 // The FP64 MFMA (16 x 16 x 4) computes D(m, n) = sum_k A(m, k) B(k, n) + C: lane l supplies
 // A(l % 16, l / 16) and B(l / 16, l % 16), and accumulator element v holds D(4 v + l / 16, l % 16),
 // so a tile's lane l owns rows 4 v + l / 16 of column l % 16.  Tile indices are compile-time
@@ -1197,7 +1253,7 @@ __global__ __launch_bounds__(512) void patch_map_kernel(const int64_t* __restric
   for (int e = tid; e < ME / 4; e += NT) out[e] = reinterpret_cast<const uint64_t*>(sm)[e];
 }
 
-template <int P, int T, int SRC>
+template <int P, int T, int SRC, bool KEYED>
 __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_setup_mfma_kernel(
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
     const int32_t* __restrict__ cell_dofs, const uint64_t* __restrict__ pmap, int32_t n_K, void* inv_out, int32_t ld_,
@@ -1377,21 +1433,33 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
         const int k = k0 + t;
-        // 32-bit pivot keys: |a|'s exponent and 13 leading mantissa bits, then 255 - row (0 for
-        // rows already pivotal), so one integer wavefront maximum gives the row as well
-        uint32_t key = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, pr[r][t]) >> 32);
-          key = max(key, (((hi & 0x7FFFFF80u) << 1) | rid[r]) & um[r]);
-        }
-        const uint32_t mk = wave_max_u32(key);
-        const int p = 255 - (int)(mk & 0xFFu);
-        // uniform: a padding column of the last panel, no nonzero candidate, or a non-finite
+        // skip, uniform: a padding column of the last panel, no nonzero candidate, or a non-finite
         // largest one (the step is then a no-op on the other columns: its row of B stays zero)
-        const bool skip = k >= N || (mk >> 8) == 0 || (mk >> 21) == 0x7FFu || p >= N;
+        bool skip;
+        int ps, pl;
+        double inv = 0.0;
+        if constexpr (KEYED) {
+          // 32-bit pivot keys: |a|'s exponent and 13 leading mantissa bits, then 255 - row (0 for
+          // rows already pivotal), so one integer wavefront maximum gives the row as well
+          uint32_t key = 0;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, pr[r][t]) >> 32);
+            key = max(key, (((hi & 0x7FFFFF80u) << 1) | rid[r]) & um[r]);
+          }
+          const uint32_t mk = wave_max_u32(key);
+          const int p = 255 - (int)(mk & 0xFFu);
+          skip = k >= N || (mk >> 8) == 0 || (mk >> 21) == 0x7FFu || p >= N;
+          pl = p & 63;
+          ps = p >> 6;
+        } else {
+          double x[R];
+#pragma unroll
+          for (int r = 0; r < R; ++r) x[r] = pr[r][t];
+          skip = !find_pivot<R>(x, um, ps, pl, inv) || k >= N;
+        }
         if (skip && k < N) singular = true;
-        const int pl = p & 63, ps = p >> 6;
+        const int p = ps * 64 + pl;
         // the pivot row's entries: every lane selects its row of block ps (uniform), lane pl's
         // are read out
         double prow[NB];
@@ -1402,7 +1470,8 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
           for (int r = 1; r < R; ++r) x = (ps == r) ? pr[r][c] : x;
           prow[c] = readlane_f64(x, pl);
         }
-        const double inv = skip ? 0.0 : recip_f64(prow[t]);
+        if (KEYED) inv = recip_f64(prow[t]);
+        inv = skip ? 0.0 : inv;
 #pragma unroll
         for (int c = 0; c < NB; ++c) prow[c] = (c == t) ? inv : prow[c] * inv;
         // straight-line update, the next panel column first (the next step's pivot search needs
@@ -1600,8 +1669,8 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
 // above; T = 4 takes 128 registers, so two patches share a SIMD), and no step needs a barrier.  Columns
 // are eliminated in panels of four, the first four columns left in tile column 0:
 //   1. the panel's columns go through LDS to one row per lane;
-//   2. four elimination steps in registers: the same 32-bit pivot keys, the pivot row read out with
-//      readlane, the refined reciprocal; M and the pivot rows q_t result;
+//   2. four elimination steps in registers: find_pivot, the pivot row read out with readlane; M and
+//      the pivot rows q_t result;
 //   3. the pivot rows' old values go to LDS as B (identity in the panel's own columns) and are cleared,
 //      as are the panel's columns; W' = W + M B on every tile then also writes M into those columns.
 // After four panels the tile columns rotate by one, so the code has one copy of the panel.
@@ -1658,7 +1727,6 @@ __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
     fence();
   }
   uint32_t um = lane < n ? 0xFFFFFFFFu : 0u;  // all ones while the lane's row may still become a pivot
-  const uint32_t rid = 255u - (uint32_t)lane;
   int my_q = lane, my_k = lane;  // pivot row of column `lane`, column of pivot row `lane`
   bool singular = false;
 #pragma unroll 1
@@ -1687,17 +1755,17 @@ __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       const int k = k0 + t;
-      const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, pr[t]) >> 32);
-      const uint32_t mk = wave_max_u32((((hi & 0x7FFFFF80u) << 1) | rid) & um);
-      const int p = 255 - (int)(mk & 0xFFu);
+      int ps, pl;
+      double inv;
+      const double x[1] = {pr[t]};
+      const uint32_t um1[1] = {um};
       // uniform: a padding column, no nonzero candidate, or a non-finite largest one
-      const bool skip = k >= n || (mk >> 8) == 0 || (mk >> 21) == 0x7FFu;
+      const bool skip = !find_pivot<1>(x, um1, ps, pl, inv) || k >= n;
       singular = singular || (skip && k < n);
-      const int pl = p & 63;
       double prow[NB];
 #pragma unroll
       for (int c = 0; c < NB; ++c) prow[c] = readlane_f64(pr[c], pl);
-      const double inv = skip ? 0.0 : recip_f64(prow[t]);
+      inv = skip ? 0.0 : inv;
 #pragma unroll
       for (int c = 0; c < NB; ++c) prow[c] = (c == t) ? inv : prow[c] * inv;
       const bool isp = !skip && lane == pl;
@@ -1817,7 +1885,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
                                                           L.ld, L.cell_stride, status)
 #define VK_MFMA_CASE(NN)                                                                     \
   case NN:                                                                                   \
-    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP><<<L.n_cells, MfCfg<(NN + 15) / 16, true>::NT, 0, s>>>( \
+    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP, NN == 170><<<L.n_cells, MfCfg<(NN + 15) / 16, true>::NT, 0, s>>>( \
         J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);   \
     return hipGetLastError();
   if (mapped) {
@@ -1863,7 +1931,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #undef VK_WIDE_CASE
     case 170:
       if (mfma)
-        patch_setup_mfma_kernel<P, 11, SRC_SEARCH><<<L.n_cells, MfCfg<11, false>::NT, 0, s>>>(
+        patch_setup_mfma_kernel<P, 11, SRC_SEARCH, true><<<L.n_cells, MfCfg<11, false>::NT, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);
       else
         patch_setup_wide_kernel<P, 170><<<L.n_cells, 64 * WideCfg<170>::NW, 0, s>>>(
@@ -2114,7 +2182,7 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
 
 template <int T>
 static hipError_t invert_items(hipStream_t s, int n_items, const vk_dense_item* items, int32_t* status) {
-  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE><<<(unsigned)n_items, MfCfg<T, true>::NT, 0, s>>>(
+  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE, false><<<(unsigned)n_items, MfCfg<T, true>::NT, 0, s>>>(
       nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, 0, items, status);
   return hipGetLastError();
 }
