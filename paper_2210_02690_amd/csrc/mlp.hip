@@ -181,8 +181,8 @@ __global__ __launch_bounds__(512) void net_kernel(net_desc net, int32_t batch, i
 
 // All weight and bias gradients, and the loss, in one launch: blockIdx.y = layer (y = L: the loss),
 // a wavefront per 16 x 16 tile of dW_l(j, i) = sum_m dz[m, j] a[m, i], one accumulator over the samples
-// in order; the tiles of the first input columns also sum dz over the samples (db).  Both operands of
-// 16 samples are one 8-byte word per lane, 8 steps in flight (per layer and 512 samples, a product with
+// in order; the tiles of the first input columns also sum dz over the samples (db: four at a time, then in 64
+// bits, since one wavefront adds up a batch of up to 2^20).  Both operands of 16 samples are one 8-byte word per lane, 8 steps in flight (per layer and 512 samples, a product with
 // scalar 2-byte loads, one round trip per step, took 44 us and the bias sums 4.7 us).
 __global__ __launch_bounds__(64) void grad_kernel(net_desc net, int32_t batch, const uint16_t* __restrict__ ta,
                                                   const uint16_t* __restrict__ tz, const float* __restrict__ part,
@@ -206,12 +206,11 @@ __global__ __launch_bounds__(64) void grad_kernel(net_desc net, int32_t batch, c
   const bf16x4* ap = reinterpret_cast<const bf16x4*>(tz + net.tz[l]) + (jt * 16 + l16) * 4 + q;
   const bf16x4* bp = reinterpret_cast<const bf16x4*>(ta + net.ta[l]) + (it * 16 + l16) * 4 + q;
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  float db = 0.0f;
+  double db = 0.0;
   auto step = [&](bf16x4 a, bf16x4 b) {
     acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
     if (it == 0)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) db += bf2f((uint16_t)a[i]);
+      db += (double)((bf2f((uint16_t)a[0]) + bf2f((uint16_t)a[1])) + (bf2f((uint16_t)a[2]) + bf2f((uint16_t)a[3])));
   };
   int s = 0;
   for (; s + 8 <= mts; s += 8) {
@@ -239,8 +238,8 @@ __global__ __launch_bounds__(64) void grad_kernel(net_desc net, int32_t batch, c
     db += __shfl_xor(db, 32, 64);
     const int j = jt * 16 + l16;
     if (q == 0 && j < fo) {
-      grad[net.b[l] + j] = db;
-      if (grad_out) grad_out[net.b[l] + j] = db;
+      grad[net.b[l] + j] = (float)db;
+      if (grad_out) grad_out[net.b[l] + j] = (float)db;
     }
   }
 }

@@ -46,3 +46,26 @@ def test_tile_edges(n_in, width, n_hidden, n_out, batch):
     L_r, g_r = omlp.loss_and_grad(p.astype(np.float64), shapes, X[rows], T[rows].astype(np.float64), bf16_points=True)
     assert abs(float(loss.item()) - L_r) <= 5e-3 * more * L_r
     assert rel(g.cpu().numpy().astype(np.float64), g_r) <= 2e-2 * more
+
+
+@pytest.mark.parametrize("batch", [512, 4099, 1 << 20])
+def test_bias_gradients_of_large_batches(batch):
+    """The last layer's bias gradient is the sum of dz = bf16(2 (y - t) / count) over the batch.  The terms have
+    8 digits and are added exactly in pairs of pairs or in 64 bits, so its error is one rounding, 2^-24, plus
+    what pairs more than 2^16 apart lose, another 2^-24 at most."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2210_02690_amd as vk
+    print(f"mlp bias gradient, batch {batch}", flush=True)
+    net = vk.MLP(4, 16, 1, 3, batch, device=DEV)
+    net.set_params(torch.from_numpy(init_mlp_params(4, 16, 1, 3, seed=3)).to(DEV))
+    g = torch.Generator(device=DEV).manual_seed(batch)
+    x = torch.randn((batch, 4), device=DEV, generator=g).to(torch.bfloat16)
+    target = 4.0 + torch.rand((batch, 3), device=DEV, generator=g)
+    y = net.forward(x)
+    _, grad = net.gradient(x, target)
+    scale = torch.tensor(2.0, device=DEV) / (torch.tensor(float(batch), device=DEV) * 3.0)
+    dz = (scale * (y - target)).to(torch.bfloat16).double()
+    want = dz.sum(dim=0)
+    assert ((grad[-3:].double() - want).abs() <= 2.0 ** -23 * dz.abs().sum(dim=0)).all()
+    net.close()
