@@ -516,6 +516,8 @@ vk_status vk_mlp_create(vk_mlp** out, int32_t n_in, int32_t width, int32_t n_hid
     const int32_t wide = 16 * (int32_t)(ti > to ? ti : to);
     if (wide > c->wide) c->wide = wide;
   }
+  // (together the two also hold a batch of outputs, see vk_mlp_forward)
+  c->n_tz = std::max(c->n_tz, mts * 16 * 2 * (int64_t)n_out - c->n_ta);
   c->P = off;
   *out = c;
   return VK_OK;
@@ -581,7 +583,21 @@ vk_status vk_mlp_forward(vk_mlp* c, int32_t batch, const uint16_t* x, const int3
   if (batch < 0 || batch > c->max_batch) return mfail(c, VK_ERR_ARG, "batch exceeds max_batch");
   if (batch == 0) return VK_OK;
   if (!x || !y) return mfail(c, VK_ERR_ARG, "null input or output");
-  MLP_TRY(run_net(c, batch, x, rows, y, nullptr, 0.0f));
+  // Workgroups write their samples' y while others still read x and rows: an output that may share memory
+  // with them (with rows, x reaches to no known end) goes through the batch arrays.
+  const char *yb = reinterpret_cast<const char*>(y), *ye = reinterpret_cast<const char*>(y + (int64_t)batch * c->n_out);
+  auto apart = [&](const void* first, const void* last) {
+    return ye <= static_cast<const char*>(first) || (last && yb >= static_cast<const char*>(last));
+  };
+  if (apart(x, rows ? nullptr : x + (int64_t)batch * c->n_in) && (!rows || apart(rows, rows + batch))) {
+    MLP_TRY(run_net(c, batch, x, rows, y, nullptr, 0.0f));
+    return VK_OK;
+  }
+  float* staged = reinterpret_cast<float*>(c->ta);
+  MLP_TRY(run_net(c, batch, x, rows, staged, nullptr, 0.0f));
+  const int64_t n = (int64_t)batch * c->n_out;
+  copy_f32_kernel<<<grid_for(n, 256), 256, 0, c->stream>>>(n, staged, y);
+  MLP_LAUNCHED("copy_f32_kernel");
   return VK_OK;
 }
 

@@ -69,3 +69,29 @@ def test_bias_gradients_of_large_batches(batch):
     want = dz.sum(dim=0)
     assert ((grad[-3:].double() - want).abs() <= 2.0 ** -23 * dz.abs().sum(dim=0)).all()
     net.close()
+
+
+@pytest.mark.parametrize("n_in,n_out,batch", [(32, 42, 4096), (84, 42, 5000), (200, 3, 3000), (1, 300, 1000)])
+@pytest.mark.parametrize("indexed", [False, True])
+def test_outputs_that_share_memory_with_the_inputs(n_in, n_out, batch, indexed):
+    """y over x, over its end, and just behind and before it: the same bits as with an output of its own."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2210_02690_amd as vk
+    print(f"mlp {n_in} -> {n_out}, batch {batch}, indexed {indexed}", flush=True)
+    net = vk.MLP(n_in, 16, 1, n_out, batch, device=DEV)
+    net.set_params(torch.from_numpy(init_mlp_params(n_in, 16, 1, n_out, seed=3)).to(DEV))
+    g = torch.Generator(device=DEV).manual_seed(batch)
+    xs = torch.randn((batch, n_in), device=DEV, generator=g).to(torch.bfloat16)
+    rows = torch.randperm(batch, device=DEV, generator=g).to(torch.int32) if indexed else None
+    want = net.forward(xs, rows=rows)
+    nx, ny = 2 * xs.numel(), 4 * want.numel()
+    pad = (ny + 255) // 256 * 256
+    for off in (0, nx // 2 // 4 * 4, (nx + 3) // 4 * 4, -(ny // 2 // 4 * 4), -ny):  # of y, from the start of x
+        buf = torch.zeros(2 * pad + nx + 256, dtype=torch.uint8, device=DEV)
+        x = buf[pad:pad + nx].view(torch.bfloat16).reshape(batch, n_in)
+        x.copy_(xs)
+        y = buf[pad + off:pad + off + ny].view(torch.float32).reshape(batch, n_out)
+        net.forward(x, rows=rows, out=y)
+        assert torch.equal(y, want), off
+    net.close()
