@@ -452,9 +452,10 @@ hipError_t run_net(vk_mlp* c, int32_t batch, const uint16_t* x, const int32_t* r
   const unsigned nt = c->wide > 64 ? 512 : 256;
   const int32_t ldk = c->wide + 4;  // rows 8 bytes apart modulo 32: the lanes' 8-byte reads spread over the banks
   const size_t lds = (size_t)2 * 16 * ldk * sizeof(uint16_t);
-  if (lds > 65000) {  // layers about 1 000 wide: beyond what a launch may take unasked
+  if (lds > 65000) {  // layers about 1 000 wide: beyond what a launch may take unasked (the same limit from every thread)
+    constexpr int limit = 2 * 16 * (1024 + 4) * (int)sizeof(uint16_t);
     const void* f = target ? reinterpret_cast<const void*>(net_kernel<true>) : reinterpret_cast<const void*>(net_kernel<false>);
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, limit);
     if (e != hipSuccess) return e;
   }
   if (target)

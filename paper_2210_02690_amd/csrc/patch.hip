@@ -2210,9 +2210,10 @@ int64_t vk_patch_map_elems(int32_t n_K) { return (int64_t)mfma_tiles(n_K) * mfma
 hipError_t launch_patch_map(hipStream_t s, const vk_csr& J, const vk_group& G, int32_t* too_long) {
   if (!G.pmap || G.n_cells == 0 || mfma_tiles(G.n_K) == 0) return hipSuccess;
   const size_t lds = patch_map_lds(G.n_K, mfma_tiles(G.n_K));
-  if (lds > 57000) {  // with the hash table beyond 64 KB, which a launch may not take unasked
+  if (lds > 57000) {  // with the hash table beyond 64 KB, which a launch may not take unasked (the same limit from
+                      // every thread)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(patch_map_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)patch_map_lds(176, 11));
     if (e != hipSuccess) return e;
   }
   patch_map_kernel<<<G.n_cells, G.n_K <= 64 ? 256 : 512, lds, s>>>(J.row_ptr, J.col, G.cell_dofs, G.n_K,
