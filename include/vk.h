@@ -365,9 +365,9 @@ int32_t vk_coarse_plan(vk_ctx* ctx, int32_t level, double* setup_flops);
 /* Autotuner: after vanka_setup, times each level's SpMV kernels (J, P, R)
  * with 4, 8, 16, 32 and 64 lanes per row (also 1 and 2 for matrices with
  * fewer than 16 entries per row on average, such as the transfers P) and the patch GEMV with 1, 2, 4 and
- * 8 cells per workgroup, or, on levels of few cells, one cell on 512 or 1024 threads
- * (`reps` launches each, HIP events) and keeps the
- * fastest for the context; on levels with one cell group the tiles of whole cells are
+ * 8 cells per workgroup, with the tile it has untuned, and, on levels of few cells, with one
+ * cell on 512 or 1024 threads (`reps` launches each, HIP events) and keeps the
+ * fastest for the context; on levels with one cell group all but the last two are
  * then timed again inside V-cycles from the finest level (three rounds of
  * `reps` V-cycles per tile, every launch timed), which decides.  Results change only in floating-point summation
  * order.  Overwrites the level scratch vectors and clears the timing

@@ -1546,12 +1546,15 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
   };
   const int lprs[7] = {1, 2, 4, 8, 16, 32, 64};
   // GEMV tiles: cells per 256-thread workgroup, or one cell on 512 or 1 024 threads where the cells are
-  // few (beyond the default rule's line they only lose)
-  constexpr int kTiles = 6, kCycled = 4;  // the first kCycled are timed again inside V-cycles
-  const int tiles[kTiles] = {1, 2, 4, 8, -512, -1024};
+  // few
+  // (beyond the default rule's line they only lose), and the rule's own choice for the group
+  constexpr int kCycled = 5;  // the whole-cell tiles and the rule's choice are timed again inside V-cycles
+  auto tiles = [&](const vk_group& G) {
+    return std::vector<int>{1, 2, 4, 8, vk_gemv_tile(G.n_cells, G.n_K, G.ld, ctx->prec), -512, -1024};
+  };
   auto tile_ok = [&](const vk_group& G, int t) {
     if (t < 0) return (int64_t)G.n_cells * -t <= (1 << 20) && -t >= G.ld / vk_prec_vw(ctx->prec);
-    return VK_NT / t >= G.ld / vk_prec_vw(ctx->prec);
+    return t > 0 && VK_NT / t >= G.ld / vk_prec_vw(ctx->prec);
   };
   for (int l = 0; l < ctx->n_levels; ++l) {
     vk_level& L = ctx->lv[l];
@@ -1589,7 +1592,7 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     for (vk_group& G : L.groups) {
       int best = 0;
       float tb = 1e30f;
-      for (int cpb : tiles) {
+      for (int cpb : tiles(G)) {
         if (!tile_ok(G, cpb)) continue;
         const float t = time_ms([&] { return launch_patch_gemv(s, G, ctx->prec, L.b, ctx->Y, cpb); });
         if (t < tb) { tb = t; best = cpb; }
@@ -1604,7 +1607,8 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
   // the last-level cache still holds (176x32 dG(2): 4 and 8 cells per workgroup time alike back
   // to back, 16.8 and 18.5 us inside the solve).  Levels with one cell group; the candidates
   // alternate over three rounds of `reps` V-cycles, every GEMV launch timed by its own events.  A level
-  // whose pick is one cell on 512 or 1 024 threads keeps it (few cells: nothing streams there).
+  // whose pick is one cell on 512 or 1 024 threads keeps it (few cells: nothing streams there).  The rule's
+  // choice is a candidate of its own where it is one cell on fewer threads.
   const int Lf = ctx->n_levels - 1;
   bool single = false;
   for (int l = 1; l <= Lf; ++l) single = single || ctx->lv[l].groups.size() == 1;
@@ -1613,6 +1617,7 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
     const int32_t t_level = ctx->timing_level, t_every = ctx->timing_every;
     const uint32_t t_kinds = ctx->timing_kinds;
     int32_t first[32] = {0};
+    std::vector<int> cand[32];
     bool valid[32][kCycled] = {};
     double tot[32][kCycled] = {};
     int64_t cnt[32][kCycled] = {};
@@ -1620,16 +1625,21 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
       if (ctx->lv[l].groups.size() == 1) {
         const vk_group& G = ctx->lv[l].groups[0];
         first[l] = G.cpb_tuned;
-        for (int c = 0; c < kCycled; ++c) valid[l][c] = G.cpb_tuned > 0 && tile_ok(G, tiles[c]);
+        cand[l] = tiles(G);
+        for (int c = 0; c < kCycled; ++c)
+          valid[l][c] = G.cpb_tuned > -512 && tile_ok(G, cand[l][c]) && (c < 4 || (cand[l][c] < 0 && cand[l][c] > -512));
       }
     vk_level& F = ctx->lv[Lf];
     VK_TRY(launch_fill(s, F.J.n_rows, 1.0, F.b));
     vk_status st = ctx->coarse_pending ? coarse_wait(ctx, true) : VK_OK;
     for (int round = 0; round < 3 && st == VK_OK; ++round)
       for (int c = 0; c < kCycled && st == VK_OK; ++c) {
+        bool some = false;
+        for (int l = 1; l <= Lf; ++l) some = some || valid[l][c];
+        if (!some) continue;
         for (int l = 1; l <= Lf; ++l)
           if (ctx->lv[l].groups.size() == 1)
-            ctx->lv[l].groups[0].cpb_tuned = valid[l][c] ? tiles[c] : first[l];
+            ctx->lv[l].groups[0].cpb_tuned = valid[l][c] ? cand[l][c] : first[l];
         if ((st = vk_timing_kinds(ctx, 1u << VK_KERNEL_PATCH_GEMV, 1)) != VK_OK) break;
         if ((st = vk_timing_enable(ctx, 1, -1)) != VK_OK) break;
         for (int r = 0; r < reps && st == VK_OK; ++r) st = vcycle_level(ctx, Lf, F.b, F.d, 2, 2);
@@ -1648,7 +1658,7 @@ vk_status vk_autotune(vk_ctx* ctx, int32_t reps) {
       for (int c = 0; c < kCycled; ++c)
         if (valid[l][c] && cnt[l][c] > 0 && (best < 0 || tot[l][c] / cnt[l][c] < tot[l][best] / cnt[l][best]))
           best = c;
-      ctx->lv[l].groups[0].cpb_tuned = (st == VK_OK && best >= 0) ? tiles[best] : first[l];
+      ctx->lv[l].groups[0].cpb_tuned = (st == VK_OK && best >= 0) ? cand[l][best] : first[l];
     }
     ctx->timing = t_on;
     ctx->timing_level = t_level;
