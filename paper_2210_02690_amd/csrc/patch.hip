@@ -1077,14 +1077,15 @@ __device__ inline double recip_f64(double a) {
 
 // The first row of largest |x| among a wavefront's rows r * 64 + lane with um[r] all ones (0: not a candidate),
 // as row block ps and lane pl, and 1 / x there; false (inv = 0) where no candidate is nonzero or the largest
-// is not finite.  One integer wavefront maximum over the high words settles nearly every step; their low words
-// are compared only where several rows share it.
+// is not finite.  One integer wavefront maximum over the high words settles nearly every step; what it leaves
+// open takes the branch: rows that share the largest high word (their low words are compared), pivots at
+// the ends of the range (divided by instead of the refined reciprocal), zeros and what is not finite.
 template <int R>
 __device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t (&um)[R], int& ps, int& pl, double& inv) {
   uint32_t key[R], lk = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    key[r] = (((uint32_t)(__builtin_bit_cast(uint64_t, x[r]) >> 32) & 0x7FFFFFFFu) + 1u) & um[r];
+    key[r] = (uint32_t)(__builtin_bit_cast(uint64_t, x[r]) >> 32) & um[r] & 0x7FFFFFFFu;
     lk = max(lk, key[r]);
   }
   const uint32_t mk = wave_max_u32(lk);
@@ -1095,40 +1096,40 @@ __device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t 
     at[r] = __ballot(key[r] == mk);
     n_at += __popcll(at[r]);
   }
-  if (n_at != 1 || mk <= 1) {  // uniform
-    uint32_t low[R], ll = 0;
+  auto choose = [&] {
+    unsigned long long m = at[0];
+    ps = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      low[r] = key[r] == mk ? (uint32_t)__builtin_bit_cast(uint64_t, x[r]) : 0u;
-      ll = max(ll, low[r]);
+    for (int r = 1; r < R; ++r) {
+      const bool next = m == 0;
+      m = next ? at[r] : m;
+      ps = next ? r : ps;
     }
-    const uint32_t ml = wave_max_u32(ll);
-    if (mk == 0 || (mk == 1 && ml == 0)) {
-      ps = pl = 0;
-      inv = 0.0;
-      return false;
-    }
+    pl = __builtin_ctzll(m);
+    double y = x[0];
 #pragma unroll
-    for (int r = 0; r < R; ++r) at[r] = __ballot(key[r] == mk && low[r] == ml);
+    for (int r = 1; r < R; ++r) y = ps == r ? x[r] : y;
+    return readlane_f64(y, pl);
+  };
+  // mk's exponent leaves the reciprocal, and its seed, in the normal range
+  if (__builtin_expect(n_at == 1 && (mk >> 20) - 2u < 0x7FBu, 1)) {  // uniform
+    inv = recip_f64(choose());
+    return true;
   }
-  ps = 0;
-  unsigned long long m = at[0];
+  uint32_t low[R], ll = 0;
 #pragma unroll
-  for (int r = 1; r < R; ++r) {
-    const bool next = m == 0;
-    m = next ? at[r] : m;
-    ps = next ? r : ps;
+  for (int r = 0; r < R; ++r) {
+    low[r] = key[r] == mk ? (uint32_t)__builtin_bit_cast(uint64_t, x[r]) & um[r] : 0u;
+    ll = max(ll, low[r]);
   }
-  pl = __builtin_ctzll(m);
-  double y = x[0];
+  const uint32_t ml = wave_max_u32(ll);
+  ps = pl = 0;
+  inv = 0.0;
+  if ((mk | ml) == 0 || (mk >> 20) == 0x7FFu) return false;
 #pragma unroll
-  for (int r = 1; r < R; ++r) y = ps == r ? x[r] : y;
-  y = readlane_f64(y, pl);
-  const uint32_t ex = (mk - 1) >> 20;
-  const bool finite = ex != 0x7FFu;
-  // the refined reciprocal where neither it nor its hardware seed leaves the normal range
-  inv = ex - 2u < 0x7FBu ? recip_f64(y) : (finite ? 1.0 / y : 0.0);
-  return finite;
+  for (int r = 0; r < R; ++r) at[r] = __ballot(um[r] != 0 && key[r] == mk && low[r] == ml);
+  inv = 1.0 / choose();
+  return true;
 }
 
 // ---------------------------------------------------------------------------
