@@ -279,17 +279,17 @@ vk_status vk_set_sweep_variant(vk_ctx* ctx, int32_t variant);
 /* Patch inversion kernel used by vanka_setup: 0 (default) keeps the patch
  * matrix in registers where a kernel for the patch width is compiled: blocked
  * Gauss-Jordan on the FP64 matrix cores (16 x 16 tiles, rank-4 panel updates),
- * one wavefront per patch for n_K <= 64, a workgroup for n_K = 84, 85, 105, 120
- * and 170, the patches gathered through a patch entry map (per cell and patch
+ * one wavefront per patch for n_K <= 64, a workgroup for n_K <= 176, the patches gathered through a patch entry map (per cell and patch
  * entry the entry's offset in its CSR row, 2 bytes each, kept in the workspace
  * and built at the first vanka_setup after vk_set_level or vk_set_workspace; a
  * level with a patch row of more than 65535 entries has none and takes the
  * kernels of variant 3); spread over a 512-thread workgroup with vector FP64
- * for n_K = 180; inverts other patches wider than 88 (up to 512) with the
- * blocked kernels of the directly solved blocks, one block per cell, and the
- * rest in LDS; 1 always uses the LDS / global-memory kernel; 2 is 0 without the
- * matrix-core kernels (one row per lane for n_K = 42, 63, the workgroup kernel
- * with vector FP64 for n_K = 84, 85, 105, 120, 170, 180); 3 is 2 but for
+ * for n_K = 180; inverts other patches (up to 512) with the blocked kernels of
+ * the directly solved blocks, one block per cell; 1 always uses the LDS /
+ * global-memory kernel; 2 is 0 without the matrix-core kernels (one row per lane
+ * for n_K = 42, 63, the workgroup kernel with vector FP64 for n_K = 84, 85, 105,
+ * 120, 170, 180, the blocked kernels for the others beyond 88, the rest in LDS);
+ * 3 is 2 but for
  * n_K = 170, which takes the matrix-core kernel with its patches gathered by a
  * search of their CSR rows instead of the map.  All compute the Gauss-Jordan
  * inverse with partial pivoting (the matrix-core kernel of n_K = 170 compares

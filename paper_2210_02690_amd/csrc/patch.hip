@@ -1133,8 +1133,7 @@ __device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t 
 }
 
 // ---------------------------------------------------------------------------
-// Wide patches (n_K = 84, 85, 105, 120 and 170) and the small blocks of a chain inverse on the FP64 matrix
-// cores: blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
+// Patches of 65 to 176 rows and the small blocks of a chain inverse on the FP64 matrix cores: blocked Gauss-Jordan with implicit partial pivoting.  The patch, padded to NP = 16 T, lives in
 // registers as T x T tiles of 16 x 16: tile-row wavefront w (of T) holds tile row w, and one more
 // wavefront, which holds no tiles, eliminates the panels.  Columns are eliminated in panels of
 // NB = 4; with panel j factored (its eliminated columns M and pivot rows q_t in LDS):
@@ -1866,14 +1865,12 @@ __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
   }
 }
 
-// Tiles per dimension of the matrix-core kernels for patches n wide, 0 where none is compiled: any width
-// up to 64 on one wavefront (T = 4 is the widest whose tiles leave room for a second patch per SIMD),
-// the widths of the repository's 3D, dG(3), dG(4) and Q4 patches up to 176 on a workgroup (12 tile rows
-// and their panels do not fit a workgroup's registers).  Against the vector kernels: 28 288 patches 85
-// wide 8.8 -> 2.9 ms, 1 408 patches 120 wide (FP64 storage) 956 -> 454 us.
-inline int mfma_tiles(int n) {
-  return n <= 64 || n == 84 || n == 85 || n == 105 || n == 120 || n == 170 ? (n + 15) / 16 : 0;
-}
+// Tiles per dimension of the matrix-core kernels for patches n wide: up to 64 on one wavefront (T = 4 is the
+// widest whose tiles leave room for a second patch per SIMD), up to 176 on a workgroup; 0 beyond (12 tile
+// rows and their panels do not fit a workgroup's registers).  768 patches, the kernels that take a width
+// otherwise -> these: 84 wide 1.08 (LDS), 0.29 (vector) -> 0.14 ms, 126, 147 and 168 wide 1.31, 1.79 and 2.13
+// (blocked) -> 0.35, 0.52 and 0.60 ms.
+inline int mfma_tiles(int n) { return n <= 176 ? (n + 15) / 16 : 0; }
 
 template <int P>
 hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t* status, bool* handled,
@@ -1884,11 +1881,9 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #define VK_WAVE_CASE(TT)                                                                                   \
   patch_setup_wave_kernel<P, TT><<<L.n_cells, 64, 0, s>>>(J.row_ptr, J.val, L.cell_dofs, pm, L.n_K, L.inv, \
                                                           L.ld, L.cell_stride, status)
-#define VK_MFMA_CASE(NN)                                                                     \
-  case NN:                                                                                   \
-    patch_setup_mfma_kernel<P, (NN + 15) / 16, SRC_MAP, NN == 170><<<L.n_cells, MfCfg<(NN + 15) / 16, true>::NT, 0, s>>>( \
-        J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);   \
-    return hipGetLastError();
+#define VK_MFMA_CASE(TT, KEYED)                                                                         \
+  patch_setup_mfma_kernel<P, TT, SRC_MAP, KEYED><<<L.n_cells, MfCfg<TT, true>::NT, 0, s>>>(             \
+      J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status)
   if (mapped) {
     if (L.n_K <= 64) {
       switch ((L.n_K + 15) / 16) {
@@ -1899,12 +1894,17 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
       }
       return hipGetLastError();
     }
-    switch (L.n_K) {
-      case 84:
-      VK_MFMA_CASE(85)
-      VK_MFMA_CASE(105)
-      VK_MFMA_CASE(120)
-      VK_MFMA_CASE(170)
+    switch (mfma_tiles(L.n_K)) {
+      case 5: VK_MFMA_CASE(5, false); return hipGetLastError();
+      case 6: VK_MFMA_CASE(6, false); return hipGetLastError();
+      case 7: VK_MFMA_CASE(7, false); return hipGetLastError();
+      case 8: VK_MFMA_CASE(8, false); return hipGetLastError();
+      case 9: VK_MFMA_CASE(9, false); return hipGetLastError();
+      case 10: VK_MFMA_CASE(10, false); return hipGetLastError();
+      case 11:
+        if (L.n_K == 170) VK_MFMA_CASE(11, true);
+        else VK_MFMA_CASE(11, false);
+        return hipGetLastError();
       default: break;
     }
   }

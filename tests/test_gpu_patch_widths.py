@@ -78,3 +78,27 @@ def test_blocked_patch_inverses(n_K):
         err = np.abs(out.cpu().numpy() - want).max(axis=(1, 2)) / np.abs(want).max(axis=(1, 2))
         assert (err <= tol + unit).all(), (prec, err.max())
     S.close()
+
+
+# one and the last width of every tile count of the workgroup's matrix-core kernel, 177 the first beyond it
+@pytest.mark.parametrize("n_K", [65, 80, 81, 96, 97, 112, 113, 126, 128, 129, 144, 145, 160, 161, 169, 171, 176, 177])
+def test_workgroup_patch_inverses(n_K):
+    """Growth of partial pivoting ~ n^(2/3) <= 32: twice the narrow patches', 2e3 eps cond."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2210_02690_amd as vk
+    print(f"patch width {n_K}", flush=True)
+    cells = 5
+    levels, blocks = _levels(vk, n_K, cells)
+    want = np.linalg.inv(blocks)
+    tol = 2e3 * np.finfo(float).eps * np.array([np.linalg.cond(b) for b in blocks])
+    S = vk.Solver(levels)
+    for prec, unit in (("f64", 0.0), ("f32", 2.0 ** -24), ("bf16", 2.0 ** -8)):
+        S.vk_set_workspace(prec, 5, device=DEV)
+        for rep in range(2):
+            S.vanka_setup(0.7)
+            out = torch.empty((cells, n_K, n_K), dtype=torch.float64, device=DEV)
+            S.vk_get_patch_inverses(1, 0, cells, out)
+            err = np.abs(out.cpu().numpy() - want).max(axis=(1, 2)) / np.abs(want).max(axis=(1, 2))
+            assert (err <= tol + unit).all(), (prec, err.max())
+    S.close()
