@@ -8,12 +8,13 @@
 // wavefront (its pairs of 64 lanes then take a row in one or two passes; 48 x 8 x 8 boxes, 32 -> 64
 // lanes: 124 entries a row 36.6 -> 26.9 us, 273 a row 200 -> 173 us; 48 x 16 x 16, 230 a row: a sweep's
 // product 0.41 -> 0.33 ms).  Below 64 a matrix beyond the 256 MB cache takes 8 lanes, whose pairs of entries
-// (pair_dot2) keep more loads in flight (64 systems of 58 entries a row, 1.8 GB: 16 lanes 458 us, 8 413);
-// a cached one of 56 a row is faster with 16 (176 x 32 k = 2: 26.5 us, 8 lanes 27.9).
+// (pair_dot2) keep more loads in flight; a cached one is faster with 16.  16 -> 8 lanes at 55 to 58 entries
+// a row, k = 2 meshes: 0.12 GB 26.8 -> 27.7 us, 0.24 GB 47.8 -> 48.2, 0.43 GB 114.4 -> 111.5, 0.70 GB 189 -> 184,
+// 1.0 GB 270 -> 264, 1.7 GB 453 -> 433; 10, 24 and 64 systems (0.29, 0.58 and 1.7 GB) 67.5 -> 63, 164.6 -> 148, 449 -> 406.
 int vk_pick_lpr_g(int64_t nnz, int64_t n_rows) {
   const double avg = n_rows > 0 ? (double)nnz / (double)n_rows : 0.0;
   if (avg >= 96) return 64;
-  if (avg >= (nnz * 12 > (1ll << 30) ? 64 : 48)) return 16;
+  if (avg >= (nnz * 12 > (1ll << 28) ? 64 : 48)) return 16;
   if (avg >= 16) return 8;
   return 4;
 }
