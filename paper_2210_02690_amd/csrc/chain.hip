@@ -813,9 +813,13 @@ vk_csr vk_chain_J(const vk_level& L) {
 }
 
 static hipError_t gemm_list(hipStream_t s, const vk_gemm_list& l) {
-  if (l.count == 0) return hipSuccess;
-  chain_gemm_kernel<<<dim3((unsigned)l.tiles, (unsigned)l.count), 256, 0, s>>>(l.items);
-  return hipGetLastError();
+  constexpr int per_launch = 32768;  // a grid's y goes to 65 536; thousands of blocks have more products a step
+  for (int i = 0; i < l.count; i += per_launch) {
+    chain_gemm_kernel<<<dim3((unsigned)l.tiles, (unsigned)std::min(per_launch, l.count - i)), 256, 0, s>>>(l.items + i);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // *flag = 0 where every chained block's inverse is within `limit`
