@@ -283,87 +283,6 @@ __global__ __launch_bounds__(256) void chain_defect_kernel(int64_t first, const 
   }
 }
 
-// breadth-first levels from `start`; the number reached, and the lowest vertex of the last level
-int64_t bfs(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, int32_t start,
-            std::vector<int32_t>& level, int32_t* last) {
-  level.assign(n, -1);
-  std::vector<int32_t> frontier{start}, next;
-  level[start] = 0;
-  int64_t seen = 1;
-  for (int l = 1; !frontier.empty(); ++l) {
-    next.clear();
-    for (int32_t v : frontier)
-      for (int64_t e = ap[v]; e < ap[v + 1]; ++e)
-        if (level[aj[e]] < 0) {
-          level[aj[e]] = l;
-          next.push_back(aj[e]);
-        }
-    if (next.empty()) *last = *std::min_element(frontier.begin(), frontier.end());
-    seen += (int64_t)next.size();
-    frontier.swap(next);
-  }
-  return seen;
-}
-
-// The chain order of one block from its symmetric adjacency: chain block of every vertex (numbered along
-// the chain) and the middle block c; false if the block has no such structure.  The construction and
-// its reasons are those of vk_bt_plan in coarse_bt.hip, with smaller blocks.
-bool chain_order(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, std::vector<int32_t>& blk,
-                 std::vector<int64_t>& size, int* c) {
-  std::vector<int32_t> d1, d2;
-  int32_t s1 = 0, s2 = 0, tmp = 0;
-  if (bfs(n, ap, aj, 0, d1, &s1) != n || bfs(n, ap, aj, s1, d1, &s2) != n || bfs(n, ap, aj, s2, d2, &tmp) != n)
-    return false;
-  const int dist = d1[s2];
-  int h1 = dist / 2, h2 = dist - h1;
-  if (h1 < 1 || h2 < 1) return false;
-  // the middle block takes level sets of both sides until it has the size of the others
-  std::vector<int64_t> lcnt, rcnt;
-  int64_t nmid = 0;
-  for (;;) {
-    lcnt.assign(h1, 0);
-    rcnt.assign(h2, 0);
-    nmid = 0;
-    for (int64_t v = 0; v < n; ++v) {
-      if (d1[v] < h1) ++lcnt[d1[v]];
-      else if (d2[v] < h2) ++rcnt[d2[v]];
-      else ++nmid;
-    }
-    if (nmid >= VK_CHAIN_MIN_BLOCK || h1 + h2 <= 2) break;
-    if (h2 >= h1) --h2;
-    else --h1;
-  }
-  if (nmid == 0) return false;
-  auto group = [](const std::vector<int64_t>& cnt, std::vector<int32_t>& lb, std::vector<int64_t>& bs) {
-    lb.assign(cnt.size(), 0);
-    for (size_t l = 0; l < cnt.size(); ++l) {
-      if (bs.empty() || bs.back() >= VK_CHAIN_MIN_BLOCK) bs.push_back(0);
-      lb[l] = (int32_t)bs.size() - 1;
-      bs.back() += cnt[l];
-    }
-    if (bs.size() > 1 && bs.back() < VK_CHAIN_MIN_BLOCK) {
-      const int64_t tail = bs.back();
-      bs.pop_back();
-      bs.back() += tail;
-      for (int32_t& b : lb) b = std::min(b, (int32_t)bs.size() - 1);
-    }
-  };
-  std::vector<int32_t> lb, rb;
-  std::vector<int64_t> ls, rs;
-  group(lcnt, lb, ls);
-  group(rcnt, rb, rs);
-  const int nl = (int)ls.size(), nb = nl + 1 + (int)rs.size();
-  size.assign(nb, 0);
-  for (int i = 0; i < nl; ++i) size[i] = ls[i];
-  size[nl] = nmid;
-  for (size_t i = 0; i < rs.size(); ++i) size[nb - 1 - i] = rs[i];
-  blk.resize(n);
-  for (int64_t v = 0; v < n; ++v)
-    blk[v] = d1[v] < h1 ? lb[d1[v]] : (d2[v] < h2 ? nb - 1 - rb[d2[v]] : nl);
-  *c = nl;
-  return true;
-}
-
 // pieces of the elimination of an s-row chain block: as few as the register-resident kernel takes, of equal
 // width rounded up to whole 16-row tiles
 int64_t piece_width(int64_t s) {
@@ -486,34 +405,8 @@ bool vk_chain_plan(vk_level& L) {
     woff[b] = w0;
     w0 += n * n;
     if (n < VK_CHAIN_MIN_N) continue;
-    std::vector<int64_t> ap(n + 1, 0);
-    bool inside = true;
-    for (int64_t r = 0; r < n && inside; ++r)
-      for (int64_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
-        const int64_t c = (int64_t)cj[e] - r0;
-        if (c < 0 || c >= n) {
-          inside = false;  // a coupling outside the block: the dense path reports it
-          break;
-        }
-        if (c != r) {
-          ++ap[r + 1];
-          ++ap[c + 1];
-        }
-      }
-    if (!inside) continue;
-    for (int64_t r = 0; r < n; ++r) ap[r + 1] += ap[r];
-    std::vector<int32_t> aj(ap[n]);
-    std::vector<int64_t> at(ap.begin(), ap.end() - 1);
-    for (int64_t r = 0; r < n; ++r)
-      for (int64_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
-        const int64_t c = (int64_t)cj[e] - r0;
-        if (c != r) {
-          aj[at[r]++] = (int32_t)c;
-          aj[at[c]++] = (int32_t)r;
-        }
-      }
     block_plan& p = plans[b];
-    if (!chain_order(n, ap, aj, p.blk, p.size, &p.c)) continue;
+    if (!vk_level_order(r0, n, &rp[r0], cj.data() + rp[r0], VK_CHAIN_MIN_BLOCK, VK_CHAIN_MIN_BLOCK, p.blk, p.size, &p.c)) continue;
     const int nb = (int)p.size.size();
     if (*std::max_element(p.size.begin(), p.size.end()) > 2048 || *std::min_element(p.size.begin(), p.size.end()) < 16)
       continue;

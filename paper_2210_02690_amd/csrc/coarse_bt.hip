@@ -211,37 +211,117 @@ hipError_t gemv2(hipStream_t s, int np, const GemvP& p0, const GemvP& p1) {
   return hipGetLastError();
 }
 
-// breadth-first levels from `start` over the symmetric adjacency (adj_ptr, adj); returns the
-// number of levels, -1 if some vertex is unreached
-int bfs_levels(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, int32_t start,
-               std::vector<int32_t>& level, int32_t* last) {
+// breadth-first levels from `start` over the symmetric adjacency (ap, aj): the number of vertices
+// reached, and the lowest vertex of the last level (deterministic)
+int64_t bfs_levels(int64_t n, const std::vector<int64_t>& ap, const std::vector<int32_t>& aj, int32_t start,
+                   std::vector<int32_t>& level, int32_t* last) {
   level.assign(n, -1);
   std::vector<int32_t> frontier{start}, next;
   level[start] = 0;
-  int nl = 0;
   int64_t seen = 1;
-  while (!frontier.empty()) {
-    ++nl;
+  for (int l = 1; !frontier.empty(); ++l) {
     next.clear();
     for (int32_t v : frontier)
-      for (int64_t e = ap[v]; e < ap[v + 1]; ++e) {
-        const int32_t u = aj[e];
-        if (level[u] < 0) {
-          level[u] = nl;
-          next.push_back(u);
+      for (int64_t e = ap[v]; e < ap[v + 1]; ++e)
+        if (level[aj[e]] < 0) {
+          level[aj[e]] = l;
+          next.push_back(aj[e]);
         }
-      }
-    if (next.empty()) {
-      // lowest-index vertex of the last level: deterministic
-      *last = *std::min_element(frontier.begin(), frontier.end());
-    }
+    if (next.empty()) *last = *std::min_element(frontier.begin(), frontier.end());
     seen += (int64_t)next.size();
     frontier.swap(next);
   }
-  return seen == n ? nl : -1;
+  return seen;
 }
 
 }  // namespace
+
+// The order: with d1, d2 the distances from two pseudo-peripheral ends (s1, the last level's vertex of a search
+// from vertex 0, and s2, the last level's of a search from s1), D = d1(s2) and h = D / 2, the left
+// part {d1 < h} and the right part {d2 < D - h} share no edge (d1 + d2 >= D, and an edge changes each by
+// at most one); the rest is the middle block.  Each part is cut into blocks of consecutive levels of
+// its own search, from its end inwards, so both chains start at a corner of the mesh (a block there is
+// a whole neighbourhood of cells, not one thin layer of level sets, whose principal submatrix can be
+// singular).
+bool vk_level_order(int64_t r0, int64_t n, const int64_t* rp, const int32_t* col, int64_t min_block, int64_t min_middle,
+                    std::vector<int32_t>& blk, std::vector<int64_t>& size, int* c) {
+  // symmetric adjacency (pattern of A + A^T, no self loops)
+  std::vector<int64_t> ap(n + 1, 0);
+  for (int64_t r = 0; r < n; ++r)
+    for (int64_t e = rp[r]; e < rp[r + 1]; ++e) {
+      const int64_t q = (int64_t)col[e - rp[0]] - r0;
+      if (q < 0 || q >= n) return false;  // a coupling outside the block: the dense path reports it
+      if (q != r) {
+        ++ap[r + 1];
+        ++ap[q + 1];
+      }
+    }
+  for (int64_t r = 0; r < n; ++r) ap[r + 1] += ap[r];
+  std::vector<int32_t> aj(ap[n]);
+  std::vector<int64_t> at(ap.begin(), ap.end() - 1);
+  for (int64_t r = 0; r < n; ++r)
+    for (int64_t e = rp[r]; e < rp[r + 1]; ++e) {
+      const int64_t q = (int64_t)col[e - rp[0]] - r0;
+      if (q != r) {
+        aj[at[r]++] = (int32_t)q;
+        aj[at[q]++] = (int32_t)r;
+      }
+    }
+  std::vector<int32_t> d1, d2;
+  int32_t s1 = 0, s2 = 0, tmp = 0;
+  if (bfs_levels(n, ap, aj, 0, d1, &s1) != n || bfs_levels(n, ap, aj, s1, d1, &s2) != n ||
+      bfs_levels(n, ap, aj, s2, d2, &tmp) != n)
+    return false;
+  const int dist = d1[s2];
+  int h1 = dist / 2, h2 = dist - h1;
+  if (h1 < 1 || h2 < 1) return false;
+  // the middle block takes level sets of both sides until it has min_middle unknowns
+  std::vector<int64_t> lcnt, rcnt;
+  int64_t nmid = 0;
+  for (;;) {
+    lcnt.assign(h1, 0);
+    rcnt.assign(h2, 0);
+    nmid = 0;
+    for (int64_t v = 0; v < n; ++v) {
+      if (d1[v] < h1) ++lcnt[d1[v]];
+      else if (d2[v] < h2) ++rcnt[d2[v]];
+      else ++nmid;
+    }
+    if (nmid >= min_middle || h1 + h2 <= 2) break;
+    if (h2 >= h1) --h2;
+    else --h1;
+  }
+  if (nmid == 0) return false;
+  // consecutive levels into blocks of at least min_block unknowns, from the end inwards (a remainder
+  // joins the block before it)
+  auto group = [min_block](const std::vector<int64_t>& cnt, std::vector<int32_t>& lb, std::vector<int64_t>& bs) {
+    lb.assign(cnt.size(), 0);
+    for (size_t l = 0; l < cnt.size(); ++l) {
+      if (bs.empty() || bs.back() >= min_block) bs.push_back(0);
+      lb[l] = (int32_t)bs.size() - 1;
+      bs.back() += cnt[l];
+    }
+    if (bs.size() > 1 && bs.back() < min_block) {
+      const int64_t tail = bs.back();
+      bs.pop_back();
+      bs.back() += tail;
+      for (int32_t& b : lb) b = std::min(b, (int32_t)bs.size() - 1);
+    }
+  };
+  std::vector<int32_t> lb, rb;
+  std::vector<int64_t> ls, rs;
+  group(lcnt, lb, ls);
+  group(rcnt, rb, rs);
+  const int nl = (int)ls.size(), nb = nl + 1 + (int)rs.size();
+  size.assign(nb, 0);
+  for (int i = 0; i < nl; ++i) size[i] = ls[i];
+  size[nl] = nmid;
+  for (size_t i = 0; i < rs.size(); ++i) size[nb - 1 - i] = rs[i];
+  blk.resize(n);
+  for (int64_t v = 0; v < n; ++v) blk[v] = d1[v] < h1 ? lb[d1[v]] : (d2[v] < h2 ? nb - 1 - rb[d2[v]] : nl);
+  *c = nl;
+  return true;
+}
 
 bool vk_bt_plan(vk_level& L) {
   vk_bt& T = L.bt;
@@ -263,87 +343,10 @@ bool vk_bt_plan(vk_level& L) {
     (void)hipGetLastError();
     return false;
   }
-  // symmetric adjacency (pattern of A + A^T, no self loops)
-  std::vector<int64_t> deg(n + 1, 0);
-  for (int64_t r = 0; r < n; ++r)
-    for (int64_t e = rp[r] - e0; e < rp[r + 1] - e0; ++e) {
-      const int64_t c = (int64_t)cj[e] - r0;
-      if (c < 0 || c >= n) return false;  // a coupling outside the block: the dense path reports it
-      if (c != r) {
-        ++deg[r + 1];
-        ++deg[c + 1];
-      }
-    }
-  for (int64_t r = 0; r < n; ++r) deg[r + 1] += deg[r];
-  std::vector<int32_t> adj(deg[n]);
-  std::vector<int64_t> fill(deg.begin(), deg.end() - 1);
-  for (int64_t r = 0; r < n; ++r)
-    for (int64_t e = rp[r] - e0; e < rp[r + 1] - e0; ++e) {
-      const int64_t c = (int64_t)cj[e] - r0;
-      if (c != r) {
-        adj[fill[r]++] = (int32_t)c;
-        adj[fill[c]++] = (int32_t)r;
-      }
-    }
-  // two pseudo-peripheral ends: s1, the last level's vertex of a search from vertex 0, and s2,
-  // the last level's vertex of a search from s1; d1, d2 the distances from them.  With D =
-  // d1(s2) and h = D / 2, the left part {d1 < h} and the right part {d2 < D - h} share no edge
-  // (d1 + d2 >= D, and an edge changes each by at most one); the rest is the middle block.
-  // Each part is cut into blocks of consecutive levels of its own search, from its end inwards,
-  // so both chains start at a corner of the mesh (a block there is a whole neighbourhood of
-  // cells, not one thin layer of level sets, whose principal submatrix can be singular).
-  std::vector<int32_t> d1, d2;
-  int32_t s1 = 0, s2 = 0;
-  if (bfs_levels(n, deg, adj, 0, d1, &s1) < 0) return false;
-  if (bfs_levels(n, deg, adj, s1, d1, &s2) < 0) return false;
-  int32_t tmp = 0;
-  if (bfs_levels(n, deg, adj, s2, d2, &tmp) < 0) return false;
-  const int dist = d1[s2];
-  const int h1 = dist / 2, h2 = dist - h1;
-  if (h1 < 1 || h2 < 1) return false;
-  // part of each vertex (0 left, 1 middle, 2 right) and its level within the part
-  std::vector<int64_t> lcnt(h1, 0), rcnt(h2, 0);
-  int64_t nmid = 0;
-  for (int64_t v = 0; v < n; ++v) {
-    if (d1[v] < h1) ++lcnt[d1[v]];
-    else if (d2[v] < h2) ++rcnt[d2[v]];
-    else ++nmid;
-  }
-  // consecutive levels into blocks of at least VK_BT_MIN_BLOCK unknowns, from the end inwards
-  // (a remainder joins the block before it)
-  auto group = [](const std::vector<int64_t>& cnt, std::vector<int32_t>& lblk, std::vector<int64_t>& bs) {
-    lblk.assign(cnt.size(), 0);
-    bs.clear();
-    int64_t cur = 0;
-    for (size_t l = 0; l < cnt.size(); ++l) {
-      if (bs.empty() || cur >= VK_BT_MIN_BLOCK) {
-        bs.push_back(0);
-        cur = 0;
-      }
-      lblk[l] = (int32_t)bs.size() - 1;
-      bs.back() += cnt[l];
-      cur += cnt[l];
-    }
-    if (bs.size() > 1 && bs.back() < VK_BT_MIN_BLOCK) {
-      const int64_t tail = bs.back();
-      bs.pop_back();
-      bs.back() += tail;
-      for (size_t l = 0; l < cnt.size(); ++l)
-        if (lblk[l] == (int32_t)bs.size()) lblk[l] = (int32_t)bs.size() - 1;
-    }
-  };
-  std::vector<int32_t> lb, rb;
-  std::vector<int64_t> lsz, rsz;
-  group(lcnt, lb, lsz);
-  group(rcnt, rb, rsz);
-  if (lsz.empty() || rsz.empty() || nmid == 0) return false;
-  // the order: left blocks from s1's end, the middle, right blocks towards s2's end
-  const int nl = (int)lsz.size(), nr = (int)rsz.size();
-  const int nb = nl + 1 + nr;
-  std::vector<int64_t> bsize(nb);
-  for (int i = 0; i < nl; ++i) bsize[i] = lsz[i];
-  bsize[nl] = nmid;
-  for (int i = 0; i < nr; ++i) bsize[nb - 1 - i] = rsz[i];
+  std::vector<int32_t> blk;
+  std::vector<int64_t> bsize;
+  if (!vk_level_order(r0, n, rp.data(), cj.data(), VK_BT_MIN_BLOCK, 0, blk, bsize, &T.c)) return false;
+  const int nb = (int)bsize.size();
   int64_t smax = 0;
   for (int64_t sz : bsize) smax = std::max(smax, sz);
   if (smax > VK_BT_MAX_BLOCK) return false;
@@ -353,12 +356,10 @@ bool vk_bt_plan(vk_level& L) {
   std::vector<int64_t> pos(T.off.begin(), T.off.end() - 1);
   std::vector<int32_t> perm(n), iperm(n);
   for (int64_t v = 0; v < n; ++v) {
-    const int blk = d1[v] < h1 ? lb[d1[v]] : (d2[v] < h2 ? nb - 1 - rb[d2[v]] : nl);
-    const int64_t p = pos[blk]++;
+    const int64_t p = pos[blk[v]]++;
     perm[p] = (int32_t)v;
     iperm[v] = (int32_t)p;
   }
-  T.c = nl;
   // element offsets and the carve of the dense-inverse buffer (doubles)
   T.nb = nb;
   T.smax = smax;

@@ -482,6 +482,11 @@ hipError_t launch_block_invert_dense_any(hipStream_t s, const vk_level& L, int32
 // block-tridiagonal factorisation of a single wide block (coarse_bt.hip): plan (host, once per
 // pattern and workspace; false: the block is not suited and stays with the dense inverse),
 // factorisation (every setup) and solve x = J^{-1} b on the block's rows
+// The block-tridiagonal order of n rows from r0 by level sets from two ends of their pattern (rp: their n + 1
+// row pointers, col: the columns from rp[0] on): blocks of at least min_block unknowns, the middle
+// one c of min_middle; block of every row and sizes; false if there is none.
+bool vk_level_order(int64_t r0, int64_t n, const int64_t* rp, const int32_t* col, int64_t min_block, int64_t min_middle,
+                    std::vector<int32_t>& blk, std::vector<int64_t>& size, int* c);
 bool vk_bt_plan(vk_level& L);
 hipError_t launch_bt_factor(hipStream_t s, const vk_level& L, int32_t* status);
 hipError_t launch_bt_solve(hipStream_t s, const vk_level& L, const double* b, double* x);
