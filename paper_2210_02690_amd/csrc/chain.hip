@@ -430,10 +430,10 @@ bool vk_chain_plan(vk_level& L) {
   T.n_chained = (int)n_chained;
   T.w = take(L.J.n_rows);
   T.wa = take(L.J.n_rows);
-  T.rs = reinterpret_cast<unsigned long long*>(take(2 * n_chained));
   T.bad = reinterpret_cast<int32_t*>(take(n_chained));
   T.zero = buf + used;
   const int64_t used0 = used;
+  T.rs = reinterpret_cast<unsigned long long*>(take(2 * n_chained));
   int64_t r_used = used;  // a refinement's buffers take the chain's place
   std::vector<vk_gemm_item> r_mul[2], r_put[2];
   int chained = 0;
@@ -715,12 +715,11 @@ static hipError_t gemm_list(hipStream_t s, const vk_gemm_list& l) {
   return hipSuccess;
 }
 
-// *flag = 0 where every chained block's inverse is within `limit`
+// *flag = 0 where every chained block's inverse is within `limit` (T.rs is zero)
 static hipError_t chain_check(hipStream_t s, const vk_level& L, double limit, int32_t* flag) {
   const vk_chain& T = L.chain;
   const int64_t nr = T.rows - T.first;
   hipError_t e;
-  if ((e = launch_fill(s, 2 * (int64_t)T.n_chained, 0.0, reinterpret_cast<double*>(T.rs))) != hipSuccess) return e;
   const unsigned g = (unsigned)((nr + 3) / 4);
   chain_probe_kernel<<<g, 256, 0, s>>>(T.first, T.rows, L.J.row_ptr, L.J.col, T.jval, L.cb_e0, T.cb, T.blocks, T.w, T.wa);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -788,6 +787,7 @@ hipError_t launch_chain_invert(hipStream_t s, const vk_level& L, int32_t* status
 hipError_t launch_chain_refine(hipStream_t s, const vk_level& L, int32_t* flag) {
   const vk_chain& T = L.chain;
   hipError_t e;
+  if ((e = launch_fill(s, 2 * (int64_t)T.n_chained, 0.0, reinterpret_cast<double*>(T.rs))) != hipSuccess) return e;
   chain_defect_kernel<<<(unsigned)(T.rows - T.first), 256, 0, s>>>(T.first, L.J.row_ptr, L.J.col, T.jval, L.cb_e0, T.cb, T.blocks,
                                                                 T.rmap, T.cmap, T.bad);
   if ((e = hipGetLastError()) != hipSuccess) return e;
