@@ -1075,13 +1075,29 @@ __device__ inline double recip_f64(double a) {
   return r;
 }
 
-// The first row of largest |x| among a wavefront's rows r * 64 + lane with um[r] all ones (0: not a candidate),
-// as row block ps and lane pl, and 1 / x there; false (inv = 0) where no candidate is nonzero or the largest
-// is not finite.  One integer wavefront maximum over the high words settles nearly every step; what it leaves
-// open takes the branch: rows that share the largest high word (their low words are compared), pivots at
-// the ends of the range (divided by instead of the refined reciprocal), zeros and what is not finite.
+// a where `first`, else b, by bits: chosen as numbers out of a register array, the compiler indexes the
+// array instead, in scratch memory
+__device__ __forceinline__ double pick_f64(bool first, double a, double b) {
+  const uint64_t m = first ? ~0ull : 0ull;
+  return __builtin_bit_cast(double, (__builtin_bit_cast(uint64_t, a) & m) | (__builtin_bit_cast(uint64_t, b) & ~m));
+}
+
+// 1 / a over the whole range, for a branch that is hardly ever taken: the empty statement keeps the
+// compiler from computing the division beside the reciprocal in every step
+__device__ __forceinline__ double div_f64(double a) {
+  asm volatile("");
+  return 1.0 / a;
+}
+
+// The first row of largest |x| among a wavefront's rows r * 64 + lane with um[r] all ones (0: not a candidate), as
+// row block ps and lane pl; false where no candidate is nonzero or the largest is not finite.  normal: its
+// exponent leaves the reciprocal, and the hardware's seed for it, in the normal range.  One integer
+// wavefront maximum over the high words settles nearly every step; what it leaves open takes the
+// branch: rows that share the largest high word (their low words are compared), the ends of the range,
+// zeros and what is not finite.  (Proposing the row by 32-bit keys of 13 mantissa bits and the row took 6 % less
+// for 512 matrices of 80 or 128 rows and the same at 170, but chose among candidates 2^-13 apart.)
 template <int R>
-__device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t (&um)[R], int& ps, int& pl, double& inv) {
+__device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t (&um)[R], int& ps, int& pl, bool& normal) {
   uint32_t key[R], lk = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -1096,40 +1112,37 @@ __device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t 
     at[r] = __ballot(key[r] == mk);
     n_at += __popcll(at[r]);
   }
-  auto choose = [&] {
-    unsigned long long m = at[0];
-    ps = 0;
+  constexpr uint32_t low_end = 2u << 20, width = 0x7FBu << 20;  // of the exponents 2 .. 0x7FC
+  const uint32_t above = mk - low_end;
+  normal = above < width;
+  bool found = true;
+  if (__builtin_expect((n_at == 1 ? above : ~0u) >= width, 0)) {  // uniform
+    uint32_t low[R], ll = 0;
 #pragma unroll
-    for (int r = 1; r < R; ++r) {
-      const bool next = m == 0;
-      m = next ? at[r] : m;
-      ps = next ? r : ps;
+    for (int r = 0; r < R; ++r) {
+      low[r] = key[r] == mk ? (uint32_t)__builtin_bit_cast(uint64_t, x[r]) & um[r] : 0u;
+      ll = max(ll, low[r]);
     }
-    pl = __builtin_ctzll(m);
-    double y = x[0];
+    const uint32_t ml = wave_max_u32(ll);
+    found = (mk | ml) != 0 && (mk >> 20) != 0x7FFu;
+    unsigned long long left = ~0ull;  // zero once a row block has the row
 #pragma unroll
-    for (int r = 1; r < R; ++r) y = ps == r ? x[r] : y;
-    return readlane_f64(y, pl);
-  };
-  // mk's exponent leaves the reciprocal, and its seed, in the normal range
-  if (__builtin_expect(n_at == 1 && (mk >> 20) - 2u < 0x7FBu, 1)) {  // uniform
-    inv = recip_f64(choose());
-    return true;
+    for (int r = 0; r < R; ++r) {
+      at[r] = __ballot(um[r] != 0 && key[r] == mk && low[r] == ml) & left;
+      left = at[r] != 0 ? 0 : left;
+    }
+    at[0] |= found ? 0 : 1;
   }
-  uint32_t low[R], ll = 0;
+  // one row block is left
+  unsigned long long m = at[0];
+  ps = 0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    low[r] = key[r] == mk ? (uint32_t)__builtin_bit_cast(uint64_t, x[r]) & um[r] : 0u;
-    ll = max(ll, low[r]);
+  for (int r = 1; r < R; ++r) {
+    ps = at[r] != 0 ? r : ps;
+    m |= at[r];
   }
-  const uint32_t ml = wave_max_u32(ll);
-  ps = pl = 0;
-  inv = 0.0;
-  if ((mk | ml) == 0 || (mk >> 20) == 0x7FFu) return false;
-#pragma unroll
-  for (int r = 0; r < R; ++r) at[r] = __ballot(um[r] != 0 && key[r] == mk && low[r] == ml);
-  inv = 1.0 / choose();
-  return true;
+  pl = __builtin_ctzll(m);
+  return found;
 }
 
 // ---------------------------------------------------------------------------
@@ -1149,17 +1162,13 @@ __device__ __forceinline__ bool find_pivot(const double (&x)[R], const uint32_t 
 // W'[i][c] = W[i][c] - W[i][k] W[p][c] / W[p][k], W'[p][c] = W[p][c] / W[p][k]).  After all steps
 // J_K^{-1}[k][q_j] = W[q_k][j], written out through LDS one 16-column block at a time so the
 // stores of a column are contiguous.
-// What bounds it: the chain of pivot steps in the panel wavefront, 600 (two rows a lane) to 750 cycles
+// What bounds it: the chain of pivot steps in the panel wavefront, 700 (two rows a lane) to 880 cycles
 // (three) a step, and at 170 rows, nearly as long, the tile wavefronts' 121 matrix products a panel.
 // FP64 matrix products hold up the FP64 instructions of other wavefronts on their SIMD, so the panel
 // wavefront has one to itself; the tile wavefronts find their pivot rows in a per-row table.
-// Measured (per matrix of 512): 170 rows 0.60 -> 0.50 us, 128 rows 0.36 -> 0.27 us, 80 rows 0.12 ->
-// 0.10 us; a single one of 170 rows 143 -> 116 us.
-// Pivot choice: the first row of largest |a| among the rows not yet pivotal (find_pivot), but with KEYED (n_K =
-// 170) compared on a 32-bit key (|a|'s exponent and 13 leading mantissa bits, then 255 - row), so one
-// integer wavefront maximum gives the row as well: candidates within a relative 2^-13 count as ties and
-// the lowest row wins (the first maximal row of the LU pivot sequence whenever the maximum is unique
-// to that precision; the multipliers stay below 1 + 2^-13 in magnitude).
+// Measured (per matrix of 512): 170 rows 0.60 -> 0.50 us, 128 rows 0.36 -> 0.29 us, 80 rows 0.12 ->
+// 0.11 us; a single one of 170 rows 143 -> 118 us.
+// Pivot choice: the first row of largest |a| among the rows not yet pivotal (find_pivot).
 // The FP64 MFMA (16 x 16 x 4) computes D(m, n) = sum_k A(m, k) B(k, n) + C: lane l supplies
 // A(l % 16, l / 16) and B(l / 16, l % 16), and accumulator element v holds D(4 v + l / 16, l % 16),
 // so a tile's lane l owns rows 4 v + l / 16 of column l % 16.  Tile indices are compile-time
@@ -1253,7 +1262,7 @@ __global__ __launch_bounds__(512) void patch_map_kernel(const int64_t* __restric
   for (int e = tid; e < ME / 4; e += NT) out[e] = reinterpret_cast<const uint64_t*>(sm)[e];
 }
 
-template <int P, int T, int SRC, bool KEYED>
+template <int P, int T, int SRC>
 __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_setup_mfma_kernel(
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
     const int32_t* __restrict__ cell_dofs, const uint64_t* __restrict__ pmap, int32_t n_K, void* inv_out, int32_t ld_,
@@ -1413,13 +1422,10 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
   __syncthreads();
   if (w == PW) {
     // ---- the panel wavefront ----
-    // per row block: all ones while the lane's row may still become a pivot, and 255 - row
-    uint32_t um[R], rid[R];
+    // per row block: all ones while the lane's row may still become a pivot
+    uint32_t um[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      um[r] = r * 64 + lane < N ? 0xFFFFFFFFu : 0u;
-      rid[r] = (uint32_t)(255 - 64 * r - lane);
-    }
+    for (int r = 0; r < R; ++r) um[r] = r * 64 + lane < N ? 0xFFFFFFFFu : 0u;
     bool singular = false;
     int old1 = -1, old2 = -1;  // lane t: the places in rowt of the last two panels' step t
     double pr[R][NB];  // the current panel's columns, the lane's rows r * 64 + lane
@@ -1435,29 +1441,12 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
         const int k = k0 + t;
         // skip, uniform: a padding column of the last panel, no nonzero candidate, or a non-finite
         // largest one (the step is then a no-op on the other columns: its row of B stays zero)
-        bool skip;
+        double x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = pr[r][t];
+        bool normal;
         int ps, pl;
-        double inv = 0.0;
-        if constexpr (KEYED) {
-          // 32-bit pivot keys: |a|'s exponent and 13 leading mantissa bits, then 255 - row (0 for
-          // rows already pivotal), so one integer wavefront maximum gives the row as well
-          uint32_t key = 0;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, pr[r][t]) >> 32);
-            key = max(key, (((hi & 0x7FFFFF80u) << 1) | rid[r]) & um[r]);
-          }
-          const uint32_t mk = wave_max_u32(key);
-          const int p = 255 - (int)(mk & 0xFFu);
-          skip = k >= N || (mk >> 8) == 0 || (mk >> 21) == 0x7FFu || p >= N;
-          pl = p & 63;
-          ps = p >> 6;
-        } else {
-          double x[R];
-#pragma unroll
-          for (int r = 0; r < R; ++r) x[r] = pr[r][t];
-          skip = !find_pivot<R>(x, um, ps, pl, inv) || k >= N;
-        }
+        const bool skip = !find_pivot<R>(x, um, ps, pl, normal) || k >= N;
         if (skip && k < N) singular = true;
         const int p = ps * 64 + pl;
         // the pivot row's entries: every lane selects its row of block ps (uniform), lane pl's
@@ -1467,10 +1456,11 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
         for (int c = 0; c < NB; ++c) {
           double x = pr[0][c];
 #pragma unroll
-          for (int r = 1; r < R; ++r) x = (ps == r) ? pr[r][c] : x;
+          for (int r = 1; r < R; ++r) x = pick_f64(ps == r, pr[r][c], x);
           prow[c] = readlane_f64(x, pl);
         }
-        if (KEYED) inv = recip_f64(prow[t]);
+        double inv = recip_f64(prow[t]);
+        if (__builtin_expect(!normal, 0)) inv = div_f64(prow[t]);  // uniform
         inv = skip ? 0.0 : inv;
 #pragma unroll
         for (int c = 0; c < NB; ++c) prow[c] = (c == t) ? inv : prow[c] * inv;
@@ -1678,7 +1668,7 @@ __global__ __launch_bounds__((MfCfg<T, (SRC != SRC_SEARCH)>::NT)) void patch_set
 // with one other patch.  A row per lane with the pivot row broadcast through LDS reads 8 n bytes per
 // lane and step, four times what a CU's LDS returns in the time of the FMAs: that kernel (variant 2)
 // takes 719 us for the 5 632 patches 63 wide of the 176 x 32 channel and 145 us for 1 408 patches 42
-// wide, this one 194 and 36 us (88 patches: 179 -> 42 and 111 -> 23 us).
+// wide, this one 203 and 37 us (88 patches: 179 -> 43 and 111 -> 24 us).
 // ---------------------------------------------------------------------------
 template <int P, int T>
 __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
@@ -1755,16 +1745,18 @@ __global__ __launch_bounds__(64, T == 4 ? 2 : 3) void patch_setup_wave_kernel(
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       const int k = k0 + t;
+      bool normal;
       int ps, pl;
-      double inv;
       const double x[1] = {pr[t]};
       const uint32_t um1[1] = {um};
       // uniform: a padding column, no nonzero candidate, or a non-finite largest one
-      const bool skip = !find_pivot<1>(x, um1, ps, pl, inv) || k >= n;
+      const bool skip = !find_pivot<1>(x, um1, ps, pl, normal) || k >= n;
       singular = singular || (skip && k < n);
       double prow[NB];
 #pragma unroll
       for (int c = 0; c < NB; ++c) prow[c] = readlane_f64(pr[c], pl);
+      double inv = recip_f64(prow[t]);
+      if (__builtin_expect(!normal, 0)) inv = div_f64(prow[t]);  // uniform
       inv = skip ? 0.0 : inv;
 #pragma unroll
       for (int c = 0; c < NB; ++c) prow[c] = (c == t) ? inv : prow[c] * inv;
@@ -1881,8 +1873,8 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #define VK_WAVE_CASE(TT)                                                                                   \
   patch_setup_wave_kernel<P, TT><<<L.n_cells, 64, 0, s>>>(J.row_ptr, J.val, L.cell_dofs, pm, L.n_K, L.inv, \
                                                           L.ld, L.cell_stride, status)
-#define VK_MFMA_CASE(TT, KEYED)                                                                         \
-  patch_setup_mfma_kernel<P, TT, SRC_MAP, KEYED><<<L.n_cells, MfCfg<TT, true>::NT, 0, s>>>(             \
+#define VK_MFMA_CASE(TT)                                                                          \
+  patch_setup_mfma_kernel<P, TT, SRC_MAP><<<L.n_cells, MfCfg<TT, true>::NT, 0, s>>>(              \
       J.row_ptr, J.col, J.val, L.cell_dofs, pm, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status)
   if (mapped) {
     if (L.n_K <= 64) {
@@ -1895,16 +1887,13 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
       return hipGetLastError();
     }
     switch (mfma_tiles(L.n_K)) {
-      case 5: VK_MFMA_CASE(5, false); return hipGetLastError();
-      case 6: VK_MFMA_CASE(6, false); return hipGetLastError();
-      case 7: VK_MFMA_CASE(7, false); return hipGetLastError();
-      case 8: VK_MFMA_CASE(8, false); return hipGetLastError();
-      case 9: VK_MFMA_CASE(9, false); return hipGetLastError();
-      case 10: VK_MFMA_CASE(10, false); return hipGetLastError();
-      case 11:
-        if (L.n_K == 170) VK_MFMA_CASE(11, true);
-        else VK_MFMA_CASE(11, false);
-        return hipGetLastError();
+      case 5: VK_MFMA_CASE(5); return hipGetLastError();
+      case 6: VK_MFMA_CASE(6); return hipGetLastError();
+      case 7: VK_MFMA_CASE(7); return hipGetLastError();
+      case 8: VK_MFMA_CASE(8); return hipGetLastError();
+      case 9: VK_MFMA_CASE(9); return hipGetLastError();
+      case 10: VK_MFMA_CASE(10); return hipGetLastError();
+      case 11: VK_MFMA_CASE(11); return hipGetLastError();
       default: break;
     }
   }
@@ -1932,7 +1921,7 @@ hipError_t setup_rows(hipStream_t s, const vk_csr& J, const vk_group& L, int32_t
 #undef VK_WIDE_CASE
     case 170:
       if (mfma)
-        patch_setup_mfma_kernel<P, 11, SRC_SEARCH, true><<<L.n_cells, MfCfg<11, false>::NT, 0, s>>>(
+        patch_setup_mfma_kernel<P, 11, SRC_SEARCH><<<L.n_cells, MfCfg<11, false>::NT, 0, s>>>(
             J.row_ptr, J.col, J.val, L.cell_dofs, nullptr, L.n_K, L.inv, L.ld, L.cell_stride, nullptr, status);
       else
         patch_setup_wide_kernel<P, 170><<<L.n_cells, 64 * WideCfg<170>::NW, 0, s>>>(
@@ -2183,7 +2172,7 @@ hipError_t gemv_prec(hipStream_t s, const vk_group& L, int cpb, const double* r,
 
 template <int T>
 static hipError_t invert_items(hipStream_t s, int n_items, const vk_dense_item* items, int32_t* status) {
-  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE, false><<<(unsigned)n_items, MfCfg<T, true>::NT, 0, s>>>(
+  patch_setup_mfma_kernel<VK_F64, T, SRC_DENSE><<<(unsigned)n_items, MfCfg<T, true>::NT, 0, s>>>(
       nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, 0, items, status);
   return hipGetLastError();
 }
