@@ -16,10 +16,11 @@
 //   G_ii = S_i^{-1} - X_i G_{i+1,i},  G_jj = T_j^{-1} - Y_j G_{j-1,j},  G_ij = -X_i G_{i+1,j},
 //   G_ji = -Y_j G_{j-1,i},   Z_i = L_{i+1} S_i^{-1},  W_j = U_{j-1} T_j^{-1},
 // two launches of matrix-core products a step.  The solve stays one product with the dense inverse.
-// Measured, dense -> chain: 592 unknowns (88 x 16, k = 1) 1.14 -> 0.37 ms, 888 (176 x 32, k = 2) 1.79 -> 0.52 ms,
-// 2 060 (88 x 16, Q4) 7.15 -> 1.43 ms, 3 213 (48 x 8 x 8, k = 2) 13.5 -> 4.0 ms, the blocks of 64 systems 17 ->
-// 6.5 ms.  What bounds it now is the chain of pivot steps inside the S_i, 0.5 us each, and for single
-// blocks the launches between them.
+// Measured in a setup, beside the patch inversions and with the check below, dense -> chain: 592 unknowns (88
+// x 16, k = 1) 1.21 -> 0.33 ms, 888 (176 x 32, k = 2) 2.04 -> 0.56 ms, 2 060 (88 x 16, Q4) 7.7 -> 1.46 ms, 3 213 (48 x
+// 8 x 8, k = 2) 20.1 -> 4.2 ms, the three levels of 64 systems 5.1, 29.6 and 18.5 -> 1.3, 8.1 and 3.7 ms.  What
+// bounds it now is the chain of pivot steps inside the S_i, 0.5 to 0.7 us each, and for single blocks
+// the launches between them.
 //
 // Pivots are sought inside a piece only, so a regular matrix can meet a singular or badly
 // conditioned one.  Each inverse is therefore checked; one that fails is refined by a step of Newton's
@@ -291,7 +292,7 @@ int64_t piece_width(int64_t s) {
 }
 
 // A block is chained where the estimated time of its chain is below 0.8 of the dense inversion's.  The
-// estimates (us): a piece in the register-resident kernel (64 rows 25, 128 rows 65, 176 rows 118) and its
+// estimates (us): a piece in the register-resident kernel (64 rows 27, 128 rows 70, 176 rows 121) and its
 // four launches; 35 a step for the products; the dense inversion's 16-column panels with their updates
 // (20 + 6 and the outer updates: 888 rows 1.8 ms).
 double chain_us(int64_t s) {
