@@ -344,7 +344,9 @@ double vk_spmv_bytes(vk_ctx* ctx, int32_t level);
  * of |G| |J_0| |v| in its block, about what Gauss-Jordan with pivoting over the
  * whole block leaves.  One that exceeds it is refined, G + G (I - J_0 G), up to
  * 64 u, or else its level is inverted by Gauss-Jordan, both with the
- * setup's values; the next setup takes the structure again.  Blocks without such a structure, and every block under mode 1, get
+ * setup's values; the next setup takes the structure again.  The workspace holds
+ * 1.5 to 2 n^2 doubles and 160 KB for every block of n in that range, whether its
+ * pattern then has the structure or not.  Blocks without such a structure, and every block under mode 1, get
  * the dense inverse by Gauss-Jordan with partial pivoting.  All
  * compute J_0^{-1} b up to rounding; a singular block is reported by the first
  * solve either way.  vk_get_coarse_inverse needs the dense inverse.  Setup must
